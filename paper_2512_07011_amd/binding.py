@@ -262,7 +262,7 @@ def bsfa_calibrate(q: torch.Tensor, k: torch.Tensor, target_skip_fractions: Sequ
     _check(lib().bsfa_calibrate(ctypes.byref(p), q.data_ptr(), k.data_ptr(), int(bool(causal)), fr, n, outp,
                                 workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                 ctypes.c_void_p(s.cuda_stream)))
-    return torch.tensor(list(outp), dtype=torch.float32).view(n, q.shape[2])
+    return torch.frombuffer(outp, dtype=torch.float32).clone().view(n, q.shape[2])
 
 
 def bsfa_calibrate_noalloc(q: torch.Tensor, k: torch.Tensor, target_skip_fractions: Sequence[float],
@@ -323,7 +323,7 @@ def bsfa_calibrate_topk(samples, ks: Sequence[int], causal: bool = True, block_m
                                          out, ws.data_ptr(), ws.numel(), ctypes.c_void_p(s.cuda_stream)))
         done += q.shape[0]
     q0 = samples[0][0]
-    return torch.tensor(list(out), dtype=torch.float32).view(n, q0.shape[2], n_tiles(q0.shape[1], block_m))
+    return torch.frombuffer(out, dtype=torch.float32).clone().view(n, q0.shape[2], n_tiles(q0.shape[1], block_m))
 
 
 def bsfa_query_build():

@@ -7,9 +7,9 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <functional>
+#include <memory>
 #include <mutex>
-#include <vector>
+#include <new>
 
 namespace {
 
@@ -149,33 +149,6 @@ size_t bsfa_calibrate_workspace_bytes(const bsfa_problem *p)
     // block-maximum dump | selection area | per-level results, each 256-byte aligned
     return dump + bsfa::select_area_bytes(p->n_q_heads) + (size_t)bsfa::kMaxLevels * p->n_q_heads * sizeof(float) + 4 * 256
            + (p->qk_fp8 ? k8_bytes(p) + 256 : 0);           // ... | fp8 K tiles
-}
-
-// Shared front half of the calibration entry points: checks, score / block-maximum kernel,
-// copy of the [batch][hq][mq][mkv] block maxima (NaN where not gateable) to the host.
-static bsfa_status block_maxima_to_host(const bsfa_problem *p, const void *q, const void *k, int causal,
-                                        void *workspace, size_t workspace_bytes, void *hip_stream,
-                                        std::vector<float> &host, bsfa::FwdParams &fp)
-{
-    if (!aligned16(q) || !aligned16(k)) return fail(BSFA_ERR_SHAPE, "q and k must be 16-byte aligned");
-    const size_t need = bsfa_calibrate_workspace_bytes(p);
-    if (!workspace || workspace_bytes < need)
-        return fail(BSFA_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace ? workspace_bytes : (size_t)0);
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    fill_params(fp, p, causal);
-    fp.q = static_cast<const uint16_t *>(q);
-    fp.k = static_cast<const uint16_t *>(k);
-    fp.block_max = reinterpret_cast<float *>((reinterpret_cast<uintptr_t>(workspace) + 255) & ~(uintptr_t)255);
-    fp.tau = nullptr;                 // the score half takes no decisions and reads no thresholds
-    fp.tau_per_tile = 0;
-    fp.tau_tiles = 1;
-    hipError_t e = bsfa::launch_forward(fp, p->head_dim, p->block_m, true, stream);
-    if (e != hipSuccess) return fail(BSFA_ERR_HIP, "calibration launch failed: %s", hipGetErrorString(e));
-    host.resize((size_t)p->batch * p->n_q_heads * fp.mq * fp.mkv);
-    e = hipMemcpyAsync(host.data(), fp.block_max, host.size() * sizeof(float), hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) return fail(BSFA_ERR_HIP, "calibration copy failed: %s", hipGetErrorString(e));
-    return BSFA_OK;
 }
 
 // Shared body of the per-head calibration entry points: argument checks, the score / block-maximum
@@ -320,39 +293,56 @@ bsfa_status bsfa_calibrate_topk(const bsfa_problem *p, const void *q, const void
     if (samples_done < 0) return fail(BSFA_ERR_SHAPE, "samples_done must be non-negative");
     for (int l = 0; l < n_levels; ++l)
         if (ks[l] < 0) return fail(BSFA_ERR_SHAPE, "k #%d = %d is negative", l, ks[l]);
-    std::vector<float> host;
+    if (!aligned16(q) || !aligned16(k)) return fail(BSFA_ERR_SHAPE, "q and k must be 16-byte aligned");
+    const size_t need = bsfa_calibrate_workspace_bytes(p);
+    if (!workspace || workspace_bytes < need)
+        return fail(BSFA_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace ? workspace_bytes : (size_t)0);
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     bsfa::FwdParams fp;
-    s = block_maxima_to_host(p, q, k, causal, workspace, workspace_bytes, hip_stream, host, fp);
-    if (s != BSFA_OK) return s;
+    fill_params(fp, p, causal);
+    fp.q = static_cast<const uint16_t *>(q);
+    fp.k = static_cast<const uint16_t *>(k);
+    fp.block_max = reinterpret_cast<float *>(up256(reinterpret_cast<uintptr_t>(workspace)));
+    fp.tau = nullptr;                 // the score half takes no decisions and reads no thresholds
+    fp.tau_per_tile = 0;
+    fp.tau_tiles = 1;
+    hipError_t e = bsfa::launch_forward(fp, p->head_dim, p->block_m, true, stream);
+    if (e != hipSuccess) return fail(BSFA_ERR_HIP, "calibration launch failed: %s", hipGetErrorString(e));
 
-    // per (head, query tile): k-th largest gateable block maximum of each sample (= batch element),
-    // folded into the running mean over samples
-    const size_t mq = (size_t)fp.mq, mkv = (size_t)fp.mkv;
-    std::vector<float> vals;
-    for (int b = 0; b < p->batch; ++b) {
-        const double done = (double)samples_done + b;
-        for (int h = 0; h < p->n_q_heads; ++h)
-            for (size_t i = 0; i < mq; ++i) {
-                const float *src = host.data() + (((size_t)b * p->n_q_heads + h) * mq + i) * mkv;
-                vals.clear();
-                for (size_t x = 0; x < mkv; ++x)
-                    if (!std::isnan(src[x])) vals.push_back(src[x]);
-                const size_t avail = vals.size();
-                for (int l = 0; l < n_levels; ++l) {
-                    const size_t kk = (size_t)ks[l];
-                    float t;
-                    if (avail <= kk) t = -INFINITY;               // keeps min(k, A) = A blocks
-                    else if (kk == 0) t = INFINITY;
-                    else {
-                        std::nth_element(vals.begin(), vals.begin() + (kk - 1), vals.end(), std::greater<float>());
-                        t = vals[kk - 1];
-                    }
-                    float &dst = thresholds_out[((size_t)l * p->n_q_heads + h) * mq + i];
+    // per (sample, head, query tile): the k-th largest gateable block maximum, selected on the GPU; only the
+    // results travel to the host (the whole dump and a selection there took 2.3 ms per 8K sample of 32 heads,
+    // eight times the score kernel).  They pass through the workspace's selection area, so a chunk of levels
+    // (and of rows, should one level not fit) at a time.
+    const long rows = (long)p->batch * p->n_q_heads * fp.mq, per_sample = (long)p->n_q_heads * fp.mq;
+    const long cap = (long)(bsfa::select_area_bytes(p->n_q_heads) / sizeof(float));
+    float *const out_dev = reinterpret_cast<float *>(up256(reinterpret_cast<uintptr_t>(fp.block_max) + (size_t)rows * fp.mkv * sizeof(float)));
+    const long n_rows_max = std::min(rows, cap);
+    const int n_lv_max = (int)std::min<long>(std::min<long>(bsfa::kTopkLevels, n_levels), cap / n_rows_max);
+    std::unique_ptr<float[]> host(new (std::nothrow) float[(size_t)n_lv_max * n_rows_max]);
+    if (!host) return fail(BSFA_ERR_HIP, "no host memory for %ld results", n_lv_max * n_rows_max);
+    for (long row0 = 0; row0 < rows; row0 += n_rows_max)
+        for (int l0 = 0; l0 < n_levels; l0 += n_lv_max) {
+            const long n_rows = std::min(n_rows_max, rows - row0);
+            const int n_lv = std::min(n_lv_max, n_levels - l0);
+            bsfa::TopkLevels lv;
+            memset(&lv, 0, sizeof(lv));
+            memcpy(lv.k, ks + l0, (size_t)n_lv * sizeof(int32_t));
+            e = bsfa::launch_topk(fp.block_max, fp.mkv, row0, n_rows, lv, n_lv, out_dev, stream);
+            if (e != hipSuccess) return fail(BSFA_ERR_HIP, "selection launch failed: %s", hipGetErrorString(e));
+            e = hipMemcpyAsync(host.get(), out_dev, (size_t)n_lv * n_rows * sizeof(float), hipMemcpyDeviceToHost, stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(stream);
+            if (e != hipSuccess) return fail(BSFA_ERR_HIP, "calibration copy failed: %s", hipGetErrorString(e));
+            // folded into the running mean over samples (= batch elements), in sample order
+            for (int l = 0; l < n_lv; ++l)
+                for (long r = 0; r < n_rows; ++r) {
+                    const long b = (row0 + r) / per_sample;
+                    const double done = (double)samples_done + b;
+                    const float t = host[(size_t)l * n_rows + r];
+                    float &dst = thresholds_out[(size_t)(l0 + l) * per_sample + (row0 + r - b * per_sample)];
                     if (done == 0.0 || std::isinf(t)) dst = t;
                     else dst = (float)(((double)dst * done + (double)t) / (done + 1.0));
                 }
-            }
-    }
+        }
     return BSFA_OK;
 }
 

@@ -55,6 +55,17 @@ size_t select_area_bytes(int hq);
 hipError_t launch_select(const float *dump, long per_head, int batch, int hq, const SelectLevels &lv, int n_levels,
                          void *area, float *out_dev, hipStream_t stream);
 
+// ---- per-row top-k of the block maxima on the GPU (bsfa_select.hip) ------------------------------
+constexpr int kTopkLevels = 64;       // levels per launch
+struct TopkLevels {
+    int32_t k[kTopkLevels];           // numbers of retained blocks, passed to the kernel by value
+};
+// dump: DEVICE [rows][mkv] block maxima, NaN = not gateable.  out_dev: DEVICE [n_lv][n_rows]: for the rows
+// row0 .. row0 + n_rows - 1 the k-th largest of the non-NaN values, -inf where there are at most k, +inf
+// for k = 0.  Enqueues on stream.
+hipError_t launch_topk(const float *dump, int mkv, long row0, long n_rows, const TopkLevels &lv, int n_lv, float *out_dev,
+                       hipStream_t stream);
+
 // ---- matrix-instruction rate probe (bsfa_probe.hip) --------------------------------------------
 constexpr int kProbeThreads = 512;        // 8 waves per workgroup: two per SIMD, as the forward kernel runs
 constexpr int kProbeMfmaPerIter = 16;     // 32x32x16 MFMAs per wave and iteration

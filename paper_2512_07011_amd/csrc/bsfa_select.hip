@@ -1,4 +1,5 @@
-// Per-head order statistics of block maxima on the GPU (the selection half of bsfa_calibrate).
+// Order statistics of block maxima on the GPU: per head (the selection half of bsfa_calibrate) and per
+// query tile (that of bsfa_calibrate_topk, at the end of this file).
 //
 // Input: the block-maximum dump of the score kernel, [batch][hq][per_head] floats with NaN where a
 // block is not gateable.  For every query head h (all batch elements pooled) and every level l with
@@ -179,6 +180,54 @@ __global__ void __launch_bounds__(256) scan_kernel(const uint32_t *hist0, uint32
     }
 }
 
+// k-th largest value of every row of the dump, for the levels of one chunk: one wave per row.  The row's
+// ordered keys (NaN: 0, below every value) stay in registers, E to a lane, and the key is built from its top
+// bit down: a bit stays set if at least k keys reach the candidate (32 steps of E compares whose ballots are
+// counted on the scalar side; no LDS, no memory).  E = 0: rows too long for that are read again in every step.
+template <int E>
+__global__ void __launch_bounds__(256) topk_kernel(const float *dump, int mkv, long row0, long n_rows, TopkLevels lv, int n_lv, float *out)
+{
+    const long r = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r >= n_rows) return;
+    const int lane = threadIdx.x & 63;
+    const float *src = dump + (size_t)(row0 + r) * mkv;
+    auto key_at = [&](int x) {
+        const float v = x < mkv ? src[x] : NAN;
+        return v == v ? ordered_key(v) : 0u;
+    };
+    uint32_t key[E > 0 ? E : 1];
+    if constexpr (E > 0) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) key[e] = key_at(e * 64 + lane);
+    }
+    auto count = [&](uint32_t least) {                // keys >= least (wave-uniform)
+        int n = 0;
+        if constexpr (E > 0) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) n += __popcll(__builtin_amdgcn_ballot_w64(key[e] >= least));
+        } else {
+            for (int x = 0; x < mkv; x += 64) n += __popcll(__builtin_amdgcn_ballot_w64(key_at(x + lane) >= least));
+        }
+        return n;
+    };
+    const int avail = count(1u);
+    for (int l = 0; l < n_lv; ++l) {
+        const int k = lv.k[l];
+        float t;
+        if (avail <= k) t = -INFINITY;                // keeps min(k, A) = A blocks
+        else if (k == 0) t = INFINITY;
+        else {
+            uint32_t found = 0u;
+            for (int bit = 31; bit >= 0; --bit) {
+                const uint32_t cand = found | (1u << bit);
+                if (count(cand) >= k) found = cand;
+            }
+            t = key_value(found);
+        }
+        if (lane == 0) out[(size_t)l * n_rows + r] = t;
+    }
+}
+
 }  // namespace
 
 size_t select_area_bytes(int hq)
@@ -209,6 +258,20 @@ hipError_t launch_select(const float *dump, long per_head, int batch, int hq, co
         hipLaunchKernelGGL((histn_kernel<2>), grid_v, dim3(kHistThreads), 0, stream, dump, per_head, hq, n_lv, state, hist);
         hipLaunchKernelGGL((scan_kernel<2>), grid_s, dim3(256), 0, stream, hist0, hist, hq, lv, l0, state, out_dev);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_topk(const float *dump, int mkv, long row0, long n_rows, const TopkLevels &lv, int n_lv, float *out_dev,
+                       hipStream_t stream)
+{
+    if (n_lv < 1 || n_lv > kTopkLevels || mkv < 1 || row0 < 0 || n_rows < 1 || (n_rows + 3) / 4 > 0x7fffffffL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((n_rows + 3) / 4));
+    // as many registers as the row needs: 8K, 32K, 128K and 256K tokens; longer rows are not kept
+    if (mkv <= 64 * 2) hipLaunchKernelGGL((topk_kernel<2>), grid, dim3(256), 0, stream, dump, mkv, row0, n_rows, lv, n_lv, out_dev);
+    else if (mkv <= 64 * 8) hipLaunchKernelGGL((topk_kernel<8>), grid, dim3(256), 0, stream, dump, mkv, row0, n_rows, lv, n_lv, out_dev);
+    else if (mkv <= 64 * 32) hipLaunchKernelGGL((topk_kernel<32>), grid, dim3(256), 0, stream, dump, mkv, row0, n_rows, lv, n_lv, out_dev);
+    else if (mkv <= 64 * 64) hipLaunchKernelGGL((topk_kernel<64>), grid, dim3(256), 0, stream, dump, mkv, row0, n_rows, lv, n_lv, out_dev);
+    else hipLaunchKernelGGL((topk_kernel<0>), grid, dim3(256), 0, stream, dump, mkv, row0, n_rows, lv, n_lv, out_dev);
     return hipGetLastError();
 }
 

@@ -430,3 +430,29 @@ def test_fp8_score_product(oracle, hq, hkv, n):
     with pytest.raises(binding.BsfaError) as e:
         binding.bsfa_forward(q, k, v, tau.to(DEV), qk_fp8=True, workspace=None)
     assert e.value.status == -5
+
+
+@pytest.mark.parametrize("b, n, bm, levels", [
+    (1, 8192, 128, 3), (1, 8256, 64, 70), (1, 32832, 128, 2),    # rows of 128, 129 and 513 blocks
+    (1, 131136, 128, 2), (1, 262208, 128, 70),                   # 2049 blocks; 4097: longer than a wave's registers
+    (5000, 128, 32, 2),                                          # more rows of a head than one chunk of results holds
+])
+def test_topk_selection_on_all_row_lengths(b, n, bm, levels):
+    """bsfa_calibrate_topk's selection against a sort of the kernel's own block maxima: equal bit for bit on one
+    sample, the fp64 running mean over samples otherwise."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    q, k = (torch.randn(b, n, 1, 64, generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    mkv = -(-n // 64)
+    ks = [0, 1] + [max(1, mkv * (x + 1) // levels) for x in range(levels - 2)] if levels > 2 else [1, mkv // 3 + 1]
+    got = binding.bsfa_calibrate_topk([(q, k)], ks, block_m=bm)
+    _, st = run_gpu(q, k, k, torch.full((1,), float("-inf"), device=DEV), bm, 64)
+    x = st.block_max[:, 0]                                       # [B, MQ, MKV]
+    avail = (~x.isnan()).sum(-1)
+    x = torch.sort(x.nan_to_num(nan=float("-inf")), dim=-1, descending=True)[0]
+    for l, kk in enumerate(ks):
+        want = x[..., min(max(kk, 1), mkv) - 1] if kk else torch.full_like(x[..., 0], float("inf"))
+        want = torch.where(avail > kk, want, float("-inf")).cpu()
+        mean = want[0].clone()
+        for s in range(1, b):
+            mean = torch.where(want[s].isinf(), want[s], ((mean.double() * s + want[s].double()) / (s + 1.0)).float())
+        assert torch.equal(got[l, 0], mean)
