@@ -665,7 +665,7 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
     }
 }
 
-__global__ void zero_counts_kernel(unsigned long long *c, int n)
+static __global__ void zero_counts_kernel(unsigned long long *c, int n)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < n) c[t] = 0ull;
@@ -758,7 +758,7 @@ static hipError_t launch_k(const FwdParams &p, bool calib, hipStream_t stream, l
 }
 
 template <int D, int NWH, int HP, int KR>
-static hipError_t launch_t(const FwdParams &p, bool calib, hipStream_t stream)
+hipError_t launch_t(const FwdParams &p, bool calib, hipStream_t stream)
 {
     const int pairs = p.batch * p.hkv;
     const int gsub = p.group / HP;
@@ -793,6 +793,18 @@ static hipError_t launch_t(const FwdParams &p, bool calib, hipStream_t stream)
     return p.f16 ? launch_k<D, NWH, HP, KR, true, false, false>(p, calib, stream, grid) : launch_k<D, NWH, HP, KR, false, false, false>(p, calib, stream, grid);
 }
 
+// The instantiations are spread over several translation units, compiled side by side from this one file:
+// BSFA_PART says which of them this one holds (0: the dispatch, none of them).
+#define BSFA_SHAPES_1(X) X(128, 4, 2, 5)
+#define BSFA_SHAPES_2(X) X(64, 4, 2, 5) X(64, 4, 1, 3)
+#define BSFA_SHAPES_3(X) X(128, 4, 1, 2)
+#define BSFA_SHAPES_4(X) X(128, 1, 1, 2) X(64, 1, 1, 2)
+#define BSFA_SHAPES_5(X) X(128, 2, 1, 2) X(64, 2, 1, 2)
+#define BSFA_EXTERN(D, N, H, K) extern template hipError_t launch_t<D, N, H, K>(const FwdParams &, bool, hipStream_t);
+#define BSFA_DEFINE(D, N, H, K) template hipError_t launch_t<D, N, H, K>(const FwdParams &, bool, hipStream_t);
+#if BSFA_PART == 0
+BSFA_SHAPES_1(BSFA_EXTERN) BSFA_SHAPES_2(BSFA_EXTERN) BSFA_SHAPES_3(BSFA_EXTERN) BSFA_SHAPES_4(BSFA_EXTERN) BSFA_SHAPES_5(BSFA_EXTERN)
+
 bool shape_supported(int head_dim, int block_m, int block_n)
 {
     if (block_n != kBlockN) return false;
@@ -818,5 +830,16 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
 #undef BSFA_CASE
     return hipErrorInvalidValue;
 }
+#elif BSFA_PART == 1
+BSFA_SHAPES_1(BSFA_DEFINE)
+#elif BSFA_PART == 2
+BSFA_SHAPES_2(BSFA_DEFINE)
+#elif BSFA_PART == 3
+BSFA_SHAPES_3(BSFA_DEFINE)
+#elif BSFA_PART == 4
+BSFA_SHAPES_4(BSFA_DEFINE)
+#elif BSFA_PART == 5
+BSFA_SHAPES_5(BSFA_DEFINE)
+#endif
 
 }  // namespace bsfa
