@@ -83,12 +83,11 @@ typedef struct {
                                      beyond seqlens[b] are left untouched, query tiles beyond it
                                      get NaN block maxima, an empty skip mask and add nothing to
                                      counts. */
-    int32_t single_head_groups;   /* optional tuning knob, 0 by default: workgroups handle two query heads
-                                     of a GQA group together when the group size is even (one K/V
-                                     stream in LDS feeds both; fastest on the dense path, by ~2.5 %).
-                                     1: one query head per workgroup — the heads' skip decisions no longer
-                                     share a barrier, which measures ~1.5 % faster at 50 % skip and 4-7 %
-                                     faster at 90 % skip (128K tokens).  Results are identical either way. */
+    int32_t single_head_groups;   /* optional tuning knob, 0 by default: the library decides how many query heads of
+                                     a GQA group one workgroup handles together (their K/V stream in LDS is then
+                                     shared): up to four with small tiles, with block_m = 128 one, or two on
+                                     long sequences.
+                                     1: always one.  Results are identical either way. */
     int32_t gate_mode;            /* optional, bsfa_forward only.  0: the paper's gate (block maximum against the
                                      threshold, Section 4.1).  1: the running-maximum predicate the paper
                                      describes for SpargeAttention's in-kernel filter (Section 3), provided for

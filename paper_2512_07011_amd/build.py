@@ -9,11 +9,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbsfa.so")
 # translation units: (source, extra flags).  bsfa_fwd.hip is compiled once per group of kernel instantiations.
-FWD_PARTS = 6
+FWD_PARTS = 9
 UNITS = [("bsfa_fwd.hip", ["-DBSFA_PART=%d" % i]) for i in range(FWD_PARTS)] + \
         [(s, []) for s in ("bsfa_select.hip", "bsfa_probe.hip", "bsfa_api.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+         # accumulators in plain VGPRs: kernels whose LDS leaves room for one wave per SIMD would otherwise be given
+         # AGPRs and copy between the two (1.2x slower at 64 and 32 query rows per tile)
+         "-mllvm", "-amdgpu-mfma-vgpr-form=1",
          # packed-fp32 VALU forms are kept out of the generated code on this target
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # the tile copies set M0 in inline asm and list it as clobbered, which clang notes for every

@@ -103,16 +103,19 @@ __device__ __forceinline__ uint32_t chunk_src_offset(int r, int tid, int stride_
 // Completion is tracked by vmcnt, which this kernel manages itself
 // (wait_vmcnt): the instruction is emitted through inline asm so that the compiler does not
 // serialise every later LDS read behind all copies in flight.
-template <int NREP, int NT>
-__device__ __forceinline__ void tile_copy_async(const void *gtile, const uint32_t (&off)[NREP],
+// off: one lane offset per repetition, or a single one and `rep` bytes between the repetitions' bases.
+template <int NREP, int NT, int NOFF>
+__device__ __forceinline__ void tile_copy_async(const void *gtile, const uint32_t (&off)[NOFF], uint32_t rep,
                                                 uint32_t lds_tile, int wave)
 {
+    static_assert(NOFF == NREP || NOFF == 1, "one offset, or one per repetition");
 #pragma unroll
     for (int r = 0; r < NREP; ++r) {
+        const void *const base = NOFF == 1 ? static_cast<const unsigned char *>(gtile) + (size_t)(r * rep) : gtile;
         const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)(r * NT + wave * 64) * 16u);
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                      :
-                     : "s"(dst), "v"(off[r]), "s"(gtile)
+                     : "s"(dst), "v"(off[NOFF == 1 ? 0 : r]), "s"(base)
                      : "memory", "m0");
     }
 }
@@ -126,12 +129,13 @@ template <int D, int NT, bool ISV>
 __device__ __forceinline__ void tile_copy_async_clamped(const uint16_t *gtile, int stride_n, int rows,
                                                         uint32_t lds_tile, int wave)
 {
-    int tid = wave * 64 + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    asm volatile("" : "+v"(tid));       // keeps the offsets from being hoisted out of the key loop
+    int tid;                            // (volatile: keeps the lane id and the offsets from being hoisted out of the key loop)
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(tid));
+    tid += wave * 64;
     uint32_t off[64 * (D / 8) / NT];
 #pragma unroll
     for (int r = 0; r < 64 * (D / 8) / NT; ++r) off[r] = chunk_src_offset<D, NT, ISV>(r, tid, stride_n, rows);
-    tile_copy_async<64 * (D / 8) / NT, NT>(gtile, off, lds_tile, wave);
+    tile_copy_async<64 * (D / 8) / NT, NT>(gtile, off, 0u, lds_tile, wave);
 }
 
 // s_waitcnt vmcnt(N) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14, no wait on the others)

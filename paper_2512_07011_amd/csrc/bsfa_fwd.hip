@@ -1,9 +1,11 @@
 // Block-Sparse FlashAttention forward kernel for gfx950 (MI355X), wave64, bf16 or fp16 MFMA.
 //
 // One workgroup = one query tile Q_i (B_M = 32 * NWH rows, NWH waves of 32 rows) of HP query heads
-// that share a KV head (GQA); it walks the reachable key blocks j in ascending order (Algorithm 1):
+// that share a KV head (GQA); it walks the reachable key blocks j in ascending order (Algorithm 1).
+// With KSP > 1 the blocks are dealt to KSP sets of waves, each with a pipeline of its own, whose
+// results are put together at the end (small problems: see launch_forward).
 //   S_ij^T = K_j Q_i^T        32x32x16 MFMA, fp32 accumulate                      (Eq. 5)
-//   s_max  = max S_ij         lane max -> wave max -> cross-wave max through LDS   (Eq. 6)
+//   s_max  = max S_ij         compared lane by lane; one flag per wave through LDS (Eq. 6)
 //   gate   : s_max / sqrt(d) >= T keeps the block; blocks touching the causal boundary bypass
 //            the gate (Section 4.1).  One decision per (head, query tile, key block).
 //   kept   : V_j is requested only after the decision (and only if some head of the group keeps
@@ -17,7 +19,7 @@
 // j is finished, so the gate decision is known one block ahead:
 //   stage j:  softmax(S_j) -> P_j          (VALU) interleaved with
 //             S_{j+1} = K_{j+1} Q^T        (MFMA); per-lane maximum of S_{j+1}; the wave's keep flag
-//             (or, in the general stages, its block maximum) -> LDS
+//             (and its block maximum, where somebody asks for it) -> LDS
 //             wait for the copies needed next; barrier
 //             O^T += V_j^T P_j^T           (MFMA), and between those MFMAs, a few instructions at a
 //             time: decide keep_{j+1}; request V_{j+1} (only if kept) and K_{j+KR+1}; running
@@ -26,29 +28,45 @@
 // both go HBM -> LDS directly, and the waits are partial (vmcnt) so that only the tile needed
 // next has to have landed.  With a workspace V arrives pre-transposed (transpose_v_kernel) and its
 // operand is a plain 16-byte LDS read; without one it is gathered with the transposing read.
+//
+// What bounds it.  Long sequences: the matrix pipe at the clock the card holds under this load (a plain
+// library product reaches 1360 TFLOP/s here, this kernel 1.12 dense) and, in the stretch between the last
+// score MFMA and the first PV MFMA of a block, instruction issue.  Two workgroups of four waves on a CU
+// (HP = 1) run independently and hide that stretch for each other; eight waves that share a K/V stream
+// (HP = 2) all stand at the same barrier, but read half as much from L2 (see launch_forward for the line).
+// Short sequences: the chain of key blocks of the longest tile, about 1.6 us a block.
 #include "bsfa_dev.h"
 
 namespace bsfa {
 
 struct ScoreTile {
     f32x16 s[2];          // S^T: [32-key half], raw q.k (no 1/sqrt(d)); column = this lane's query
+    float mx0;            // fp8 score product: lane maximum of s[0]
     float mx;             // row max of the lane's query, equal in lanes l and l^32
     bool keep;            // gate decision of this wave's head (uniform over the head's waves)
     bool any_keep;        // some head of the workgroup keeps the block (workgroup-uniform): V is fetched
-    float m_use;          // kept blocks: row max the exponentials are taken against (log2 units)
-    float alpha;          // kept blocks: factor that rescales the running accumulator and normaliser
-    bool resc;            // kept blocks: alpha differs from 1 in some lane of the wave
+    float alpha;          // kept blocks: factor that rescales the accumulator, if ...
+    bool resc;            // ... the running maximum of some row of the wave has grown
 };
 
-template <int D, int NWH, int HP, int KR, bool CALIB, bool F16, bool VT, bool QK8>
-__global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdParams p)
+// Waves per SIMD the registers are allocated for: two, or three at head_dim 64 where the LDS holds as many
+// workgroups of four waves (8K tokens, 32 heads of width 64: 306 us with two, 253 us with three; what the
+// 168 registers do not hold then lies outside the loop over full blocks).
+constexpr int min_waves(int d, int waves, int lds_bytes)
+{
+    return d == 64 && waves * (160 * 1024 / (lds_bytes + 1024)) >= 12 && waves <= 4 ? 3 : 2;
+}
+
+template <int D, int NWH, int HP, int KSP, int KR, bool CALIB, bool F16, bool VT, bool QK8>
+__global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * KSP, KSP * (KR + 2) * 128 * D)) bsfa_fwd_kernel(const FwdParams p)
 {
     typedef typename Elem<F16>::T el;                    // element type of Q, K, V, P, O
     typedef typename Elem<F16>::x8 bf16x8;               // (the vector names keep the default type's name)
     typedef typename Elem<F16>::x4 bf16x4;
     typedef typename Elem<F16>::x2 bf16x2;
-    constexpr int NW = NWH * HP;
-    constexpr int NT = NW * 64;
+    static_assert(KSP == 1 || (!CALIB && !VT && !QK8), "shares of the key blocks: V in place");
+    constexpr int NW = NWH * HP * KSP;
+    constexpr int NT = NWH * HP * 64;                    // threads that share one stream of K and V tiles
     constexpr int BM = NWH * 32;
     constexpr int BN = kBlockN;
     constexpr int KS = D / 16;       // MFMA k-steps over the head dim
@@ -61,19 +79,26 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
     constexpr int ROW_BYTES = D * 2;
     constexpr int R = KR + 1;        // K tiles are requested R blocks ahead
     constexpr int VR = CALIB ? 0 : 2;
+    static_assert(64 * CPR % NT == 0, "every thread copies the same number of chunks");
     static_assert(NST >= 1 && (R < 4 || NSTK * (R - 3) < 64), "copy repetitions");
 
-    __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[(KR + VR) * TILE_BYTES];
-    __shared__ float lds_red[2][NW];
-    // V slots first: their gather offsets then fit the 16-bit immediate of the LDS reads
-    const uint32_t lds_v0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw);
-    const uint32_t lds_k0 = lds_v0 + VR * TILE_BYTES;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[KSP * (KR + VR) * TILE_BYTES];
+    __shared__ float lds_red[2][NW];                                  // the waves' block maxima, where somebody asks for them
+    __shared__ __attribute__((aligned(8))) uint8_t lds_flag[2][NW];   // the waves' keep flags
+    __shared__ uint32_t lds_mask[HP][KSP > 1 ? kSplitMaskWords : 1];  // KSP > 1: the tiles' skip masks, put together
 
     int b, h0, i;
     if (!decode_work<HP>(p, blockIdx.x, b, h0, i)) return;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63;
+    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ksel = KSP > 1 ? wave_all / (NWH * HP) : 0;   // which share of the key blocks: those with j % KSP == ksel
+    const int wave = KSP > 1 ? wave_all % (NWH * HP) : wave_all, tid = wave * 64 + lane;
     const int hsel = wave / NWH, wrow = wave % NWH;      // which head of the group, which 32-row slice
+    const int team = wave_all / NWH;                     // the NWH waves that decide about a block together
+    // V slots first: their gather offsets then fit the 16-bit immediate of the LDS reads
+    const uint32_t lds_v0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw) + ksel * (KR + VR) * TILE_BYTES;
+    const uint32_t lds_k0 = lds_v0 + VR * TILE_BYTES;
+    const uint32_t lds_flag0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint8_t *)lds_flag);
     const int h = h0 + hsel;
     const int l32 = lane & 31, hh = lane >> 5;
     const int g = h0 / p.group;
@@ -103,45 +128,55 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
     // non-causal: blocks [own_lo, own_hi) overlap the tile's own tokens and bypass the gate.
     const int n_gate = p.causal ? (int)((row0 + 1) / BN) : 0;
     const int own_lo = (int)(row0 / BN), own_hi = (int)((row0 + BM + BN - 1) / BN);
+    // Block indices from here on: `j` counts the blocks of this wave's share, glob(j) is the key block it stands
+    // for, own(x) is the number of its blocks below key block x.  All the same thing unless KSP > 1.
+    auto glob = [&](int jl) { return KSP > 1 ? jl * KSP + ksel : jl; };
+    auto own = [&](int x) { return KSP > 1 ? max(0, (x - ksel + KSP - 1) / KSP) : x; };
+    const int n_own = own(n_blk), own_max = KSP > 1 ? (n_blk + KSP - 1) / KSP : n_own;
+    if constexpr (KSP > 1) {
+        for (int w = threadIdx.x; w < HP * kSplitMaskWords; w += NW * 64) (&lds_mask[0][0])[w] = 0u;   // (a barrier follows before its first use)
+    }
 
     const uint16_t *kbase = p.k + (int64_t)b * p.ksb + (int64_t)g * p.ksh;
     // VT: V comes from the workspace, one pre-transposed, pre-swizzled 64-key tile after the other
     const uint16_t *vbase = VT ? p.vt + ((int64_t)b * p.hkv + g) * p.mkv * (int64_t)(BN * D)
                                : p.v + (int64_t)b * p.vsb + (int64_t)g * p.vsh;
-    float tau_h[HP];                                      // thresholds of the group's heads for this tile
+    // threshold of this wave's head; tiles past the calibrated length use its last tile's (Section 4.3)
+    const float tau_own = CALIB ? -INFINITY      // the score half takes no decisions
+                                : p.tau[p.tau_per_tile ? (int64_t)h * p.tau_tiles + min(i, p.tau_tiles - 1) : h];
+    // Source offsets of the copies.  Where a repetition covers a multiple of 16 rows (the period of the swizzles;
+    // and for tiles copied linearly) all repetitions share one lane offset and the scalar base advances.
+    constexpr bool ONE_OFF = (NT / CPR) % 16 == 0;
+    constexpr int NKO = QK8 || ONE_OFF ? 1 : NSTK, NVO = VT || ONE_OFF ? 1 : NST;
+    uint32_t koff[NKO], voff[NVO];
 #pragma unroll
-    for (int x = 0; x < HP; ++x)     // tiles past the calibrated length use its last tile's threshold (Section 4.3)
-        tau_h[x] = CALIB ? -INFINITY      // the score half takes no decisions
-                         : p.tau[p.tau_per_tile ? (int64_t)(h0 + x) * p.tau_tiles + min(i, p.tau_tiles - 1) : (h0 + x)];
-
-    const float tau_own = hsel ? tau_h[HP - 1] : tau_h[0];
-    uint32_t koff[NSTK], voff[NST];
+    for (int r = 0; r < NKO; ++r) koff[r] = QK8 ? (uint32_t)tid * 16u : chunk_src_offset<D, NT, false>(r, tid, (int)p.ksn);
 #pragma unroll
-    for (int r = 0; r < NST; ++r) {
-        if (r < NSTK) koff[r] = QK8 ? (uint32_t)(r * NT + tid) * 16u : chunk_src_offset<D, NT, false>(r, tid, (int)p.ksn);
-        voff[r] = VT ? (uint32_t)(r * NT + tid) * 16u : chunk_src_offset<D, NT, true>(r, tid, (int)p.vsn);
-    }
+    for (int r = 0; r < NVO; ++r) voff[r] = VT ? (uint32_t)tid * 16u : chunk_src_offset<D, NT, true>(r, tid, (int)p.vsn);
+    const uint32_t krep = QK8 ? NT * 16u : (uint32_t)(NT / CPR) * (uint32_t)p.ksn * 2u;      // bytes from one repetition to the next
+    const uint32_t vrep = VT ? NT * 16u : (uint32_t)(NT / CPR) * (uint32_t)p.vsn * 2u;
     // QK8: K comes from the workspace as fp8 tiles (64 rows of D bytes, swizzled for the operand reads)
     const uint8_t *k8base = QK8 ? p.k8 + ((int64_t)b * p.hkv + g) * p.mkv * (int64_t)(BN * D) : nullptr;
     const int64_t kstep = (int64_t)BN * p.ksn, vstep = VT ? (int64_t)(BN * D) : (int64_t)BN * p.vsn;
     // K_t, whose first row is at `src`, into the ring slot at LDS byte address dst
     auto copy_k_from = [&](const unsigned char *src, int t, uint32_t dst) {
         if constexpr (QK8) {
-            tile_copy_async<NSTK, NT>(src, koff, dst, wave);                                  // (padded already)
+            tile_copy_async<NSTK, NT>(src, koff, krep, dst, wave);                                  // (padded already)
         } else {
-            if (t == partial_blk) tile_copy_async_clamped<D, NT, false>(reinterpret_cast<const uint16_t *>(src), (int)p.ksn, partial_rows, dst, wave);
-            else tile_copy_async<NSTK, NT>(src, koff, dst, wave);
+            if (glob(t) == partial_blk) tile_copy_async_clamped<D, NT, false>(reinterpret_cast<const uint16_t *>(src), (int)p.ksn, partial_rows, dst, wave);
+            else tile_copy_async<NSTK, NT>(src, koff, krep, dst, wave);
         }
     };
     // V_t, whose first row is at `src`, into slot t & 1
     auto copy_v_from = [&](const unsigned char *src, int t) {
         const uint32_t dst = lds_v0 + (uint32_t)(t & 1) * TILE_BYTES;
-        if (!VT && t == partial_blk) tile_copy_async_clamped<D, NT, true>(reinterpret_cast<const uint16_t *>(src), (int)p.vsn, partial_rows, dst, wave);
-        else tile_copy_async<NST, NT>(src, voff, dst, wave);                                  // (workspace tiles are padded already)
+        if (!VT && glob(t) == partial_blk) tile_copy_async_clamped<D, NT, true>(reinterpret_cast<const uint16_t *>(src), (int)p.vsn, partial_rows, dst, wave);
+        else tile_copy_async<NST, NT>(src, voff, vrep, dst, wave);                                  // (workspace tiles are padded already)
     };
-    const unsigned char *const k_bytes = QK8 ? reinterpret_cast<const unsigned char *>(k8base) : reinterpret_cast<const unsigned char *>(kbase);
-    const unsigned char *const v_bytes = reinterpret_cast<const unsigned char *>(vbase);
-    const int64_t kstep_b = QK8 ? (int64_t)(BN * D) : kstep * 2, vstep_b = vstep * 2;      // bytes from one tile to the next
+    const unsigned char *const k_bytes = QK8 ? reinterpret_cast<const unsigned char *>(k8base) : reinterpret_cast<const unsigned char *>(kbase) + ksel * kstep * 2;
+    const unsigned char *const v_bytes = reinterpret_cast<const unsigned char *>(vbase) + ksel * vstep * 2;
+    // bytes from one tile of this wave's share to the next
+    const int64_t kstep_b = KSP * (QK8 ? (int64_t)(BN * D) : kstep * 2), vstep_b = KSP * vstep * 2;
     auto copy_k = [&](int t, uint32_t dst) { copy_k_from(k_bytes + t * kstep_b, t, dst); };
     auto copy_v = [&](int t) { copy_v_from(v_bytes + t * vstep_b, t); };
 
@@ -214,7 +249,9 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
     for (int x = 0; x < DB; ++x)
 #pragma unroll
         for (int e = 0; e < 16; ++e) oacc[x][e] = 0.f;
-    float m_run = -INFINITY;   // running row max, log2 units (score * log2(e)/sqrt(d))
+    // Running maximum of the row, log2 units (score * log2(e)/sqrt(d)).  The start value is finite, so that rows
+    // without a visible key yet need no special case, and below any score (fp32 products times log2(e)/sqrt(d)).
+    float m_run = -3.0e38f;
     float l_run = 0.f;         // this lane's share of the running normaliser
 
     unsigned n_skipped = 0;    // per-head statistics, uniform over the head's waves
@@ -222,20 +259,27 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
 
     auto is_gated = [&](int j) { return p.causal ? (j < n_gate) : (j < own_lo || j >= own_hi); };
 
-    // K operand n (= k-step n/2, 32-key half n%2) of the tile at LDS byte address kaddr (+ka_base)
+    // Order of the score MFMAs: the two 32-key halves in turn; with fp8 operands (four long MFMAs) one half after
+    // the other, so that the first half's maxima are taken while the second half is multiplied (1.5 % faster
+    // there, 1 % slower with 16-bit operands).
+    constexpr bool HALVES = QK8;
+    auto kst = [](int n) { return HALVES ? n % KSQ : n >> 1; };
+    auto khalf = [](int n) { return HALVES ? n / KSQ : n & 1; };
+    // K operand n (k-step kst(n), 32-key half khalf(n)) of the tile at LDS byte address kaddr (+ka_base)
     auto k_operand = [&](uint32_t kaddr, int n) {
+        const int st = kst(n), kb = khalf(n);
         if constexpr (QK8) {
-            const uint32_t a_s = (kaddr ^ (uint32_t)((n >> 1) << 6)) + (n & 1) * 32 * 128;
+            const uint32_t a_s = (kaddr ^ (uint32_t)(st << 6)) + kb * 32 * 128;
             const i32x4 lo = *LDS_PTR(const i32x4, a_s);
             const i32x4 hi = *LDS_PTR(const i32x4, a_s ^ 16u);
             return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         } else {
-            const uint32_t a_s = kaddr ^ (uint32_t)((n >> 1) << 5);
-            return *LDS_PTR(const bf16x8, a_s + (n & 1) * 32 * ROW_BYTES);
+            const uint32_t a_s = kaddr ^ (uint32_t)(st << 5);
+            return *LDS_PTR(const bf16x8, a_s + kb * 32 * ROW_BYTES);
         }
     };
-    constexpr int PD = 5;            // LDS operand reads are issued PD MFMAs ahead of their use (measured: 5 is 0.6 % faster
-                                     // than 4; 6 gains another 0.4 % but spills a few registers outside the loop)
+    
+    constexpr int PD = 4;            // LDS operand reads are issued PD MFMAs ahead of their use (3 to 6 measure within 1 %)
     constexpr int PDK = QK8 ? 2 : PD; // ... of the score operands (the fp8 ones are twice as wide and four in all)
     // The first PDK score operands of a block are read one phase early (at the end of the previous
     // stage, behind its last MFMAs), so that the score MFMAs do not start with an LDS round trip.
@@ -243,6 +287,13 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
     auto prefetch_k = [&](uint32_t kt) {
 #pragma unroll
         for (int n = 0; n < PDK; ++n) kpre[n] = k_operand(kt + ka_base, n);
+    };
+
+    auto half_max = [&](ScoreTile &t, int n) {              // after MFMA n, once s[0] is complete
+        if (n != KSQ + 1) return;
+        t.mx0 = fmaxf(t.s[0][0], t.s[0][1]);
+#pragma unroll
+        for (int e = 2; e < 16; ++e) t.mx0 = fmaxf(t.mx0, t.s[0][e]);
     };
 
     // S^T of block j from the K tile at LDS byte address `kt` (MFMA and LDS reads only); the
@@ -260,39 +311,46 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
 #pragma unroll
         for (int n = 0; n < NQK; ++n) {
             if (n + PDK < NQK) a[n + PDK] = k_operand(kaddr, n + PDK);
-            t.s[n & 1] = qk_mma(a[n], qreg[n >> 1], t.s[n & 1]);
+            t.s[khalf(n)] = qk_mma(a[n], qreg[kst(n)], t.s[khalf(n)]);
+            if (HALVES) half_max(t, n);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    // causal mask on boundary blocks, row maxima, and the wave's block maximum into
-    // lds_red[j & 1].  FAST: the block is known to be gateable (no causal mask).
-    // FAST in the forward kernel proper: nobody asks for the maximum itself, only for the decision,
-    // and  max_lanes(m) * c >= T  <=>  some lane has m * c >= T  (c > 0, rounding is monotone): every
-    // lane compares its own maximum with its head's threshold and the wave publishes one flag.  That
-    // takes the cross-lane reductions out of the stretch between the last score MFMA and the barrier,
-    // where nothing else runs; the row maximum the softmax needs is completed after the barrier.
+    // Causal mask on boundary blocks, lane / row maxima, and the wave's keep flag into lds_flag[j & 1]: the
+    // decision is about the maximum over the head's waves, and  max(m) * c >= T  <=>  some m * c >= T
+    // (c > 0, rounding is monotone), so flags are all the waves have to exchange.  The maxima themselves go to
+    // lds_red[j & 1] if somebody asks for them (dump, calibration).
+    // FAST: the block is known to be gateable (no causal mask).  There every lane compares its own maximum:
+    // that takes the cross-lane reductions out of the stretch between the last score MFMA and the barrier;
+    // the row maximum the softmax needs is completed after the barrier, for kept blocks only.
     auto reduce_scores = [&](ScoreTile &t, int j, auto fast_tag) {
         constexpr bool FAST = decltype(fast_tag)::value;
         if constexpr (FAST && !CALIB) {
             float mx = -INFINITY;
+            if constexpr (HALVES) {
+                mx = t.mx0;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int e = 0; e < 16; ++e) mx = fmaxf(mx, t.s[1][e]);
+            } else {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) mx = fmaxf(mx, t.s[kb][e]);
-            t.mx = mx;                                        // this lane's half of the row; see finish_row_max
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, t.s[kb][e]);
+            }
+            t.mx = mx;                                        // this lane's half of the row
             const bool wave_ge = __builtin_amdgcn_ballot_w64(mx * p.scale >= tau_own) != 0ull;
-            if (lane == 0) lds_red[j & 1][wave] = wave_ge ? 1.f : 0.f;
+            if (lane == 0) lds_flag[j & 1][wave_all] = wave_ge ? 1 : 0;
             return;
         }
-        const bool gated = FAST ? true : is_gated(j);
+        const bool gated = FAST ? true : is_gated(glob(j));
         if constexpr (!FAST) {
             if (p.causal && !gated) {
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) {
-                        const int key = j * BN + 32 * kb + 8 * (e >> 2) + 4 * hh + (e & 3);
+                        const int key = glob(j) * BN + 32 * kb + 8 * (e >> 2) + 4 * hh + (e & 3);
                         if (key > q_row) t.s[kb][e] = -INFINITY;
                     }
             }
@@ -303,80 +361,116 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
 #pragma unroll
             for (int e = 0; e < 16; ++e) mx = fmaxf(mx, t.s[kb][e]);
         t.mx = pair_max(mx);
+        bool ge = true;                                       // blocks that bypass the gate are kept
         if (gated) {
-            float stat = t.mx;
+            float stat = t.mx, unit = p.scale;                // natural score units (Eq. 5-6)
             if constexpr (!FAST) {
                 // the comparison predicate (Section 3): local row maximum minus the running row maximum
                 // after this block, natural units; m_run covers the kept blocks before this one
-                if (p.gate_mode) stat = fminf(t.mx * p.scale - m_run * 0.6931471805599453f, 0.f);
-            }
-            const float wm = wave_max_paired(stat);
-            if (lane == 0) lds_red[j & 1][wave] = wm;
-        }
-    };
-
-    // gate decisions for block j + statistics.  `red` holds the waves' block maxima, read from
-    // lds_red[j & 1] after the barrier that publishes them (the read is issued early by the caller
-    // so that its latency is covered)
-    auto decide = [&](ScoreTile &t, int j, const float (&red)[NW], auto fast_tag) {
-        constexpr bool FAST = decltype(fast_tag)::value;
-        bool keep = true, any_keep = true;
-        float bmax = NAN;
-        if (FAST || is_gated(j)) {
-            any_keep = false;
-#pragma unroll
-            for (int x = 0; x < HP; ++x) {
-                float r = red[x * NWH];
-#pragma unroll
-                for (int w = 1; w < NWH; ++w) r = fmaxf(r, red[x * NWH + w]);
-                const float sm = (!FAST && p.gate_mode) ? r : r * p.scale;   // natural score units (Eq. 5-6)
-                const bool kx = (sm >= tau_h[x]);                    // skip iff s_max < T
-                any_keep = any_keep || kx;
-                if (x == hsel) {
-                    keep = kx;
-                    bmax = sm;
+                if (p.gate_mode) {
+                    stat = fminf(t.mx * p.scale - m_run * 0.6931471805599453f, 0.f);
+                    unit = 1.f;
                 }
             }
+            const float wm = wave_max_paired(stat) * unit;
+            ge = wm >= tau_own;                               // skip iff s_max < T
+            if ((CALIB || p.block_max) && lane == 0) lds_red[j & 1][wave_all] = wm;
         }
-        t.keep = keep;
-        t.any_keep = any_keep;
+        if (!CALIB && lane == 0) lds_flag[j & 1][wave_all] = ge ? 1 : 0;
+    };
+
+    // the keep flags of team x of the workgroup for a block of parity par, as published before the last barrier
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef std::conditional_t<NWH == 4, uint32_t, std::conditional_t<NWH == 2, uint16_t, uint8_t>> flag_t;
+    auto read_team = [&](int x, int par) { return (uint32_t)*LDS_PTR(const flag_t, lds_flag0 + (uint32_t)(par * NW + x * NWH)); };
+    auto read_flags = [&](uint32_t (&flags)[HP], int par) {
+        if constexpr (HP == 2 && NWH == 4) {              // both heads in one read
+            const u32x2 f = *LDS_PTR(const u32x2, lds_flag0 + (uint32_t)(par * NW + ksel * HP * NWH));
+            flags[0] = f[0];
+            flags[1] = f[1];
+        } else {
+#pragma unroll
+            for (int x = 0; x < HP; ++x) flags[x] = read_team(ksel * HP + x, par);
+        }
+    };
+    // Decisions from the read flags.  They are consumed here and not earlier (nothing computed from them may be
+    // hoisted in front of the PV MFMAs, where it would wait for the LDS read), and made scalar, so that the
+    // branches on them are uniform.
+    auto decide = [&](ScoreTile &t, const uint32_t (&flags)[HP]) {
+        bool own_head = false, any = false;
+#pragma unroll
+        for (int x = 0; x < HP; ++x) {
+            uint32_t f = flags[x];
+            asm volatile("" : "+v"(f));
+            const bool kx = __builtin_amdgcn_readfirstlane((int)f) != 0;
+            any = any || kx;
+            own_head = hsel == x ? kx : own_head;
+        }
+        t.keep = own_head;
+        t.any_keep = any;
+    };
+
+    // statistics of block j: decision of this wave's head, and its maximum if asked for
+    auto record = [&](bool keep, int jl, auto fast_tag) {
+        constexpr bool FAST = decltype(fast_tag)::value;
+        const int j = glob(jl);
         n_skipped += keep ? 0 : 1;
         mask_word |= (keep ? 0u : 1u) << (j & 31);
-        if (p.block_max && stat_lane) p.block_max[stat_row * p.mkv + j] = bmax;
-        if ((j & 31) == 31 || j == n_blk - 1) {
-            if (p.skip_mask && stat_lane) p.skip_mask[stat_row * p.mask_words + (j >> 5)] = mask_word;
+        if (CALIB || !FAST) {
+            if (p.block_max && stat_lane) {
+                float bmax = NAN;
+                if (FAST || is_gated(j)) {
+                    bmax = lds_red[jl & 1][team * NWH];
+#pragma unroll
+                    for (int w = 1; w < NWH; ++w) bmax = fmaxf(bmax, lds_red[jl & 1][team * NWH + w]);
+                }
+                p.block_max[stat_row * p.mkv + j] = bmax;
+            }
+        }
+        if ((j & 31) > 31 - KSP || j > n_blk - 1 - KSP) {      // the last block of a mask word, or of the tile
+            if (p.skip_mask && stat_lane) {
+                if constexpr (KSP > 1) atomicOr(&lds_mask[hsel][j >> 5], mask_word);
+                else p.skip_mask[stat_row * p.mask_words + (j >> 5)] = mask_word;
+            }
             mask_word = 0;
         }
     };
 
     // online-softmax update of the running statistics with block `t`: new row max and the
     // accumulator's rescale factor first, then the exponentials, P (bf16) into pb
+    // Running maximum and rescale factor for block `t`; most blocks of a long sequence raise no row's maximum and
+    // leave both alone.  (A maximum that follows lazily would save most of the other rescales, 3 % on an 8K
+    // prompt, but costs precision: against the row's own maximum the largest probabilities sit just below a power
+    // of two, where rounding them to 16 bits is most exact.  Error against 64 bits 0.00199 -> 0.00214.)
     auto softmax_begin = [&](ScoreTile &t) {
-        const float m_new = fmaxf(m_run, t.mx * p.scale_log2);
-        t.m_use = (m_new == -INFINITY) ? 0.f : m_new;
-        t.alpha = __builtin_amdgcn_exp2f(m_run - t.m_use);
-        t.resc = __builtin_amdgcn_ballot_w64(t.alpha != 1.0f) != 0ull;
-        m_run = m_new;
+        const float mb = t.mx * p.scale_log2;
+        t.resc = __builtin_amdgcn_ballot_w64(mb > m_run) != 0ull;
+        if (t.resc) {
+            const float m_new = fmaxf(m_run, mb);
+            t.alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= t.alpha;
+            m_run = m_new;
+        }
     };
-    auto softmax_exp = [&](ScoreTile &t, float m_use, float alpha, bf16x8 (&pb)[4]) {
+    auto softmax_exp = [&](ScoreTile &t, bf16x8 (&pb)[4]) {
         float psum = 0.f;
 #pragma unroll
         for (int idx = 0; idx < 32; idx += 2) {
             const int kb = idx >> 4, e = idx & 15;
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(t.s[kb][e], p.scale_log2, -m_use));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(t.s[kb][e + 1], p.scale_log2, -m_use));
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(t.s[kb][e], p.scale_log2, -m_run));
+            const float p1 = __builtin_amdgcn_exp2f(fmaf(t.s[kb][e + 1], p.scale_log2, -m_run));
             const bf16x2 pp = {(el)p0, (el)p1};
             psum = pair_sum(pp, psum);                                       // sum of the rounded values
             pb[idx >> 3][idx & 7] = pp[0];
             pb[idx >> 3][(idx & 7) + 1] = pp[1];
         }
-        l_run = l_run * alpha + psum;
+        l_run += psum;
     };
     // softmax_exp(cur) and qk_mfma(nxt) fused.  The exponentials of block j and the score MFMAs
     // of block j+1 are independent: they are written interleaved (per MFMA a few exponentials,
     // their row-sum adds and bf16 packs) and pinned in that order, so that the matrix pipe and
     // the VALU run together.  K operands are read PD MFMAs ahead.
-    auto fused_exp_qk = [&](ScoreTile &cur, ScoreTile &nxt, uint32_t kt, float m_use, float alpha, bf16x8 (&pb)[4]) {
+    auto fused_exp_qk = [&](ScoreTile &cur, ScoreTile &nxt, uint32_t kt, bf16x8 (&pb)[4]) {
         const uint32_t kaddr = kt + ka_base;
         kop_t a[NQK + PDK];
 #pragma unroll
@@ -405,29 +499,21 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
 #pragma unroll
         for (int n = 0; n < NQK; ++n) {
             if (n + PDK < NQK) a[n + PDK] = k_operand(kaddr, n + PDK);
-            nxt.s[n & 1] = qk_mma(a[n], qreg[n >> 1], nxt.s[n & 1]);
+            nxt.s[khalf(n)] = qk_mma(a[n], qreg[kst(n)], nxt.s[khalf(n)]);
             float nx[EPM];
 #pragma unroll
             for (int t = 0; t < EPM; ++t) {
                 const int idx = n * EPM + t;
-                nx[t] = __builtin_amdgcn_exp2f(fmaf(cur.s[idx >> 4][idx & 15], p.scale_log2, -m_use));
+                nx[t] = __builtin_amdgcn_exp2f(fmaf(cur.s[idx >> 4][idx & 15], p.scale_log2, -m_run));
             }
             if (n > 0) pack(n - 1);
+            if (HALVES) half_max(nxt, n);
 #pragma unroll
             for (int t = 0; t < EPM; ++t) ex[t] = nx[t];
             __builtin_amdgcn_sched_barrier(0);
         }
         pack(NQK - 1);
-        l_run = l_run * alpha + (psum0 + psum1);
-    };
-
-    auto rescale = [&](const ScoreTile &t) {
-        if (t.resc) {
-#pragma unroll
-            for (int x = 0; x < DB; ++x)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) oacc[x][e] *= t.alpha;
-        }
+        l_run += psum0 + psum1;
     };
 
     // O^T += V^T P^T for the V tile at LDS byte address `vt`; operand n = (k-step u = n / DB,
@@ -436,7 +522,7 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
     // happen soon after the barrier goes there in small pieces, beside the matrix pipe instead of in
     // front of it
     constexpr int NPV = 4 * DB;
-    auto pv = [&](const bf16x8 (&pb)[4], uint32_t vt, auto hook) {
+    auto pv = [&](const ScoreTile &t, const bf16x8 (&pb)[4], uint32_t vt, auto hook) {
         const uint32_t vaddr = vt + va_base;
         auto v_operand = [&](int n) {
             const int u = n / DB, x = n % DB;
@@ -454,6 +540,12 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
         static_for<NPV>([&](auto nc) {
             constexpr int n = decltype(nc)::value;
             if constexpr (n + PD < NPV) a[n + PD] = v_operand(n + PD);
+            if constexpr (n < DB) {                   // the running maximum has grown: O^T follows, a block of it at a time
+                if (t.resc) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) oacc[n][e] *= t.alpha;
+                }
+            }
             oacc[n % DB] = mfma16(a[n], pb[n / DB], oacc[n % DB]);
             __builtin_amdgcn_sched_barrier(0);
             hook(nc);
@@ -466,11 +558,10 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
     const unsigned char *k_ahead = k_bytes + R * kstep_b;
     const unsigned char *v_ahead = v_bytes + vstep_b;
     // One pipeline stage: finish block j (`cur`), look ahead to block j+1 (`nxt`).
-    // FAST: block j+1 exists and is gateable, so the look-ahead has no mask and no conditionals.
+    // Block j+1 exists (the tile's last block is finished by last_stage).  FAST: it is gateable, so the
+    // look-ahead has no mask and fewer conditionals.
     auto stage = [&](ScoreTile &cur, ScoreTile &nxt, int j, auto fast_tag) {
         constexpr bool FAST = decltype(fast_tag)::value;
-        constexpr bool FLAGS = FAST && !CALIB;           // the waves publish decisions, not maxima (see reduce_scores)
-        const bool has_next = FAST || (j + 1 < n_blk);
         bf16x8 pb[4];
         const bool do_pv = !CALIB && cur.keep;
         // slot of K_{j+1}; K_{j+R} is requested into the same slot once block j+1 has left it
@@ -481,86 +572,52 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
         k_ahead += kstep_b;
         v_ahead += vstep_b;
         if (do_pv) {
-            rescale(cur);                         // the previous block's PV has been issued already
-            if constexpr (FAST) {
-                fused_exp_qk(cur, nxt, kt_next, cur.m_use, cur.alpha, pb);
-            } else {
-                softmax_exp(cur, cur.m_use, cur.alpha, pb);
-                if (has_next) qk_mfma(nxt, kt_next);
-            }
+            fused_exp_qk(cur, nxt, kt_next, pb);
         } else {
-            if (has_next) qk_mfma(nxt, kt_next);
+            qk_mfma(nxt, kt_next);
         }
-        if (has_next) reduce_scores(nxt, j + 1, fast_tag);
+        reduce_scores(nxt, j + 1, fast_tag);
         // copies that must have landed before the barrier: V_j (if requested) and K_{j+2}; every
         // younger request (K_{j+3} .. K_{j+R-1}, issued after V_j) may stay in flight
-        if (R >= 4 && j - 1 + R < n_blk) {
+        if (R >= 4 && j - 1 + R < n_own) {
             if (!CALIB && cur.any_keep) wait_vmcnt<NSTK>();
             else wait_vmcnt<(R >= 4 ? NSTK * (R - 3) : 0)>();
         } else {
             wait_vmcnt<0>();
         }
         wg_barrier();
-        float red[NW];
-        if (has_next) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w) red[w] = lds_red[(j + 1) & 1][w];
-        }
+        uint32_t flags[HP] = {};
+        if constexpr (!CALIB) read_flags(flags, (j + 1) & 1);
         __builtin_amdgcn_sched_barrier(0);
         // The look-ahead -- decision for block j+1, its statistics, the requests for V_{j+1} and
         // K_{j+R}, the running maximum -- in pieces, so that a kept block can issue them between its
         // PV MFMAs a few instructions at a time.
         auto la_decide = [&]() {
-            if (!has_next) return;
-            // the maxima are consumed here and not earlier: nothing computed from them may be
-            // hoisted in front of the PV MFMAs, where it would wait for the LDS read
-#pragma unroll
-            for (int w = 0; w < NW; ++w) asm volatile("" : "+v"(red[w]));
-            if constexpr (FLAGS) {
-                bool kx[HP];
-#pragma unroll
-                for (int x = 0; x < HP; ++x) {
-                    float f = red[x * NWH];
-#pragma unroll
-                    for (int w = 1; w < NWH; ++w) f = fmaxf(f, red[x * NWH + w]);
-                    kx[x] = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, f)) != 0;   // a scalar: the branches below are uniform
-                }
-                const bool keep = hsel ? kx[HP - 1] : kx[0];
-                nxt.keep = keep;
-                nxt.any_keep = kx[0] || kx[HP - 1];
-                n_skipped += keep ? 0 : 1;
-                mask_word |= (keep ? 0u : 1u) << ((j + 1) & 31);
-            } else {
-                decide(nxt, j + 1, red, fast_tag);
-            }
+            if constexpr (!CALIB) decide(nxt, flags);
+            else nxt.keep = true;
         };
         auto la_stats = [&]() {
-            if constexpr (FLAGS) {                        // (block j+1 is never the tile's last one here)
-                if (((j + 1) & 31) == 31) {
-                    if (p.skip_mask && stat_lane) p.skip_mask[stat_row * p.mask_words + ((j + 1) >> 5)] = mask_word;
-                    mask_word = 0;
-                }
-            }
+            record(nxt.keep, j + 1, fast_tag);
         };
         auto la_vcopy = [&]() {
-            if (has_next && !CALIB && nxt.any_keep) {
-                if constexpr (FAST) tile_copy_async<NST, NT>(v_src, voff, lds_v0 + (uint32_t)((j + 1) & 1) * TILE_BYTES, wave);
+            if (!CALIB && nxt.any_keep) {
+                if constexpr (FAST) tile_copy_async<NST, NT>(v_src, voff, vrep, lds_v0 + (uint32_t)((j + 1) & 1) * TILE_BYTES, wave);
                 else copy_v_from(v_src, j + 1);           // a gateable block is never the partial one
             }
         };
         auto la_kcopy = [&]() {
-            if (has_next && j + R < n_blk) copy_k_from(k_src, j + R, kt_next);
+            if (j + R < n_own) copy_k_from(k_src, j + R, kt_next);
         };
         auto la_softmax = [&]() {                        // running max and rescale factor, off the critical path
-            if (has_next && !CALIB && nxt.keep) {
-                if constexpr (FLAGS) nxt.mx = pair_max(nxt.mx);
+            if (!CALIB && nxt.keep) {
+                if constexpr (FAST) nxt.mx = pair_max(nxt.mx);
                 softmax_begin(nxt);
             }
         };
         if (do_pv) {
             if constexpr (!CALIB) {
                 constexpr int HS = NPV / 8;               // MFMAs from one piece to the next
-                pv(pb, lds_v0 + (uint32_t)(j & 1) * TILE_BYTES, [&](auto nc) {
+                pv(cur, pb, lds_v0 + (uint32_t)(j & 1) * TILE_BYTES, [&](auto nc) {
                     constexpr int n = decltype(nc)::value;
                     if constexpr (n == HS) la_decide();
                     if constexpr (n == 2 * HS) la_stats();
@@ -584,62 +641,121 @@ __global__ void __launch_bounds__(NWH * HP * 64, 2) bsfa_fwd_kernel(const FwdPar
         }
     };
 
-    // ---- prologue: scores and decision of block 0, then K_1 .. K_{R-1} and V_0 -----------------
+    // The tile's last block (it touches the causal boundary, or there is no mask): nothing to look ahead to.
+    auto last_stage = [&](ScoreTile &cur, int j) {
+        if constexpr (!CALIB) {
+            bf16x8 pb[4];
+            if (cur.keep) {
+                softmax_exp(cur, pb);
+            }
+            wait_vmcnt<0>();
+            wg_barrier();
+            if (cur.keep) pv(cur, pb, lds_v0 + (uint32_t)(j & 1) * TILE_BYTES, [](auto) {});
+        }
+    };
+
+    // ---- prologue: scores and decision of block 0 -----------------------------------------------
+    // All K tiles the ring holds are requested at once with K_0, and what follows (V_0, K_{R-1}) is left in flight
+    // for the first stage: one trip to memory before the pipeline starts instead of two.
     ScoreTile ta, tb;
-    copy_k(0, lds_k0);
+#pragma unroll
+    for (int t = 0; t < KR; ++t)
+        if (t < n_own) copy_k(t, lds_k0 + (uint32_t)t * TILE_BYTES);
     wait_vmcnt<0>();
     wg_barrier();
     prefetch_k(lds_k0);
     qk_mfma(ta, lds_k0);
-    reduce_scores(ta, 0, std::false_type{});
-    wg_barrier();                                       // block maxima visible, K_0 consumed
-    {
-        float red[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) red[w] = lds_red[0][w];
-        decide(ta, 0, red, std::false_type{});
-        if (!CALIB && ta.keep) softmax_begin(ta);
-    }
-    if (!CALIB && ta.any_keep) copy_v(0);
-#pragma unroll
-    for (int t = 1; t < R; ++t)                            // K_{R-1} reuses the slot block 0 has just left
-        if (t < n_blk) copy_k(t, lds_k0 + (uint32_t)(t % KR) * TILE_BYTES);
-    wait_vmcnt<0>();                                       // drained once; from here on the steady-state rule holds
-    wg_barrier();
     prefetch_k(lds_k0 + kring);                            // K_1 for the first stage
+    reduce_scores(ta, 0, std::false_type{});
+    wg_barrier();                                       // flags visible, K_0 consumed
+    if constexpr (!CALIB) {
+        uint32_t flags[HP];
+        read_flags(flags, 0);
+        decide(ta, flags);
+        if (KSP > 1 && n_own == 0) ta.keep = ta.any_keep = false;      // a share without blocks
+        if (ta.any_keep) copy_v(0);
+        if (ta.keep) softmax_begin(ta);
+    } else {
+        ta.keep = true;
+    }
+    if (R - 1 < n_own) copy_k(R - 1, lds_k0);              // the slot block 0 has just left
+    if (KSP == 1 || n_own > 0) record(ta.keep, 0, std::false_type{});
 
-    // main loop, two stages per trip.  A pair runs the fused, mask-free stages when both of its
+    // main loop, two stages per trip.  A pair runs the mask-free stages when both of its
     // look-ahead blocks (j+1, j+2) exist and are gateable: every pair below the causal boundary;
     // without the causal mask every pair before the tile's own token range and, in a second
     // segment, every pair behind it (Section 4.3, last sentence: only the own-range blocks bypass the
-    // gate).  The remaining pairs take the general stages.
+    // gate).  The remaining blocks take the general stages, one at a time.
     int j = 0;
     for (int seg = 0; seg < 2; ++seg) {
-        const int fast_end = (p.gate_mode || (!CALIB && p.block_max)) ? 0 : seg == 0 ? (p.causal ? n_gate : own_lo) : (p.causal ? 0 : n_blk);
+        const int fast_end = (p.gate_mode || (!CALIB && p.block_max)) ? 0 : seg == 0 ? own(p.causal ? n_gate : own_lo) : (p.causal ? 0 : n_own);
         for (; j + 2 < fast_end; j += 2) {
             stage(ta, tb, j, std::true_type{});
             stage(tb, ta, j + 1, std::true_type{});
         }
-        // first even j whose look-ahead block lies behind the own range
-        const int gen_end = (seg == 0 && !p.causal) ? min(own_hi & ~1, n_blk) : n_blk;
-        for (; j < gen_end; j += 2) {
+        // up to the first block whose look-ahead block lies behind the own range
+        const int gen_end = (seg == 0 && !p.causal) ? min(own(own_hi) - 1, n_own - 1) : n_own - 1;
+        for (; j < gen_end; ++j) {
             stage(ta, tb, j, std::false_type{});
-            if (j + 1 < n_blk) stage(tb, ta, j + 1, std::false_type{});
+            ta = tb;
         }
+    }
+    if constexpr (KSP > 1) {
+        if (n_own > 0) last_stage(ta, j);
+        for (int x = n_own; x < own_max; ++x) wg_barrier();          // every wave passes own_max barriers since the prologue
+    } else {
+        last_stage(ta, j);
     }
 
     // ---- statistics ------------------------------------------------------------------------
     const int htid = tid - hsel * NWH * 64;               // thread index within the head's waves
-    if (p.block_max)
+    if (p.block_max && ksel == 0)
         for (int jj = n_blk + htid; jj < p.mkv; jj += NWH * 64) p.block_max[stat_row * p.mkv + jj] = NAN;
-    if (p.skip_mask)
-        for (int w = ((n_blk + 31) >> 5) + htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = 0u;
+    if constexpr (KSP == 1) {
+        if (p.skip_mask)
+            for (int w = ((n_blk + 31) >> 5) + htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = 0u;
+    }
     if (p.counts && stat_lane) {
         unsigned long long *c = p.counts + ((int64_t)b * p.hq + h) * 3;
         const int gateable = p.causal ? n_gate : (p.mkv - (own_hi - own_lo));
         atomicAdd(c + 0, (unsigned long long)n_skipped);
-        atomicAdd(c + 1, (unsigned long long)gateable);
-        atomicAdd(c + 2, (unsigned long long)n_blk);
+        if (ksel == 0) {
+            atomicAdd(c + 1, (unsigned long long)gateable);
+            atomicAdd(c + 2, (unsigned long long)n_blk);
+        }
+    }
+
+    // ---- the shares of a tile's key blocks put together: (m, l, O~) of every further share through LDS ----
+    if constexpr (KSP > 1) {
+        constexpr int PER_WAVE = 64 * (16 * DB + 2);      // floats
+        static_assert((KSP - 1) * NWH * HP * PER_WAVE * 4 <= (int)sizeof(lds_raw), "the tile slots hold the shares");
+        float *const part = reinterpret_cast<float *>(lds_raw);
+        wg_barrier();                                     // nobody reads the slots any more; the mask words are complete
+        if (p.skip_mask && ksel == 0)
+            for (int w = htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = lds_mask[hsel][w];
+        if (ksel > 0) {
+            float *const mine = part + ((ksel - 1) * NWH * HP + wave) * PER_WAVE + lane;
+#pragma unroll
+            for (int x = 0; x < DB; ++x)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) mine[(16 * x + e) * 64] = oacc[x][e];
+            mine[16 * DB * 64] = m_run;
+            mine[(16 * DB + 1) * 64] = l_run;
+        }
+        wg_barrier();
+        if (ksel > 0) return;
+#pragma unroll 1
+        for (int sh = 1; sh < KSP; ++sh) {
+            const float *const its = part + ((sh - 1) * NWH * HP + wave) * PER_WAVE + lane;
+            const float m_its = its[16 * DB * 64], m_new = fmaxf(m_run, m_its);
+            const float a_own = __builtin_amdgcn_exp2f(m_run - m_new), a_its = __builtin_amdgcn_exp2f(m_its - m_new);
+            m_run = m_new;
+            l_run = l_run * a_own + its[(16 * DB + 1) * 64] * a_its;
+#pragma unroll
+            for (int x = 0; x < DB; ++x)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) oacc[x][e] = oacc[x][e] * a_own + its[(16 * x + e) * 64] * a_its;
+        }
     }
 
     // ---- O_i = O~_i / l_i, written as bf16 ----------------------------------------------------
@@ -747,63 +863,113 @@ __global__ void __launch_bounds__(256) quantize_k_kernel(const FwdParams p)
     }
 }
 
-template <int D, int NWH, int HP, int KR, bool F16, bool VT, bool QK8>
-static hipError_t launch_k(const FwdParams &p, bool calib, hipStream_t stream, long grid)
+// workgroups of the work decomposition (decode_work), or 0 if they do not fit a launch
+template <int HP> static unsigned grid_size(const FwdParams &p)
 {
-    if (calib)
-        hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, KR, true, F16, false, QK8>), dim3((unsigned)grid), dim3(NWH * HP * 64), 0, stream, p);
-    else
-        hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, KR, false, F16, VT, QK8>), dim3((unsigned)grid), dim3(NWH * HP * 64), 0, stream, p);
+    const int pairs = p.batch * p.hkv, gsub = p.group / HP;
+    const long grid = (pairs >= 8) ? 8L * ((pairs + 7) / 8) * gsub * p.mq : (long)pairs * gsub * p.mq;
+    return grid > 0 && grid <= 0x7fffffffL ? (unsigned)grid : 0u;
+}
+
+// K -> workspace as fp8 tiles and V -> workspace as transposed tiles, as far as the call has room for them
+template <int D> static hipError_t launch_prepasses(const FwdParams &p, hipStream_t stream)
+{
+    if (!p.vt && !p.k8) return hipSuccess;
+    if (p.hkv > 65535 || p.batch > 65535) return hipErrorInvalidValue;    // grid y, z limits
+    const dim3 tiles((unsigned)p.mkv, (unsigned)p.hkv, (unsigned)p.batch);
+    if (p.vt) hipLaunchKernelGGL((transpose_v_kernel<D>), tiles, dim3(256), 0, stream, p);
+    if (p.k8 && p.f16) hipLaunchKernelGGL((quantize_k_kernel<true>), tiles, dim3(256), 0, stream, p);
+    if (p.k8 && !p.f16) hipLaunchKernelGGL((quantize_k_kernel<false>), tiles, dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 
-template <int D, int NWH, int HP, int KR>
-hipError_t launch_t(const FwdParams &p, bool calib, hipStream_t stream)
+// forward pass
+template <int D, int NWH, int HP, int KSP, int KR>
+hipError_t launch_fwd(const FwdParams &p, hipStream_t stream)
 {
-    const int pairs = p.batch * p.hkv;
-    const int gsub = p.group / HP;
-    long grid = (pairs >= 8) ? 8L * ((pairs + 7) / 8) * gsub * p.mq : (long)pairs * gsub * p.mq;
-    if (grid <= 0 || grid > 0x7fffffffL) return hipErrorInvalidValue;
+    const dim3 grid(grid_size<HP>(p)), threads(NWH * HP * KSP * 64);
+    if (grid.x == 0) return hipErrorInvalidValue;
     if (p.counts) {
         const int n = p.batch * p.hq * 3;
         hipLaunchKernelGGL(zero_counts_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, p.counts, n);
     }
-    if constexpr (NWH == 4) {          // the 128-row tile can take V (and fp8 K) from the workspace
-        if (p.k8 && !calib && !p.vt) return hipErrorInvalidValue;   // the fp8 score path always takes V from the workspace
-        if ((p.vt && !calib) || p.k8) {
-            if (p.hkv > 65535 || p.batch > 65535) return hipErrorInvalidValue;    // grid y, z limits
-            const dim3 tiles((unsigned)p.mkv, (unsigned)p.hkv, (unsigned)p.batch);
-            if (p.vt && !calib) hipLaunchKernelGGL((transpose_v_kernel<D>), tiles, dim3(256), 0, stream, p);
-            if constexpr (D == 128) {
-                if (p.k8) {
-                    if (p.f16) hipLaunchKernelGGL((quantize_k_kernel<true>), tiles, dim3(256), 0, stream, p);
-                    else hipLaunchKernelGGL((quantize_k_kernel<false>), tiles, dim3(256), 0, stream, p);
-                    hipError_t e = hipGetLastError();
-                    if (e != hipSuccess) return e;
-                    return p.f16 ? launch_k<D, NWH, HP, KR, true, true, true>(p, calib, stream, grid)
-                                 : launch_k<D, NWH, HP, KR, false, true, true>(p, calib, stream, grid);
-                }
-            }
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            return p.f16 ? launch_k<D, NWH, HP, KR, true, true, false>(p, calib, stream, grid) : launch_k<D, NWH, HP, KR, false, true, false>(p, calib, stream, grid);
+    constexpr bool WS = NWH == 4 && KSP == 1;          // V (and fp8 K) from the workspace, if the call has one
+    constexpr bool FP8 = WS && D == 128;
+    if (p.k8 && (!FP8 || !p.vt)) return hipErrorInvalidValue;
+    if constexpr (WS) {
+        const hipError_t e = launch_prepasses<D>(p, stream);
+        if (e != hipSuccess) return e;
+    }
+#define BSFA_LAUNCH(F16, VT, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, KSP, KR, false, F16, VT, QK8>), grid, threads, 0, stream, p)
+    if constexpr (FP8) {
+        if (p.k8) {
+            if (p.f16) BSFA_LAUNCH(true, true, true);
+            else BSFA_LAUNCH(false, true, true);
+            return hipGetLastError();
         }
     }
-    if (p.k8) return hipErrorInvalidValue;             // fp8 score operands need the 128 x 64 tile and head_dim 128
-    return p.f16 ? launch_k<D, NWH, HP, KR, true, false, false>(p, calib, stream, grid) : launch_k<D, NWH, HP, KR, false, false, false>(p, calib, stream, grid);
+    if constexpr (WS) {
+        if (p.vt) {
+            if (p.f16) BSFA_LAUNCH(true, true, false);
+            else BSFA_LAUNCH(false, true, false);
+            return hipGetLastError();
+        }
+    }
+    if (p.f16) BSFA_LAUNCH(true, false, false);
+    else BSFA_LAUNCH(false, false, false);
+#undef BSFA_LAUNCH
+    return hipGetLastError();
+}
+
+// score / block-maximum half (calibration)
+template <int D, int NWH, int HP, int KR>
+hipError_t launch_scores(const FwdParams &p, hipStream_t stream)
+{
+    const dim3 grid(grid_size<HP>(p)), threads(NWH * HP * 64);
+    if (grid.x == 0) return hipErrorInvalidValue;
+    constexpr bool FP8 = NWH == 4 && D == 128;
+    if (p.k8 && !FP8) return hipErrorInvalidValue;     // fp8 score operands need the 128 x 64 tile and head_dim 128
+#define BSFA_LAUNCH(F16, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, 1, KR, true, F16, false, QK8>), grid, threads, 0, stream, p)
+    if constexpr (FP8) {
+        if (p.k8) {
+            const hipError_t e = launch_prepasses<D>(p, stream);
+            if (e != hipSuccess) return e;
+            if (p.f16) BSFA_LAUNCH(true, true);
+            else BSFA_LAUNCH(false, true);
+            return hipGetLastError();
+        }
+    }
+    if (p.f16) BSFA_LAUNCH(true, false);
+    else BSFA_LAUNCH(false, false);
+#undef BSFA_LAUNCH
+    return hipGetLastError();
 }
 
 // The instantiations are spread over several translation units, compiled side by side from this one file:
 // BSFA_PART says which of them this one holds (0: the dispatch, none of them).
-#define BSFA_SHAPES_1(X) X(128, 4, 2, 5)
-#define BSFA_SHAPES_2(X) X(64, 4, 2, 5) X(64, 4, 1, 3)
-#define BSFA_SHAPES_3(X) X(128, 4, 1, 2)
-#define BSFA_SHAPES_4(X) X(128, 1, 1, 2) X(64, 1, 1, 2)
-#define BSFA_SHAPES_5(X) X(128, 2, 1, 2) X(64, 2, 1, 2)
-#define BSFA_EXTERN(D, N, H, K) extern template hipError_t launch_t<D, N, H, K>(const FwdParams &, bool, hipStream_t);
-#define BSFA_DEFINE(D, N, H, K) template hipError_t launch_t<D, N, H, K>(const FwdParams &, bool, hipStream_t);
+// F(head_dim, waves per head, heads, shares of the key blocks, K ring), S(head_dim, waves per head, heads, K ring)
+#define BSFA_SHAPES_1(F, S) F(128, 4, 1, 1, 2) F(128, 4, 2, 1, 5)
+#define BSFA_SHAPES_2(F, S) F(128, 4, 1, 2, 2) F(64, 4, 1, 1, 3) F(64, 4, 1, 2, 3)
+#define BSFA_SHAPES_3(F, S) S(128, 4, 2, 4) S(128, 4, 1, 2) S(64, 4, 1, 3) S(128, 2, 2, 2) S(128, 2, 1, 2) S(64, 2, 2, 4) S(64, 2, 1, 2)
+#define BSFA_SHAPES_4(F, S) F(128, 2, 2, 1, 2) F(128, 2, 1, 1, 2)
+#define BSFA_SHAPES_5(F, S) F(128, 2, 2, 2, 2) F(128, 2, 1, 2, 2)
+#define BSFA_SHAPES_6(F, S) F(64, 2, 2, 1, 4) F(64, 2, 1, 1, 2) F(64, 2, 1, 2, 2)
+#define BSFA_SHAPES_7(F, S) F(128, 1, 4, 1, 2) F(128, 1, 2, 1, 2) F(128, 1, 1, 1, 2)
+#define BSFA_SHAPES_8(F, S) F(64, 1, 4, 1, 4) F(64, 1, 2, 1, 4) F(64, 1, 1, 1, 2) S(128, 1, 4, 2) S(128, 1, 2, 2) S(128, 1, 1, 2) \
+                            S(64, 1, 4, 4) S(64, 1, 2, 4) S(64, 1, 1, 2)
+#define BSFA_EXTERN_F(D, N, H, P, K) extern template hipError_t launch_fwd<D, N, H, P, K>(const FwdParams &, hipStream_t);
+#define BSFA_EXTERN_S(D, N, H, K) extern template hipError_t launch_scores<D, N, H, K>(const FwdParams &, hipStream_t);
+#define BSFA_DEFINE_F(D, N, H, P, K) template hipError_t launch_fwd<D, N, H, P, K>(const FwdParams &, hipStream_t);
+#define BSFA_DEFINE_S(D, N, H, K) template hipError_t launch_scores<D, N, H, K>(const FwdParams &, hipStream_t);
 #if BSFA_PART == 0
-BSFA_SHAPES_1(BSFA_EXTERN) BSFA_SHAPES_2(BSFA_EXTERN) BSFA_SHAPES_3(BSFA_EXTERN) BSFA_SHAPES_4(BSFA_EXTERN) BSFA_SHAPES_5(BSFA_EXTERN)
+BSFA_SHAPES_1(BSFA_EXTERN_F, BSFA_EXTERN_S)
+BSFA_SHAPES_2(BSFA_EXTERN_F, BSFA_EXTERN_S)
+BSFA_SHAPES_3(BSFA_EXTERN_F, BSFA_EXTERN_S)
+BSFA_SHAPES_4(BSFA_EXTERN_F, BSFA_EXTERN_S)
+BSFA_SHAPES_5(BSFA_EXTERN_F, BSFA_EXTERN_S)
+BSFA_SHAPES_6(BSFA_EXTERN_F, BSFA_EXTERN_S)
+BSFA_SHAPES_7(BSFA_EXTERN_F, BSFA_EXTERN_S)
+BSFA_SHAPES_8(BSFA_EXTERN_F, BSFA_EXTERN_S)
 
 bool shape_supported(int head_dim, int block_m, int block_n)
 {
@@ -812,34 +978,84 @@ bool shape_supported(int head_dim, int block_m, int block_n)
     return block_m == 32 || block_m == 64 || block_m == 128;
 }
 
+// Which kernel a call gets.  Figures: bf16, 32 query heads over 8 KV heads, half skip, unless stated.
+//
+// `rows` -- query rows over all heads, twice as many without the causal mask -- is what the choice depends on: a
+// tile's key blocks are taken one after the other, so a call takes at least the longest tile's chain, and there
+// is work for the whole chip beside that chain only from rows of about 100 000 on (32 heads: 3K tokens).
+//  - Below that the key blocks of a tile are dealt to two sets of waves (KSP = 2): half the chain for the same
+//    work, at the price of a merge and of a K/V stream for each set.  1000 tokens 33.8 -> 20.9 us, 2048 tokens
+//    58 -> 46 us, 8K tokens of 4 heads 173 -> 90 us; at rows 73 600 (2300 tokens) it is 58 us against 53 us.
+//    V is read in place then, which saves the launch that would rewrite it.
+//  - Heads of a GQA group that share a workgroup share one K/V stream in LDS.  128-row tiles have waves enough
+//    without that, and two independent workgroups on a CU hide each other's barriers: single heads against pairs,
+//    8K tokens 2.8 % faster (dense 0 %), 16K 3.3 % (-0.7 %), 24K 2.8 % (-0.6 %).  But they read twice as much from
+//    L2 for a launch that the card's power limits, and beyond the L2 they drift apart in sequences many times its
+//    size: dense 32K tokens 0 to 2 % slower than pairs (half skip 1 % faster), dense without the mask 2.1 % at
+//    16K, 128K 2.5 % slower at half skip.  So heads are paired beyond 24K tokens, without the mask beyond 8K; with
+//    the fp8 score product, whose K stream is half as wide, beyond 64K (16K tokens 6 % faster single, 64K 2 %).
+//    With 64 rows at head_dim 128 two heads fill the CU's two waves per SIMD (8K tokens 654 -> 428 us), with 32 rows four (1358 -> 469 us; two
+//    heads 731 us).  At head_dim 64 the smaller tiles of single heads already do and sharing pays on long
+//    sequences only: 64 rows from rows 131 072 on (8K tokens 279 -> 271 us, 3K tokens 47 -> 55 us), 32 rows two
+//    heads always (2000 tokens 41 -> 34 us) and four from 81 920 on (8K tokens 368 -> 285 us, 2000: 34 -> 39 us).
+//  - The score half alone (calibration) has registers and LDS to spare and shares where it can; 128-row tiles
+//    from rows 262 144 on (6000 tokens 209 us either way, 32K tokens 3.50 ms in pairs).
+// Results do not depend on how heads share; the split does change the order of sums, so it must not depend on
+// single_head or on the workspace, between which results are equal bit for bit.
 hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool calib, hipStream_t stream)
 {
     if (!shape_supported(head_dim, block_m, kBlockN)) return hipErrorInvalidValue;
     // the copies address a tile with 32-bit byte offsets
     if (p.ksn * 128 > 0x7fff0000LL || p.vsn * 128 > 0x7fff0000LL) return hipErrorInvalidValue;
-    const bool pair_heads = (p.group % 2 == 0) && !p.single_head;
-#define BSFA_CASE(DD, NN, HH, KK) \
-    if (head_dim == DD && block_m == 32 * NN) return launch_t<DD, NN, HH, KK>(p, calib, stream);
-    if (pair_heads) {
-        // two query heads of a GQA group per workgroup: one K/V stream in LDS feeds both
-        BSFA_CASE(128, 4, 2, 5)
-        BSFA_CASE(64, 4, 2, 5)
+    const bool two = p.group % 2 == 0 && !p.single_head, four = p.group % 4 == 0 && !p.single_head;
+    const int64_t rows = (int64_t)p.batch * p.hq * p.seqlen * (p.causal ? 1 : 2);
+    const bool d128 = head_dim == 128;
+    if (calib) {
+        if (block_m == 128)
+            return !d128 ? launch_scores<64, 4, 1, 3>(p, stream)
+                 : two && rows > 262144 ? launch_scores<128, 4, 2, 4>(p, stream) : launch_scores<128, 4, 1, 2>(p, stream);
+        if (block_m == 64)
+            return d128 ? (two ? launch_scores<128, 2, 2, 2>(p, stream) : launch_scores<128, 2, 1, 2>(p, stream))
+                        : (two ? launch_scores<64, 2, 2, 4>(p, stream) : launch_scores<64, 2, 1, 2>(p, stream));
+        return d128 ? (four ? launch_scores<128, 1, 4, 2>(p, stream) : two ? launch_scores<128, 1, 2, 2>(p, stream) : launch_scores<128, 1, 1, 2>(p, stream))
+                    : (four ? launch_scores<64, 1, 4, 4>(p, stream) : two ? launch_scores<64, 1, 2, 4>(p, stream) : launch_scores<64, 1, 1, 2>(p, stream));
     }
-    BSFA_CASE(64, 1, 1, 2) BSFA_CASE(64, 2, 1, 2) BSFA_CASE(64, 4, 1, 3)
-    BSFA_CASE(128, 1, 1, 2) BSFA_CASE(128, 2, 1, 2) BSFA_CASE(128, 4, 1, 2)
-#undef BSFA_CASE
-    return hipErrorInvalidValue;
+    // (the comparison predicate depends on the order of the blocks; the mask words of a split tile must fit the LDS)
+    const bool split = !p.k8 && !p.gate_mode && p.mask_words <= kSplitMaskWords;
+    if (block_m == 128) {
+        if (split && rows <= 65536) return d128 ? launch_fwd<128, 4, 1, 2, 2>(p, stream) : launch_fwd<64, 4, 1, 2, 3>(p, stream);
+        if (d128 && two && p.seqlen > (p.k8 ? 65536 : p.causal ? 24576 : 8192)) return launch_fwd<128, 4, 2, 1, 5>(p, stream);
+        return d128 ? launch_fwd<128, 4, 1, 1, 2>(p, stream) : launch_fwd<64, 4, 1, 1, 3>(p, stream);
+    }
+    if (block_m == 64 && d128) {
+        // (two shares of one head are only four waves, and 128 KiB of LDS: one workgroup per CU)
+        if (split && rows <= (p.group % 2 == 0 ? 45056 : 32768)) return two ? launch_fwd<128, 2, 2, 2, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 2>(p, stream);
+        return two ? launch_fwd<128, 2, 2, 1, 2>(p, stream) : launch_fwd<128, 2, 1, 1, 2>(p, stream);
+    }
+    if (block_m == 64) {
+        if (split && rows <= 65536) return launch_fwd<64, 2, 1, 2, 2>(p, stream);
+        return two && rows > 131072 ? launch_fwd<64, 2, 2, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 1, 2>(p, stream);
+    }
+    if (d128) return four ? launch_fwd<128, 1, 4, 1, 2>(p, stream) : two ? launch_fwd<128, 1, 2, 1, 2>(p, stream) : launch_fwd<128, 1, 1, 1, 2>(p, stream);
+    return four && rows > 81920 ? launch_fwd<64, 1, 4, 1, 4>(p, stream) : two ? launch_fwd<64, 1, 2, 1, 4>(p, stream) : launch_fwd<64, 1, 1, 1, 2>(p, stream);
 }
+
 #elif BSFA_PART == 1
-BSFA_SHAPES_1(BSFA_DEFINE)
+BSFA_SHAPES_1(BSFA_DEFINE_F, BSFA_DEFINE_S)
 #elif BSFA_PART == 2
-BSFA_SHAPES_2(BSFA_DEFINE)
+BSFA_SHAPES_2(BSFA_DEFINE_F, BSFA_DEFINE_S)
 #elif BSFA_PART == 3
-BSFA_SHAPES_3(BSFA_DEFINE)
+BSFA_SHAPES_3(BSFA_DEFINE_F, BSFA_DEFINE_S)
 #elif BSFA_PART == 4
-BSFA_SHAPES_4(BSFA_DEFINE)
+BSFA_SHAPES_4(BSFA_DEFINE_F, BSFA_DEFINE_S)
 #elif BSFA_PART == 5
-BSFA_SHAPES_5(BSFA_DEFINE)
+BSFA_SHAPES_5(BSFA_DEFINE_F, BSFA_DEFINE_S)
+#elif BSFA_PART == 6
+BSFA_SHAPES_6(BSFA_DEFINE_F, BSFA_DEFINE_S)
+#elif BSFA_PART == 7
+BSFA_SHAPES_7(BSFA_DEFINE_F, BSFA_DEFINE_S)
+#elif BSFA_PART == 8
+BSFA_SHAPES_8(BSFA_DEFINE_F, BSFA_DEFINE_S)
 #endif
 
 }  // namespace bsfa

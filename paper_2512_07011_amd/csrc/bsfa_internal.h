@@ -7,6 +7,8 @@ namespace bsfa {
 
 // Key/value block rows; the library is built for B_N = 64 only.
 constexpr int kBlockN = 64;
+// Mask words of a query tile that a workgroup which splits the key blocks can put together (256K tokens).
+constexpr int kSplitMaskWords = 128;
 
 struct FwdParams {
     const uint16_t *q, *k, *v;       // bf16 or fp16 bit patterns (f16 says which)

@@ -1,0 +1,114 @@
+"""The kernels a call can be sent to (heads shared or not, key blocks of a tile dealt to two sets of waves or not)
+against each other, over the forms that each accepts."""
+import pytest
+import torch
+
+from paper_2512_07011_amd import binding
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def make(b, n, hq, hkv, d, layout, dtype, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    q, k, v = (torch.randn(b, n, h, d, generator=g, device=DEV).to(dtype) for h in (hq, hkv, hkv))
+    if layout == "qkv":                                     # slices of one fused projection
+        return torch.cat([q, k, v], dim=2).split([hq, hkv, hkv], dim=2)
+    if layout == "bhnd":
+        return tuple(t.transpose(1, 2).contiguous().transpose(1, 2) for t in (q, k, v))
+    return q, k, v
+
+
+def call(q, k, v, tau, bm, causal, dump=False, **kw):
+    st = binding.alloc_stats(q, bm, 64, counts=True, skip_mask=True, block_max=dump, lse=True)
+    st.lse.fill_(7.0)                                       # rows that do not exist keep it
+    out = torch.full_like(q.contiguous(), 7.0)
+    binding.bsfa_forward(q, k, v, tau, causal=causal, out=out, skip_stats=st, block_m=bm, **kw)
+    torch.cuda.synchronize()
+    return out, st.lse, st.counts, st.skip_mask
+
+
+# (b, n, hq, hkv, d, bm, causal, layout): every tile shape with an even, an odd and no group of heads; lengths around
+# tile and block edges, shares of the key blocks with no block, one block and an odd number of them
+CASES = [
+    (1, 1, 4, 2, 128, 128, True, "bnhd"), (1, 64, 4, 2, 128, 128, True, "bnhd"), (1, 65, 4, 2, 64, 128, True, "qkv"),
+    (1, 127, 2, 2, 64, 64, True, "bnhd"), (2, 129, 4, 1, 128, 64, True, "bhnd"), (1, 193, 3, 1, 128, 64, True, "qkv"),
+    (3, 1000, 8, 2, 128, 128, True, "qkv"), (1, 2047, 6, 2, 64, 64, True, "bnhd"), (2, 777, 4, 1, 64, 32, True, "bnhd"),
+    (1, 640, 4, 2, 128, 128, False, "bnhd"), (1, 320, 4, 2, 64, 64, False, "bhnd"), (2, 832, 6, 2, 128, 64, False, "bnhd"),
+    (1, 960, 8, 2, 128, 32, False, "qkv"), (1, 512, 4, 1, 64, 32, False, "bnhd"), (1, 4096, 2, 1, 128, 128, False, "bnhd"),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_small_calls_agree_with_every_other_form(case):
+    """One call by itself against (a) the same with the block maxima dumped (general stages only), bit for bit; (b) one
+    head per workgroup, bit for bit; (c) the same element inside a batch large enough for the kernels that do not split
+    a tile's key blocks: decisions bit for bit (the scores are the same sums in the same order), out and lse up to the
+    rounding of P, of the row sums over rounded P, and of the result: 2^-9 relative each on either side, so 2^-7 of the
+    largest |V| for out and 2^-8 for lse, bf16."""
+    b, n, hq, hkv, d, bm, causal, layout = case
+    q, k, v = make(b, n, hq, hkv, d, layout, torch.bfloat16, n)
+    tau = binding.bsfa_calibrate(q, k, [0.5], causal=causal, block_m=bm)[0]
+    tau = torch.where(tau.isfinite(), tau, torch.zeros_like(tau)).to(DEV)
+    alone = call(q, k, v, tau, bm, causal)
+    for other in (call(q, k, v, tau, bm, causal, dump=True), call(q, k, v, tau, bm, causal, single_head_groups=True)):
+        for x, y in zip(alone, other):
+            assert torch.equal(x, y)
+    if n > 256:
+        assert alone[2][..., 0].sum() > 0                   # something is skipped
+    times = 1 + 150000 // (b * hq * n * (1 if causal else 2))
+    if times * b * 4 > 60000:                               # (a single token: the batch would not fit a launch)
+        times = 60000 // (4 * b)
+    many = call(*(t.repeat(times, 1, 1, 1) for t in (q, k, v)), tau, bm, causal)
+    for lo in (0, (times - 1) * b):
+        out, lse, counts, mask = (x[lo:lo + b] for x in many)
+        assert torch.equal(mask, alone[3]) and torch.equal(counts, alone[2])
+        assert (out.float() - alone[0].float()).abs().max() <= 2.0 ** -7 * v.float().abs().max()
+        assert (lse - alone[1]).abs().max() <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("d, bm", [(128, 128), (64, 128), (128, 64), (64, 64)])
+def test_split_tiles_with_lengths_and_thresholds_per_tile(d, bm):
+    """Batch elements of different lengths (empty, one token, ends of tiles and blocks) and thresholds per query tile
+    through the kernels that split a tile's key blocks, against one call per element at its own length."""
+    n, hq, hkv = 700, 4, 2
+    lengths = [0, 1, 63, 64, 129, 447, 640, 700]
+    q, k, v = make(len(lengths), n, hq, hkv, d, "bnhd", torch.float16, d + bm)
+    g = torch.Generator().manual_seed(bm)
+    tau = (3.0 + torch.rand(hq, -(-n // bm), generator=g)).to(DEV)
+    sl = torch.tensor(lengths, dtype=torch.int32, device=DEV)
+    out, lse, counts, mask = call(q, k, v, tau, bm, True, seqlens=sl)
+    for e, m in enumerate(lengths):
+        assert (out[e, m:] == 7.0).all() and (lse[e, m:] == 7.0).all()
+        if m == 0:
+            assert (counts[e] == 0).all() and (mask[e] == 0).all()
+            continue
+        one = call(*(t[e:e + 1, :m] for t in (q, k, v)), tau, bm, True)
+        assert torch.equal(out[e, :m], one[0][0]) and torch.equal(lse[e, :m], one[1][0]) and torch.equal(counts[e], one[2][0])
+        tiles, words = one[3].shape[2:]
+        assert torch.equal(mask[e, :, :tiles, :words], one[3][0]) and (mask[e, :, tiles:] == 0).all() and (mask[e, :, :tiles, words:] == 0).all()
+
+
+@pytest.mark.parametrize("hq, hkv, n, d, bm", [(32, 8, 2304, 128, 64), (32, 8, 4160, 64, 64), (32, 8, 2624, 64, 32), (8, 2, 1024, 128, 32),
+                                                 (4, 2, 24640, 128, 128)])
+def test_shared_heads_are_bit_identical(hq, hkv, n, d, bm):
+    """Two and four heads to a workgroup against one, fast stages and all, on problems large enough to be sent there."""
+    q, k, v = make(1, n, hq, hkv, d, "bnhd", torch.bfloat16, n)
+    for tau in (binding.bsfa_calibrate(q, k, [0.6], block_m=bm)[0].to(DEV), torch.full((hq,), float("-inf"), device=DEV)):
+        for x, y in zip(call(q, k, v, tau, bm, True), call(q, k, v, tau, bm, True, single_head_groups=True)):
+            assert torch.equal(x, y)
+
+
+def test_running_maximum_over_large_score_ranges():
+    """Rows whose maximum grows with every block, only in the first one, and hardly at all, with scores of several
+    hundred: finite, and equal to softmax in 64 bits (2e-2, the bound of every parity test; for lse the rounding of P
+    and 32-bit scores)."""
+    n, d = 1024, 128
+    q, k, v = make(1, n, 1, 1, d, "bnhd", torch.bfloat16, 3)
+    ramp = torch.linspace(0.2, 30.0, n, device=DEV)[None, :, None, None]
+    for scale in (ramp, ramp.flip(1), torch.full_like(ramp, 1e-3)):
+        ks = (k.float() * scale).to(torch.bfloat16)
+        out, lse, _, _ = call(q, ks, v, torch.full((1,), float("-inf"), device=DEV), 128, True)
+        s = (q[0, :, 0].double() @ ks[0, :, 0].double().t() / d ** 0.5).masked_fill(torch.ones(n, n, device=DEV).triu(1).bool(), float("-inf"))
+        assert (out[0, :, 0].double() - s.softmax(-1) @ v[0, :, 0].double()).abs().max() <= 2e-2
+        assert (lse[0, :, 0].double() - s.logsumexp(-1)).abs().max() <= 2.0 ** -8 + 1e-6 * s[s.isfinite()].abs().max()
