@@ -115,19 +115,14 @@ def make_problem(q: torch.Tensor, k: torch.Tensor, v: Optional[torch.Tensor], ou
                  seqlens: Optional[torch.Tensor] = None, single_head_groups: bool = False) -> bsfa_problem:
     """Descriptor for [B, N, H, d] views (any strides with a contiguous last dimension)."""
     B, N, Hq, d = q.shape
-    p = bsfa_problem()
-    p.batch, p.seqlen, p.n_q_heads, p.n_kv_heads, p.head_dim = B, N, Hq, k.shape[2], d
-    p.block_m, p.block_n = block_m, block_n
-    for name, t in (("q", q), ("k", k), ("v", v if v is not None else k), ("o", out if out is not None else q)):
-        if t.stride(3) != 1:
-            raise ValueError("%s: head dimension must be contiguous" % name)
-        setattr(p, name + "_stride_b", t.stride(0))
-        setattr(p, name + "_stride_n", t.stride(1))
-        setattr(p, name + "_stride_h", t.stride(2))
-    p.dtype = DTYPES[q.dtype]
-    p.thresholds_per_tile = int(thresholds_per_tile)
-    p.threshold_tiles = int(threshold_tiles)
-    p.single_head_groups = int(bool(single_head_groups))
+    qs, ks = q.stride(), k.stride()
+    vs, os_ = v.stride() if v is not None else ks, out.stride() if out is not None else qs
+    if qs[3] != 1 or ks[3] != 1 or vs[3] != 1 or os_[3] != 1:
+        name = "qkvo"[[t[3] != 1 for t in (qs, ks, vs, os_)].index(True)]
+        raise ValueError("%s: head dimension must be contiguous" % name)
+    # (members in order; one call: setting them one by one is a quarter of a small forward call's host time)
+    p = bsfa_problem(B, Hq, k.shape[2], N, d, block_m, block_n, *qs[:3], *ks[:3], *vs[:3], *os_[:3], DTYPES[q.dtype],
+                     int(thresholds_per_tile), int(threshold_tiles), None, int(bool(single_head_groups)))
     if seqlens is not None:
         if seqlens.dtype != torch.int32 or not seqlens.is_contiguous() or tuple(seqlens.shape) != (B,) or not seqlens.is_cuda:
             raise TypeError("bsfa: seqlens must be a contiguous int32 GPU tensor of shape [batch]")
@@ -193,6 +188,14 @@ def _dev_check(*ts):
             raise ValueError("bsfa: tensors must live on the GPU")
 
 
+def _raw_stream(stream, device) -> int:
+    """hipStream_t of ``stream``, or of torch's current stream on ``device`` (asked for without building a
+    stream object: 0.2 us instead of 1.9)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
 def bsfa_forward(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, thresholds: torch.Tensor,
                  causal: bool = True, out: Optional[torch.Tensor] = None,
                  skip_stats: Optional[SkipStats] = None, block_m: int = 128, block_n: int = 64,
@@ -207,36 +210,37 @@ def bsfa_forward(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, thresholds: 
     running-maximum comparison predicate (thresholds then hold its lambda).  Enqueues on ``stream`` (default:
     torch's current stream)."""
     _dev_check(q, k, v, thresholds, out)
-    _same_16bit("bsfa_forward", q, k, v, *([out] if out is not None else []))
+    if out is None:
+        _same_16bit("bsfa_forward", q, k, v)
+    else:
+        _same_16bit("bsfa_forward", q, k, v, out)
     if thresholds.dtype != torch.float32 or not thresholds.is_contiguous():
         raise TypeError("bsfa_forward: thresholds must be contiguous float32")
-    per_tile = thresholds.dim() == 2
-    B, N, Hq, d = q.shape
-    if thresholds.dim() not in (1, 2) or thresholds.shape[0] != Hq or (per_tile and thresholds.shape[1] < 1):
-        raise ValueError("bsfa_forward: thresholds shape %s, expected [Hq] or [Hq, tiles]" % (tuple(thresholds.shape),))
+    ts = thresholds.shape
+    per_tile = len(ts) == 2
+    if len(ts) not in (1, 2) or ts[0] != q.shape[2] or (per_tile and ts[1] < 1):
+        raise ValueError("bsfa_forward: thresholds shape %s, expected [Hq] or [Hq, tiles]" % (tuple(ts),))
     if out is None:
         out = torch.empty_like(q)
-    p = make_problem(q, k, v, out, block_m, block_n, per_tile, thresholds.shape[1] if per_tile else 0, seqlens,
-                     single_head_groups)
+    L = lib()
+    p = make_problem(q, k, v, out, block_m, block_n, per_tile, ts[1] if per_tile else 0, seqlens, single_head_groups)
     p.gate_mode = int(gate_mode)
     p.qk_fp8 = int(bool(qk_fp8))
+    pref = ctypes.byref(p)
     if workspace is True:
-        workspace = _cached_workspace(q.device, lib().bsfa_forward_workspace_bytes(ctypes.byref(p)))
+        workspace = _cached_workspace(q.device, L.bsfa_forward_workspace_bytes(pref))
     if workspace is not None and workspace is not False:
         _dev_check(workspace)
         p.workspace = workspace.data_ptr()
         p.workspace_bytes = workspace.numel() * workspace.element_size()
     st = None
     if skip_stats is not None:
-        st = bsfa_skip_stats(
-            skip_stats.counts.data_ptr() if skip_stats.counts is not None else None,
-            skip_stats.skip_mask.data_ptr() if skip_stats.skip_mask is not None else None,
-            skip_stats.block_max.data_ptr() if skip_stats.block_max is not None else None,
-            skip_stats.lse.data_ptr() if skip_stats.lse is not None else None)
-    s = stream if stream is not None else torch.cuda.current_stream(q.device)
-    _check(lib().bsfa_forward(ctypes.byref(p), q.data_ptr(), k.data_ptr(), v.data_ptr(), thresholds.data_ptr(),
-                              int(bool(causal)), out.data_ptr(), ctypes.byref(st) if st is not None else None,
-                              ctypes.c_void_p(s.cuda_stream)))
+        st = ctypes.byref(bsfa_skip_stats(*[None if t is None else t.data_ptr() for t in (
+            skip_stats.counts, skip_stats.skip_mask, skip_stats.block_max, skip_stats.lse)]))
+    rc = L.bsfa_forward(pref, q.data_ptr(), k.data_ptr(), v.data_ptr(), thresholds.data_ptr(), 1 if causal else 0,
+                        out.data_ptr(), st, _raw_stream(stream, q.device))
+    if rc != BSFA_OK:
+        _check(rc)
     return out
 
 
