@@ -800,6 +800,8 @@ __global__ void __launch_bounds__(256) transpose_v_kernel(const FwdParams p)
     constexpr int BN = kBlockN, CPR = D / 8, LD = D + 8;
     __shared__ __attribute__((aligned(16))) uint16_t tile[BN * LD];
     const int j = blockIdx.x, g = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    if (p.counts && j == 0 && g == 0 && b == 0)       // (saves the launch that would clear them)
+        for (int t = tid; t < p.batch * p.hq * 3; t += 256) p.counts[t] = 0ull;
     int n_tok = p.seqlen;
     if (p.seqlens) n_tok = min(max(p.seqlens[b], 0), p.seqlen);
     if (j * BN >= n_tok) return;
@@ -889,13 +891,13 @@ hipError_t launch_fwd(const FwdParams &p, hipStream_t stream)
 {
     const dim3 grid(grid_size<HP>(p)), threads(NWH * HP * KSP * 64);
     if (grid.x == 0) return hipErrorInvalidValue;
-    if (p.counts) {
-        const int n = p.batch * p.hq * 3;
-        hipLaunchKernelGGL(zero_counts_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, p.counts, n);
-    }
     constexpr bool WS = NWH == 4 && KSP == 1;          // V (and fp8 K) from the workspace, if the call has one
     constexpr bool FP8 = WS && D == 128;
     if (p.k8 && (!FP8 || !p.vt)) return hipErrorInvalidValue;
+    if (p.counts && !(WS && p.vt)) {                   // (the pass over V clears them)
+        const int n = p.batch * p.hq * 3;
+        hipLaunchKernelGGL(zero_counts_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, p.counts, n);
+    }
     if constexpr (WS) {
         const hipError_t e = launch_prepasses<D>(p, stream);
         if (e != hipSuccess) return e;
