@@ -198,31 +198,28 @@ template <int N, class F> __device__ __forceinline__ void static_for(F &&f)
 // workgroup id, which is the XCD the hardware dispatches the group to, so that all groups
 // streaming one K/V sequence share one L2.  Heavy (late) query tiles first.
 template <int HP>
-__device__ __forceinline__ bool decode_work(const FwdParams &p, int w, int &b, int &h0, int &i)
+__device__ __forceinline__ bool decode_work(const FwdParams &p, uint32_t w, int &b, int &g, int &h0, int &i)
 {
     const int pairs = p.batch * p.hkv;
-    const int gsub = p.group / HP;               // head groups per KV head
-    int pair, hg, idesc;
+    const int gsub = p.group / HP;               // head groups per KV head (HP: 1, 2 or 4)
+    uint32_t idesc, rest, pl;
     if (pairs >= 8) {
-        const int x = w & 7, r = w >> 3;
         const int npx = (pairs + 7) >> 3;
-        const int per_tile = npx * gsub;
-        idesc = r / per_tile;
-        const int rest = r - idesc * per_tile;
-        const int pl = rest / gsub;
-        hg = rest - pl * gsub;
-        pair = x + 8 * pl;
-        if (pair >= pairs) return false;
+        idesc = p.div_tile.of(w >> 3);
+        rest = (w >> 3) - idesc * (uint32_t)(npx * gsub);
+        pl = p.div_gsub.of(rest);
+        g = (int)((w & 7) + 8 * pl);
+        if (g >= pairs) return false;
     } else {
-        const int per_tile = pairs * gsub;
-        idesc = w / per_tile;
-        const int rest = w - idesc * per_tile;
-        pair = rest / gsub;
-        hg = rest - pair * gsub;
+        idesc = p.div_tile.of(w);
+        rest = w - idesc * (uint32_t)(pairs * gsub);
+        pl = p.div_gsub.of(rest);
+        g = (int)pl;
     }
-    b = pair / p.hkv;
-    h0 = (pair - b * p.hkv) * p.group + hg * HP;
-    i = p.mq - 1 - idesc;
+    b = (int)p.div_hkv.of((uint32_t)g);
+    g -= b * p.hkv;
+    h0 = g * p.group + (int)(rest - pl * (uint32_t)gsub) * HP;
+    i = p.mq - 1 - (int)idesc;
     return true;
 }
 

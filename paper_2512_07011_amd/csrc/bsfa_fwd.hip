@@ -87,8 +87,8 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     __shared__ __attribute__((aligned(8))) uint8_t lds_flag[2][NW];   // the waves' keep flags
     __shared__ uint32_t lds_mask[HP][KSP > 1 ? kSplitMaskWords : 1];  // KSP > 1: the tiles' skip masks, put together
 
-    int b, h0, i;
-    if (!decode_work<HP>(p, blockIdx.x, b, h0, i)) return;
+    int b, g, h0, i;
+    if (!decode_work<HP>(p, blockIdx.x, b, g, h0, i)) return;
     const int lane = threadIdx.x & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ksel = KSP > 1 ? wave_all / (NWH * HP) : 0;   // which share of the key blocks: those with j % KSP == ksel
@@ -101,7 +101,6 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     const uint32_t lds_flag0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint8_t *)lds_flag);
     const int h = h0 + hsel;
     const int l32 = lane & 31, hh = lane >> 5;
-    const int g = h0 / p.group;
     const bool stat_lane = (wrow == 0 && lane == 0);     // one lane per head writes statistics
 
     const int64_t row0 = (int64_t)i * BM;                 // first query row of the tile
@@ -210,6 +209,12 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // (row parity, chunk) slots), and at twice the LDS rate of the transposing reads.
     const uint32_t va_base = VT ? (uint32_t)(l32 * 128 + ((hh ^ ((l32 >> 1) & 7)) << 4))
                                 : (uint32_t)(vrow * ROW_BYTES + (((vcol >> 3) ^ swz_v<D>(vrow)) << 4) + ((vcol >> 2) & 1) * 8);
+
+    // All K tiles the ring holds are requested before anything else, and what follows block 0 (V_0, K_{R-1}) is left
+    // in flight for the first stage: one trip to memory before the pipeline starts instead of two.
+#pragma unroll
+    for (int t = 0; t < KR; ++t)
+        if (t < n_own) copy_k(t, lds_k0 + (uint32_t)t * TILE_BYTES);
 
     // Q_i^T as the B operand: lane holds query (32*wrow + l32), head-dim slice 16s + 8hh .. +7
     // (QK8: slice 64s + 32hh .. +31, rounded to fp8 here, once)
@@ -655,12 +660,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     };
 
     // ---- prologue: scores and decision of block 0 -----------------------------------------------
-    // All K tiles the ring holds are requested at once with K_0, and what follows (V_0, K_{R-1}) is left in flight
-    // for the first stage: one trip to memory before the pipeline starts instead of two.
     ScoreTile ta, tb;
-#pragma unroll
-    for (int t = 0; t < KR; ++t)
-        if (t < n_own) copy_k(t, lds_k0 + (uint32_t)t * TILE_BYTES);
     wait_vmcnt<0>();
     wg_barrier();
     prefetch_k(lds_k0);
@@ -762,22 +762,39 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     if constexpr (!CALIB) {
         const float l_tot = l_run + __shfl_xor(l_run, 32);
         const float inv = 1.0f / l_tot;
-        if (q_row >= n_tok) return;     // padding rows of the last tile are not stored
-        if (p.lse && hh == 0)           // L = m + log(l); m_run is in log2 units
+        if (p.lse && hh == 0 && q_row < n_tok)      // L = m + log(l); m_run is in log2 units
             p.lse[((int64_t)b * p.seqlen + q_row) * p.hq + h] = m_run * 0.6931471805599453f + __logf(l_tot);
-        uint16_t *op = p.out + (int64_t)b * p.osb + (int64_t)q_row * p.osn + (int64_t)h * p.osh;
+        // The wave's 32 rows go through LDS, so that a store instruction writes whole rows instead of 16 bytes of each
+        // (32 rows of 16 bytes at a time the epilogue took 2.5 us of a workgroup at 128 x 128, all of it waiting for
+        // addresses).  Their place is free: the K ring, which nobody reads after the barrier of the last stage, or the
+        // share this wave has just merged.  16-byte chunks are XOR-ed with the row as in the K tiles.
+        static_assert(KSP > 1 || NWH * HP * 32 * ROW_BYTES <= KR * TILE_BYTES, "the K ring holds the output rows");
+        const uint32_t o_lds = KSP > 1 ? (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw) + wave * (64 * (16 * DB + 2) * 4)
+                                       : lds_k0 + wave * (32 * ROW_BYTES);
+        const uint32_t o_row = o_lds + l32 * ROW_BYTES + 8 * hh;
+        asm volatile("" ::: "memory");              // (a merged share has been read; one wave's LDS accesses complete in order)
 #pragma unroll
         for (int x = 0; x < DB; ++x)
 #pragma unroll
             for (int e4 = 0; e4 < 4; ++e4) {
                 // O^T row 8*e4 + 4hh + e of block x -> head-dim column (see the V operand mapping)
-                const int m0 = 8 * e4 + 4 * hh;
+                const int m0 = 8 * e4;
                 const int d0 = VT ? 32 * x + m0 : X_COLS * x + (m0 < 16 ? m0 : G16_COLS + m0 - 16);
                 bf16x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = (el)(oacc[x][4 * e4 + e] * inv);
-                *reinterpret_cast<bf16x4 *>(op + d0) = o;
+                *LDS_PTR(bf16x4, o_row + (((d0 >> 3) ^ swz_k<D>(l32)) << 4)) = o;
             }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        uint16_t *op = p.out + (int64_t)b * p.osb + (int64_t)h * p.osh;
+#pragma unroll
+        for (int it = 0; it < 32 * CPR / 64; ++it) {
+            const int row = it * (64 / CPR) + lane / CPR, c = lane % CPR;
+            const i32x4 o = *LDS_PTR(const i32x4, o_lds + row * ROW_BYTES + ((c ^ swz_k<D>(row)) << 4));
+            const int token = (int)row0 + wrow * 32 + row;
+            if (token < n_tok) *reinterpret_cast<i32x4 *>(op + (int64_t)token * p.osn + 8 * c) = o;   // (padding rows of the last tile are not stored)
+        }
     }
 }
 
@@ -865,12 +882,17 @@ __global__ void __launch_bounds__(256) quantize_k_kernel(const FwdParams p)
     }
 }
 
-// workgroups of the work decomposition (decode_work), or 0 if they do not fit a launch
-template <int HP> static unsigned grid_size(const FwdParams &p)
+// the call's parameters with the divisors of the work decomposition (decode_work), and its workgroups (0: they do
+// not fit a launch)
+template <int HP> static unsigned decompose(FwdParams &p)
 {
-    const int pairs = p.batch * p.hkv, gsub = p.group / HP;
-    const long grid = (pairs >= 8) ? 8L * ((pairs + 7) / 8) * gsub * p.mq : (long)pairs * gsub * p.mq;
-    return grid > 0 && grid <= 0x7fffffffL ? (unsigned)grid : 0u;
+    const long pairs = (long)p.batch * p.hkv, gsub = p.group / HP;
+    const long per_tile = (pairs >= 8 ? (pairs + 7) / 8 : pairs) * gsub, wide = pairs >= 8 ? 8 : 1;
+    if (pairs <= 0 || per_tile <= 0 || per_tile * wide * p.mq > 0x7fffffffL) return 0u;
+    p.div_tile = fast_div((uint32_t)per_tile);
+    p.div_gsub = fast_div((uint32_t)gsub);
+    p.div_hkv = fast_div((uint32_t)p.hkv);
+    return (unsigned)(per_tile * wide * p.mq);
 }
 
 // K -> workspace as fp8 tiles and V -> workspace as transposed tiles, as far as the call has room for them
@@ -887,9 +909,10 @@ template <int D> static hipError_t launch_prepasses(const FwdParams &p, hipStrea
 
 // forward pass
 template <int D, int NWH, int HP, int KSP, int KR>
-hipError_t launch_fwd(const FwdParams &p, hipStream_t stream)
+hipError_t launch_fwd(const FwdParams &params, hipStream_t stream)
 {
-    const dim3 grid(grid_size<HP>(p)), threads(NWH * HP * KSP * 64);
+    FwdParams p = params;
+    const dim3 grid(decompose<HP>(p)), threads(NWH * HP * KSP * 64);
     if (grid.x == 0) return hipErrorInvalidValue;
     constexpr bool WS = NWH == 4 && KSP == 1;          // V (and fp8 K) from the workspace, if the call has one
     constexpr bool FP8 = WS && D == 128;
@@ -925,9 +948,10 @@ hipError_t launch_fwd(const FwdParams &p, hipStream_t stream)
 
 // score / block-maximum half (calibration)
 template <int D, int NWH, int HP, int KR>
-hipError_t launch_scores(const FwdParams &p, hipStream_t stream)
+hipError_t launch_scores(const FwdParams &params, hipStream_t stream)
 {
-    const dim3 grid(grid_size<HP>(p)), threads(NWH * HP * 64);
+    FwdParams p = params;
+    const dim3 grid(decompose<HP>(p)), threads(NWH * HP * 64);
     if (grid.x == 0) return hipErrorInvalidValue;
     constexpr bool FP8 = NWH == 4 && D == 128;
     if (p.k8 && !FP8) return hipErrorInvalidValue;     // fp8 score operands need the 128 x 64 tile and head_dim 128

@@ -10,6 +10,20 @@ constexpr int kBlockN = 64;
 // Mask words of a query tile that a workgroup which splits the key blocks can put together (256K tokens).
 constexpr int kSplitMaskWords = 128;
 
+// Division of numbers below 2^31 by a number fixed at launch: a multiplication and a shift (of the 64-bit
+// product), exact because the multiplier exceeds 2^(31+s) / d by less than 2^s / d (Granlund and Montgomery,
+// "Division by invariant integers using multiplication", Theorem 4.2).
+struct FastDiv {
+    uint32_t mul, shift;
+    __host__ __device__ uint32_t of(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> shift); }
+};
+inline FastDiv fast_div(uint32_t d)               // 1 <= d < 2^31
+{
+    uint32_t s = 0;
+    while ((1ull << s) < d) ++s;
+    return {(uint32_t)(((1ull << (31 + s)) + d - 1) / d), 31 + s};
+}
+
 struct FwdParams {
     const uint16_t *q, *k, *v;       // bf16 or fp16 bit patterns (f16 says which)
     uint16_t *out;
@@ -32,6 +46,8 @@ struct FwdParams {
     float *block_max;                // [batch][hq][mq][mkv] or null
     float *lse;                      // [batch][seqlen][hq] or null
     int mask_words;
+    FastDiv div_tile, div_gsub, div_hkv;   // work decomposition (decode_work): work items per query tile, head groups per
+                                           // KV head, KV heads; set by the launch
 };
 
 // Launches the forward kernel (calib == false) or its score/block-maximum half only
