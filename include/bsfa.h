@@ -110,7 +110,8 @@ typedef struct {
                                      16-bit ones by a few hundredths. */
     void   *workspace;            /* optional, DEVICE, 256-byte aligned, bsfa_forward only: scratch memory of at
                                      least bsfa_forward_workspace_bytes() bytes, overwritten by every call.
-                                     With it (and block_m = 128) the forward pass first rewrites V, once, as
+                                     Where it pays (block_m = 128, head_dim 128, more than 12K tokens, or
+                                     qk_fp8) the forward pass first rewrites V into it, once, as
                                      transposed 64-key tiles (an O(N) pass: 2 x the size of V in traffic) so
                                      that the second matrix product reads its V operand from on-chip memory
                                      with full-width reads; the per-(tile, block) V loads stay conditional on

@@ -65,6 +65,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     typedef typename Elem<F16>::x4 bf16x4;
     typedef typename Elem<F16>::x2 bf16x2;
     static_assert(KSP == 1 || (!CALIB && !VT && !QK8), "shares of the key blocks: V in place");
+    static_assert(!VT || D == 128, "V from the workspace: head_dim 128");
     constexpr int NW = NWH * HP * KSP;
     constexpr int NT = NWH * HP * 64;                    // threads that share one stream of K and V tiles
     constexpr int BM = NWH * 32;
@@ -811,10 +812,9 @@ static __global__ void zero_counts_kernel(unsigned long long *c, int n)
 // (row >> 1) & 7.  Rows at and beyond the sequence end repeat the last token (Section 4.3), so the
 // tile of a partial block holds finite values everywhere; blocks that lie entirely beyond the end
 // are never read and are not written.  One workgroup per tile, through LDS.
-template <int D>
-__global__ void __launch_bounds__(256) transpose_v_kernel(const FwdParams p)
+static __global__ void __launch_bounds__(256) transpose_v_kernel(const FwdParams p)
 {
-    constexpr int BN = kBlockN, CPR = D / 8, LD = D + 8;
+    constexpr int BN = kBlockN, D = 128, CPR = D / 8, LD = D + 8;
     __shared__ __attribute__((aligned(16))) uint16_t tile[BN * LD];
     const int j = blockIdx.x, g = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     if (p.counts && j == 0 && g == 0 && b == 0)       // (saves the launch that would clear them)
@@ -896,12 +896,12 @@ template <int HP> static unsigned decompose(FwdParams &p)
 }
 
 // K -> workspace as fp8 tiles and V -> workspace as transposed tiles, as far as the call has room for them
-template <int D> static hipError_t launch_prepasses(const FwdParams &p, hipStream_t stream)
+static hipError_t launch_prepasses(const FwdParams &p, hipStream_t stream)
 {
     if (!p.vt && !p.k8) return hipSuccess;
     if (p.hkv > 65535 || p.batch > 65535) return hipErrorInvalidValue;    // grid y, z limits
     const dim3 tiles((unsigned)p.mkv, (unsigned)p.hkv, (unsigned)p.batch);
-    if (p.vt) hipLaunchKernelGGL((transpose_v_kernel<D>), tiles, dim3(256), 0, stream, p);
+    if (p.vt) hipLaunchKernelGGL(transpose_v_kernel, tiles, dim3(256), 0, stream, p);
     if (p.k8 && p.f16) hipLaunchKernelGGL((quantize_k_kernel<true>), tiles, dim3(256), 0, stream, p);
     if (p.k8 && !p.f16) hipLaunchKernelGGL((quantize_k_kernel<false>), tiles, dim3(256), 0, stream, p);
     return hipGetLastError();
@@ -914,26 +914,23 @@ hipError_t launch_fwd(const FwdParams &params, hipStream_t stream)
     FwdParams p = params;
     const dim3 grid(decompose<HP>(p)), threads(NWH * HP * KSP * 64);
     if (grid.x == 0) return hipErrorInvalidValue;
-    constexpr bool WS = NWH == 4 && KSP == 1;          // V (and fp8 K) from the workspace, if the call has one
-    constexpr bool FP8 = WS && D == 128;
-    if (p.k8 && (!FP8 || !p.vt)) return hipErrorInvalidValue;
+    constexpr bool WS = NWH == 4 && KSP == 1 && D == 128;      // V (and fp8 K) from the workspace, if the call has one
+    if (p.k8 && (!WS || !p.vt)) return hipErrorInvalidValue;
     if (p.counts && !(WS && p.vt)) {                   // (the pass over V clears them)
         const int n = p.batch * p.hq * 3;
         hipLaunchKernelGGL(zero_counts_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, p.counts, n);
     }
     if constexpr (WS) {
-        const hipError_t e = launch_prepasses<D>(p, stream);
+        const hipError_t e = launch_prepasses(p, stream);
         if (e != hipSuccess) return e;
     }
 #define BSFA_LAUNCH(F16, VT, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, KSP, KR, false, F16, VT, QK8>), grid, threads, 0, stream, p)
-    if constexpr (FP8) {
+    if constexpr (WS) {
         if (p.k8) {
             if (p.f16) BSFA_LAUNCH(true, true, true);
             else BSFA_LAUNCH(false, true, true);
             return hipGetLastError();
         }
-    }
-    if constexpr (WS) {
         if (p.vt) {
             if (p.f16) BSFA_LAUNCH(true, true, false);
             else BSFA_LAUNCH(false, true, false);
@@ -958,7 +955,7 @@ hipError_t launch_scores(const FwdParams &params, hipStream_t stream)
 #define BSFA_LAUNCH(F16, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, 1, KR, true, F16, false, QK8>), grid, threads, 0, stream, p)
     if constexpr (FP8) {
         if (p.k8) {
-            const hipError_t e = launch_prepasses<D>(p, stream);
+            const hipError_t e = launch_prepasses(p, stream);
             if (e != hipSuccess) return e;
             if (p.f16) BSFA_LAUNCH(true, true);
             else BSFA_LAUNCH(false, true);
@@ -1012,7 +1009,11 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //  - Below that the key blocks of a tile are dealt to two sets of waves (KSP = 2): half the chain for the same
 //    work, at the price of a merge and of a K/V stream for each set.  1000 tokens 33.8 -> 20.9 us, 2048 tokens
 //    58 -> 46 us, 8K tokens of 4 heads 173 -> 90 us; at rows 73 600 (2300 tokens) it is 58 us against 53 us.
-//    V is read in place then, which saves the launch that would rewrite it.
+//    (The line is drawn for half skip; dense it would lie higher: 2048 tokens 48 us split, 53 us not.)
+//  - V is rewritten into the workspace only where the pass over it pays for itself, which takes its reuse by many
+//    query tiles: head_dim 128 beyond 12K tokens (in place against rewritten: 4096 tokens 126 / 131 us, 12K equal,
+//    32K 6.33 / 6.27 ms, 64K 25.3 / 25.0 ms).  At head_dim 64 it never does (8K tokens 256 / 268 us, 32K 3.69 /
+//    3.81 ms).  The fp8 score product is built for the rewritten V.
 //  - Heads of a GQA group that share a workgroup share one K/V stream in LDS.  128-row tiles have waves enough
 //    without that, and two independent workgroups on a CU hide each other's barriers: single heads against pairs,
 //    8K tokens 2.8 % faster (dense 0 %), 16K 3.3 % (-0.7 %), 24K 2.8 % (-0.6 %).  But they read twice as much from
@@ -1036,6 +1037,11 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
     const bool two = p.group % 2 == 0 && !p.single_head, four = p.group % 4 == 0 && !p.single_head;
     const int64_t rows = (int64_t)p.batch * p.hq * p.seqlen * (p.causal ? 1 : 2);
     const bool d128 = head_dim == 128;
+    if (!calib && p.vt && !p.k8 && !(d128 && p.seqlen > 12288)) {
+        FwdParams in_place = p;
+        in_place.vt = nullptr;
+        return launch_forward(in_place, head_dim, block_m, false, stream);
+    }
     if (calib) {
         if (block_m == 128)
             return !d128 ? launch_scores<64, 4, 1, 3>(p, stream)

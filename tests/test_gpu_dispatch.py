@@ -99,6 +99,17 @@ def test_shared_heads_are_bit_identical(hq, hkv, n, d, bm):
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("hq, hkv, n, dtype", [(6, 2, 12500, torch.bfloat16), (3, 1, 24577, torch.float16), (4, 2, 24700, torch.bfloat16)])
+def test_rewritten_v_is_bit_identical_to_v_in_place(hq, hkv, n, dtype):
+    """Long enough for the pass over V (ragged, so the last tile repeats the last token), single heads and pairs."""
+    q, k, v = make(1, n, hq, hkv, 128, "qkv", dtype, n)
+    tau = binding.bsfa_calibrate(q, k, [0.5])[0].to(DEV)
+    ws = torch.full((binding.forward_workspace_bytes(q, k),), 0xFF, dtype=torch.uint8, device=DEV)      # NaN everywhere
+    for x, y in zip(call(q, k, v, tau, 128, True, workspace=ws), call(q, k, v, tau, 128, True, workspace=None)):
+        assert torch.equal(x, y)
+    assert (ws != 0xFF).any()
+
+
 def test_running_maximum_over_large_score_ranges():
     """Rows whose maximum grows with every block, only in the first one, and hardly at all, with scores of several
     hundred: finite, and equal to softmax in 64 bits (2e-2, the bound of every parity test; for lse the rounding of P
