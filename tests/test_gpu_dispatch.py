@@ -110,6 +110,29 @@ def test_rewritten_v_is_bit_identical_to_v_in_place(hq, hkv, n, dtype):
     assert (ws != 0xFF).any()
 
 
+@pytest.mark.parametrize("b, n, n_levels, equal", [
+    (1, 64, 3, False), (1, 640, 64, False), (3, 700, 8, True),          # nothing gateable; several rounds; all maxima equal
+    (2, 8192, 9, False), (1, 11584, 7, False), (1, 11648, 9, False),     # 32768, 32761 and 33124 maxima a head
+])
+def test_order_statistics_on_both_selections(b, n, n_levels, equal):
+    """bsfa_calibrate against a sort of the kernel's own block maxima, bit for bit, on dumps that one workgroup per head
+    selects from and on those that go through separate passes."""
+    q, k, _ = make(b, n, 2, 1, 64, "bnhd", torch.bfloat16, n)
+    if equal:
+        k = torch.zeros_like(k)
+    fr = [l / max(1, n_levels - 1) for l in range(n_levels)]
+    got = binding.bsfa_calibrate(q, k, fr, block_m=64)
+    st = binding.alloc_stats(q, 64, 64, counts=False, block_max=True)
+    binding.bsfa_forward(q, k, k, torch.full((2,), float("-inf"), device=DEV), skip_stats=st, block_m=64)
+    for h in range(2):
+        x = st.block_max[:, h].reshape(-1)
+        x = torch.sort(x[~x.isnan()])[0].cpu()
+        for l, f in enumerate(torch.tensor(fr).double().tolist()):
+            r = int(f * len(x))
+            want = float("-inf") if r == 0 else float("inf") if r >= len(x) else float(x[r])
+            assert float(got[l, h]) == want, (h, f)
+
+
 def test_running_maximum_over_large_score_ranges():
     """Rows whose maximum grows with every block, only in the first one, and hardly at all, with scores of several
     hundred: finite, and equal to softmax in 64 bits (2e-2, the bound of every parity test; for lse the rounding of P
