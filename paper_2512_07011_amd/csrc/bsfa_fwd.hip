@@ -566,6 +566,9 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // One pipeline stage: finish block j (`cur`), look ahead to block j+1 (`nxt`).
     // Block j+1 exists (the tile's last block is finished by last_stage).  FAST: it is gateable, so the
     // look-ahead has no mask and fewer conditionals.
+    // PRIO: heads that share a workgroup come out of the barrier together; of a SIMD's two waves the one still in its
+    // PV half goes first (32K tokens half skip 1.2 % faster, 128K 0.9 %, dense even; single heads 1 to 2 % slower with it).
+    constexpr bool PRIO = HP == 2 && NWH == 4 && !CALIB;
     auto stage = [&](ScoreTile &cur, ScoreTile &nxt, int j, auto fast_tag) {
         constexpr bool FAST = decltype(fast_tag)::value;
         bf16x8 pb[4];
@@ -594,6 +597,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         wg_barrier();
         uint32_t flags[HP] = {};
         if constexpr (!CALIB) read_flags(flags, (j + 1) & 1);
+        if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
         __builtin_amdgcn_sched_barrier(0);
         // The look-ahead -- decision for block j+1, its statistics, the requests for V_{j+1} and
         // K_{j+R}, the running maximum -- in pieces, so that a kept block can issue them between its
@@ -645,6 +649,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
             la_stats();
             if constexpr (!(VT || CALIB)) prefetch_k(lds_k0 + kring);
         }
+        if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
     };
 
     // The tile's last block (it touches the causal boundary, or there is no mask): nothing to look ahead to.
