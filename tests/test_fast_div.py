@@ -1,0 +1,35 @@
+"""The division by a launch-time constant that the work decomposition uses, against the divide operator, on the host."""
+import subprocess
+
+from paper_2512_07011_amd import build
+
+SRC = r"""
+#include "bsfa_internal.h"
+#include <cstdio>
+int main()
+{
+    unsigned long long bad = 0, seen = 0, rng = 88172645463325252ull;
+    auto next = [&] { rng ^= rng << 13; rng ^= rng >> 7; rng ^= rng << 17; return (uint32_t)(rng & 0x7fffffffu); };
+    auto check = [&](uint32_t d) {
+        const bsfa::FastDiv f = bsfa::fast_div(d);
+        auto one = [&](uint32_t n) { if (n <= 0x7fffffffu) { ++seen; bad += f.of(n) != n / d; } };
+        const uint32_t top = 0x7fffffffu / d * d;
+        for (uint32_t n : {0u, 1u, d - 1, d, d + 1, top - 1, top, 0x7ffffffeu, 0x7fffffffu}) one(n);
+        for (int i = 0; i < 100; ++i) { one(next()); const uint32_t m = next() / d * d; one(m); if (m) one(m - 1); }
+    };
+    for (uint32_t d = 1; d <= 5000; ++d) check(d);
+    for (int s = 1; s < 31; ++s) for (int e = -1; e <= 1; ++e) if ((1ll << s) + e > 0) check((uint32_t)((1ll << s) + e));
+    check(0x7fffffffu);
+    for (int i = 0; i < 5000; ++i) check(next() | 1u);
+    std::printf("%llu %llu\n", bad, seen);
+}
+"""
+
+
+def test_fast_div_is_exact_below_2_31(tmp_path):
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text(SRC)
+    subprocess.run([build.HIPCC, "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-std=c++17", "-O2", "-I" + build.CSRC,
+                    "-I/opt/rocm/include", "-o", str(exe), str(src)], check=True, capture_output=True)
+    bad, seen = map(int, subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split())
+    assert bad == 0 and seen > 1000000
