@@ -1023,8 +1023,9 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    without that, and two independent workgroups on a CU hide each other's barriers: single heads against pairs,
 //    8K tokens 2.8 % faster (dense 0 %), 16K 3.3 % (-0.7 %), 24K 2.8 % (-0.6 %).  But they read twice as much from
 //    L2 for a launch that the card's power limits, and beyond the L2 they drift apart in sequences many times its
-//    size: dense 32K tokens 0 to 2 % slower than pairs (half skip 1 % faster), dense without the mask 2.1 % at
-//    16K, 128K 2.5 % slower at half skip.  So heads are paired beyond 24K tokens, without the mask beyond 8K; with
+//    size: dense 32K tokens 0 to 2 % slower than pairs (half skip 1 % faster), 128K 2.5 % slower at half skip.
+//    Without the mask, where all tiles are equally long, pairs are never behind (4096 tokens 2 %, 6144 1 %, 8K
+//    even at half skip and 0.5 % dense).  So heads are paired beyond 24K tokens, without the mask beyond 3K; with
 //    the fp8 score product, whose K stream is half as wide, beyond 64K (16K tokens 6 % faster single, 64K 2 %).
 //    With 64 rows at head_dim 128 two heads fill the CU's two waves per SIMD (8K tokens 654 -> 428 us), with 32 rows four (1358 -> 469 us; two
 //    heads 731 us).  At head_dim 64 the smaller tiles of single heads already do and sharing pays on long
@@ -1061,7 +1062,7 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
     const bool split = !p.k8 && !p.gate_mode && p.mask_words <= kSplitMaskWords;
     if (block_m == 128) {
         if (split && rows <= 65536) return d128 ? launch_fwd<128, 4, 1, 2, 2>(p, stream) : launch_fwd<64, 4, 1, 2, 3>(p, stream);
-        if (d128 && two && p.seqlen > (p.k8 ? 65536 : p.causal ? 24576 : 8192)) return launch_fwd<128, 4, 2, 1, 5>(p, stream);
+        if (d128 && two && p.seqlen > (p.k8 ? 65536 : p.causal ? 24576 : 3072)) return launch_fwd<128, 4, 2, 1, 5>(p, stream);
         return d128 ? launch_fwd<128, 4, 1, 1, 2>(p, stream) : launch_fwd<64, 4, 1, 1, 3>(p, stream);
     }
     if (block_m == 64 && d128) {
