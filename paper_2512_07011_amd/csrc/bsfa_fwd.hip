@@ -256,8 +256,10 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
 #pragma unroll
         for (int e = 0; e < 16; ++e) oacc[x][e] = 0.f;
     // Running maximum of the row, log2 units (score * log2(e)/sqrt(d)).  The start value is finite, so that rows
-    // without a visible key yet need no special case, and below any score (fp32 products times log2(e)/sqrt(d)).
-    float m_run = -3.0e38f;
+    // without a visible key yet need no special case, and below any finite score (fp32 products times
+    // log2(e)/sqrt(d)).
+    constexpr float M_NONE = -3.0e38f;
+    float m_run = M_NONE;
     float l_run = 0.f;         // this lane's share of the running normaliser
 
     unsigned n_skipped = 0;    // per-head statistics, uniform over the head's waves
@@ -372,9 +374,10 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
             float stat = t.mx, unit = p.scale;                // natural score units (Eq. 5-6)
             if constexpr (!FAST) {
                 // the comparison predicate (Section 3): local row maximum minus the running row maximum
-                // after this block, natural units; m_run covers the kept blocks before this one
+                // after this block, natural units; m_run covers the kept blocks before this one.  A row that has
+                // seen no finite score yet is at its running maximum whatever this block holds, -inf included.
                 if (p.gate_mode) {
-                    stat = fminf(t.mx * p.scale - m_run * 0.6931471805599453f, 0.f);
+                    stat = m_run > M_NONE ? fminf(t.mx * p.scale - m_run * 0.6931471805599453f, 0.f) : 0.f;
                     unit = 1.f;
                 }
             }

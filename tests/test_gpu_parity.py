@@ -390,6 +390,25 @@ def test_running_max_predicate_matches_algorithm(oracle, qk_fp8):
         binding.bsfa_forward(qd, kd, vd, lam_d, gate_mode=2)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_running_max_predicate_before_any_finite_score(dtype):
+    """gate_mode = 1 where every score of the first block is minus infinity: no running maximum exists yet, so the block
+    does not fall behind one and the statistic is 0 (kept at any lambda <= 0), as for the first block of finite scores.
+    The keys behind it score 0 on every row, none of them is skipped, and rows with a visible one average their V."""
+    n, h, d = 700, 4, 128
+    q, k = (torch.zeros(1, n, x, d, device=DEV) for x in (h, 2))
+    v = torch.randn(1, n, 2, d, generator=torch.Generator().manual_seed(3)).to(dtype).to(DEV)
+    q[..., 0] = 2.0 ** 15 if dtype is torch.float16 else 2.0 ** 120
+    k[:, :64, :, 0] = float("-inf") if dtype is torch.float16 else -2.0 ** 120
+    st = binding.alloc_stats(q, 128, 64, counts=True, skip_mask=True, block_max=True)
+    out = binding.bsfa_forward(q.to(dtype), k.to(dtype), v, torch.full((h,), -2.0, device=DEV), skip_stats=st, gate_mode=1)
+    torch.cuda.synchronize()
+    assert (st.skip_mask == 0).all() and (st.counts[..., 0] == 0).all()
+    assert (st.block_max[:, :, 1:, 0] == 0).all()
+    ref = v[0, 64:].float().cumsum(0) / torch.arange(1, n - 63, device=DEV)[:, None, None]
+    assert (out[0, 64:].float() - ref.repeat_interleave(2, dim=1)).abs().max() <= parity.MAX_ABS
+
+
 def _to_e4m3(t):
     """Round to fp8 e4m3 (nearest even) and widen back: every value is then exact in bf16."""
     return t.to(torch.float8_e4m3fn).to(torch.bfloat16)
