@@ -159,19 +159,14 @@ def alloc_stats(q: torch.Tensor, block_m: int, block_n: int, counts=True, skip_m
     return s
 
 
-_workspaces = {}
-
-
-def _cached_workspace(device, nbytes: int):
-    """One growing scratch tensor per device for callers that do not manage the forward workspace
-    themselves (calls that overlap on different streams must pass their own)."""
-    if nbytes == 0:
-        return None
-    w = _workspaces.get(device)
-    if w is None or w.numel() < nbytes:
-        w = torch.empty(nbytes, dtype=torch.uint8, device=device)
-        _workspaces[device] = w
-    return w
+def _scratch(nbytes: int, device, stream) -> torch.Tensor:
+    """Scratch memory of one call, from torch's allocator on the stream that the call's kernels run on: dropped
+    after the launch, it is handed out again only to later work of that stream, so calls on other streams, from other
+    threads or in a captured graph (whose allocations stay in the graph's own pool) never write into it."""
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
 def forward_workspace_bytes(q: torch.Tensor, k: torch.Tensor, block_m: int = 128, block_n: int = 64,
@@ -205,9 +200,9 @@ def bsfa_forward(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, thresholds: 
     """out = block-sparse attention of bf16 (or fp16) q [B,N,Hq,d], k, v [B,N,Hkv,d]; thresholds fp32 on the
     GPU, [Hq] or [Hq, T] (T tiles calibrated; later tiles use the last one).  ``seqlens`` (int32
     GPU tensor [B], causal only) gives each batch element its own length.  ``workspace``: a uint8
-    GPU tensor of at least forward_workspace_bytes(...) bytes, True (a cached tensor per device is
-    used) or False/None (no workspace: V is read in place).  ``gate_mode`` 1 selects the
-    running-maximum comparison predicate (thresholds then hold its lambda).  Enqueues on ``stream`` (default:
+    GPU tensor of at least forward_workspace_bytes(...) bytes (calls that overlap need one each), True
+    (scratch memory of the call's own, from torch's allocator) or False/None (no workspace: V is read
+    in place).  ``gate_mode`` 1 selects the running-maximum comparison predicate (thresholds then hold its lambda).  Enqueues on ``stream`` (default:
     torch's current stream)."""
     _dev_check(q, k, v, thresholds, out)
     if out is None:
@@ -228,7 +223,8 @@ def bsfa_forward(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, thresholds: 
     p.qk_fp8 = int(bool(qk_fp8))
     pref = ctypes.byref(p)
     if workspace is True:
-        workspace = _cached_workspace(q.device, L.bsfa_forward_workspace_bytes(pref))
+        need = L.bsfa_forward_workspace_bytes(pref)
+        workspace = _scratch(need, q.device, stream) if need else None
     if workspace is not None and workspace is not False:
         _dev_check(workspace)
         p.workspace = workspace.data_ptr()
@@ -258,7 +254,7 @@ def bsfa_calibrate(q: torch.Tensor, k: torch.Tensor, target_skip_fractions: Sequ
     if need == 0:
         _check(lib().bsfa_calibrate(ctypes.byref(p), q.data_ptr(), k.data_ptr(), int(bool(causal)), None, 0, None, None, 0, None))
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+        workspace = _scratch(need, q.device, stream)
     n = len(target_skip_fractions)
     fr = (ctypes.c_float * n)(*[float(f) for f in target_skip_fractions])
     outp = (ctypes.c_float * (n * q.shape[2]))()
@@ -296,7 +292,7 @@ def mfma_rate_probe(operands: torch.Tensor, workgroups: int, iters: int, sink: O
         raise TypeError("mfma_rate_probe: operands must be a contiguous float32 GPU tensor of at least 4096 values")
     need = lib().bsfa_mfma_rate_probe_sink_bytes(int(workgroups))
     if sink is None:
-        sink = torch.empty(max(need, 4) // 4, dtype=torch.float32, device=operands.device)
+        sink = _scratch(max(need, 4), operands.device, stream)
     s = stream if stream is not None else torch.cuda.current_stream(operands.device)
     _check(lib().bsfa_mfma_rate_probe(operands.data_ptr(), sink.data_ptr(), sink.numel() * sink.element_size(),
                                       int(workgroups), int(iters), ctypes.c_void_p(s.cuda_stream)))
@@ -319,7 +315,7 @@ def bsfa_calibrate_topk(samples, ks: Sequence[int], causal: bool = True, block_m
         p = make_problem(q, k, None, None, block_m, block_n)
         need = lib().bsfa_calibrate_workspace_bytes(ctypes.byref(p))
         if ws is None or ws.numel() < need:
-            ws = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
+            ws = _scratch(max(need, 1), q.device, stream)
         if out is None:
             out = (ctypes.c_float * (n * q.shape[2] * n_tiles(q.shape[1], block_m)))()
         s = stream if stream is not None else torch.cuda.current_stream(q.device)

@@ -1,5 +1,7 @@
 """The kernels a call can be sent to (heads shared or not, key blocks of a tile dealt to two sets of waves or not)
 against each other, over the forms that each accepts."""
+import threading
+
 import pytest
 import torch
 
@@ -146,3 +148,56 @@ def test_running_maximum_over_large_score_ranges():
         s = (q[0, :, 0].double() @ ks[0, :, 0].double().t() / d ** 0.5).masked_fill(torch.ones(n, n, device=DEV).triu(1).bool(), float("-inf"))
         assert (out[0, :, 0].double() - s.softmax(-1) @ v[0, :, 0].double()).abs().max() <= 2e-2
         assert (lse[0, :, 0].double() - s.logsumexp(-1)).abs().max() <= 2.0 ** -8 + 1e-6 * s[s.isfinite()].abs().max()
+
+
+@pytest.mark.parametrize("side_by_side", ["streams", "threads"])
+def test_calls_that_overlap_do_not_share_scratch_memory(side_by_side):
+    """Calls whose V goes through scratch memory of the binding's own, on two streams and from two threads on one stream,
+    each side with its own V, against the same calls one after the other, bit for bit."""
+    q, k, v = make(1, 16500, 8, 2, 128, "bnhd", torch.bfloat16, 1)
+    vs = (v, v.flip(1).contiguous())
+    tau = torch.full((8,), 3.0, device=DEV)
+    want = [binding.bsfa_forward(q, k, x, tau) for x in vs]
+    got = [[torch.empty_like(q) for _ in range(4)] for _ in vs]
+    torch.cuda.synchronize()
+    if side_by_side == "streams":
+        streams = [torch.cuda.Stream() for _ in vs]
+        for r in range(4):
+            for x, o, s in zip(vs, got, streams):
+                binding.bsfa_forward(q, k, x, tau, out=o[r], stream=s)
+    else:
+        def calls(x, o):
+            for r in range(4):
+                binding.bsfa_forward(q, k, x, tau, out=o[r])
+        side = [threading.Thread(target=calls, args=a) for a in zip(vs, got)]
+        for t in side:
+            t.start()
+        for t in side:
+            t.join()
+    torch.cuda.synchronize()
+    for w, outs in zip(want, got):
+        for o in outs:
+            assert torch.equal(o, w)
+
+
+def test_captured_call_keeps_its_scratch_memory():
+    """A captured call with scratch memory, replayed between larger eager calls and tensors that take up whatever memory
+    those have given back: every replay equals the eager result."""
+    q, k, v = make(1, 1024, 4, 2, 128, "bnhd", torch.bfloat16, 2)
+    big = make(1, 6000, 4, 2, 128, "bnhd", torch.bfloat16, 3)
+    tau = torch.full((4,), 1.0, device=DEV)
+    out = torch.empty_like(q)
+    want = binding.bsfa_forward(q, k, v, tau, qk_fp8=True)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        binding.bsfa_forward(q, k, v, tau, out=out, qk_fp8=True)
+    for r in range(3):
+        want_big = binding.bsfa_forward(*big, tau, qk_fp8=True)
+        others = [torch.full((s,), 0xFF, dtype=torch.uint8, device=DEV) for s in (1 << 20, 3 << 20, 9 << 20)]
+        out.fill_(7.0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), r
+        assert torch.equal(binding.bsfa_forward(*big, tau, qk_fp8=True), want_big)
+        assert all((o == 0xFF).all() for o in others)
