@@ -109,8 +109,10 @@ typedef struct {
                                      the same setting, since block maxima of fp8-rounded operands differ from the
                                      16-bit ones by a few hundredths. */
     void   *workspace;            /* optional, DEVICE, 256-byte aligned, bsfa_forward only: scratch memory of at
-                                     least bsfa_forward_workspace_bytes() bytes, overwritten by every call.
-                                     Where it pays (block_m = 128, head_dim 128, more than 12K tokens, or
+                                     least bsfa_forward_workspace_bytes() bytes, overwritten by every call that
+                                     makes use of it (the others look neither at it nor at its size; calls that
+                                     overlap need one each).
+                                     Where it pays (block_m = 128, head_dim 128, more than 12288 tokens, or
                                      qk_fp8) the forward pass first rewrites V into it, once, as
                                      transposed 64-key tiles (an O(N) pass: 2 x the size of V in traffic) so
                                      that the second matrix product reads its V operand from on-chip memory
@@ -154,8 +156,8 @@ bsfa_status bsfa_forward(const bsfa_problem *p, const void *q, const void *k, co
                          const bsfa_skip_stats *skip_stats /* may be NULL */, void *hip_stream);
 
 /* Bytes of workspace bsfa_forward can use for *p (size of V rounded up to whole 64-key blocks, plus
- * half as much for the fp8 copy of K if p->qk_fp8, plus alignment slack); 0 if *p is invalid or its
- * tile shape makes no use of a workspace. */
+ * half of that with qk_fp8, each plus alignment).  0 if *p is invalid or no call of that shape makes
+ * use of one: see the member `workspace`. */
 size_t bsfa_forward_workspace_bytes(const bsfa_problem *p);
 
 /*

@@ -171,7 +171,7 @@ def _scratch(nbytes: int, device, stream) -> torch.Tensor:
 
 def forward_workspace_bytes(q: torch.Tensor, k: torch.Tensor, block_m: int = 128, block_n: int = 64,
                             qk_fp8: bool = False) -> int:
-    """Bytes of workspace bsfa_forward can use for these shapes (0: none)."""
+    """Bytes of workspace bsfa_forward can use for these shapes (0: no call of that shape uses one)."""
     p = make_problem(q, k, None, None, block_m, block_n)
     p.qk_fp8 = int(bool(qk_fp8))
     return int(lib().bsfa_forward_workspace_bytes(ctypes.byref(p)))

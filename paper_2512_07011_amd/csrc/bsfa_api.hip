@@ -113,14 +113,12 @@ bsfa_status bsfa_forward(const bsfa_problem *p, const void *q, const void *k, co
     fp.v = static_cast<const uint16_t *>(v);
     fp.out = static_cast<uint16_t *>(out);
     fp.tau = thresholds;
-    if (p->workspace) {
+    if (p->workspace && (p->qk_fp8 || bsfa::rewrites_v(fp, p->head_dim, p->block_m))) {
         const size_t need = bsfa_forward_workspace_bytes(p);
-        if (need) {                   // (tile shapes that take V in place ignore the workspace)
-            if ((size_t)p->workspace_bytes < need)
-                return fail(BSFA_ERR_WORKSPACE, "forward workspace of %zu bytes needed, %lld given", need, (long long)p->workspace_bytes);
-            fp.vt = reinterpret_cast<uint16_t *>((reinterpret_cast<uintptr_t>(p->workspace) + 255) & ~(uintptr_t)255);
-            if (p->qk_fp8) fp.k8 = reinterpret_cast<uint8_t *>((reinterpret_cast<uintptr_t>(fp.vt) + 2 * k8_bytes(p) + 255) & ~(uintptr_t)255);
-        }
+        if ((size_t)p->workspace_bytes < need)
+            return fail(BSFA_ERR_WORKSPACE, "forward workspace of %zu bytes needed, %lld given", need, (long long)p->workspace_bytes);
+        fp.vt = reinterpret_cast<uint16_t *>((reinterpret_cast<uintptr_t>(p->workspace) + 255) & ~(uintptr_t)255);
+        if (p->qk_fp8) fp.k8 = reinterpret_cast<uint8_t *>((reinterpret_cast<uintptr_t>(fp.vt) + 2 * k8_bytes(p) + 255) & ~(uintptr_t)255);
     }
     if (p->qk_fp8 && !fp.k8) return fail(BSFA_ERR_WORKSPACE, "qk_fp8 needs the forward workspace (bsfa_forward_workspace_bytes)");
     if (skip_stats) {
@@ -136,7 +134,8 @@ bsfa_status bsfa_forward(const bsfa_problem *p, const void *q, const void *k, co
 
 size_t bsfa_forward_workspace_bytes(const bsfa_problem *p)
 {
-    if (check_problem(p, 1) != BSFA_OK || p->block_m != 128) return 0;
+    if (check_problem(p, 1) != BSFA_OK) return 0;
+    if (!p->qk_fp8 && !bsfa::v_rewrite_pays(p->head_dim, p->block_m, p->seqlen)) return 0;
     // transposed V tiles | fp8 K tiles (if asked for), each 256-byte aligned
     return 2 * k8_bytes(p) + 256 + (p->qk_fp8 ? k8_bytes(p) + 256 : 0);
 }

@@ -1038,19 +1038,29 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    from rows 262 144 on (6000 tokens 209 us either way, 32K tokens 3.50 ms in pairs).
 // Results do not depend on how heads share; the split does change the order of sums, so it must not depend on
 // single_head or on the workspace, between which results are equal bit for bit.
+static int64_t dispatch_rows(const FwdParams &p) { return (int64_t)p.batch * p.hq * p.seqlen * (p.causal ? 1 : 2); }
+
+static bool splits_tiles(const FwdParams &p, int head_dim, int block_m)
+{
+    // (the comparison predicate depends on the order of the blocks; the mask words of a split tile must fit the LDS)
+    if (block_m == 32 || p.k8 || p.gate_mode || p.mask_words > kSplitMaskWords) return false;
+    // (64 rows at head_dim 128: two shares of one head are only four waves, and 128 KiB of LDS: one workgroup per CU)
+    return dispatch_rows(p) <= (block_m == 64 && head_dim == 128 ? (p.group % 2 == 0 ? 45056 : 32768) : 65536);
+}
+
+bool rewrites_v(const FwdParams &p, int head_dim, int block_m)
+{
+    return v_rewrite_pays(head_dim, block_m, p.seqlen) && !splits_tiles(p, head_dim, block_m);
+}
+
 hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool calib, hipStream_t stream)
 {
     if (!shape_supported(head_dim, block_m, kBlockN)) return hipErrorInvalidValue;
     // the copies address a tile with 32-bit byte offsets
     if (p.ksn * 128 > 0x7fff0000LL || p.vsn * 128 > 0x7fff0000LL) return hipErrorInvalidValue;
     const bool two = p.group % 2 == 0 && !p.single_head, four = p.group % 4 == 0 && !p.single_head;
-    const int64_t rows = (int64_t)p.batch * p.hq * p.seqlen * (p.causal ? 1 : 2);
+    const int64_t rows = dispatch_rows(p);
     const bool d128 = head_dim == 128;
-    if (!calib && p.vt && !p.k8 && !(d128 && p.seqlen > 12288)) {
-        FwdParams in_place = p;
-        in_place.vt = nullptr;
-        return launch_forward(in_place, head_dim, block_m, false, stream);
-    }
     if (calib) {
         if (block_m == 128)
             return !d128 ? launch_scores<64, 4, 1, 3>(p, stream)
@@ -1061,20 +1071,18 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
         return d128 ? (four ? launch_scores<128, 1, 4, 2>(p, stream) : two ? launch_scores<128, 1, 2, 2>(p, stream) : launch_scores<128, 1, 1, 2>(p, stream))
                     : (four ? launch_scores<64, 1, 4, 4>(p, stream) : two ? launch_scores<64, 1, 2, 4>(p, stream) : launch_scores<64, 1, 1, 2>(p, stream));
     }
-    // (the comparison predicate depends on the order of the blocks; the mask words of a split tile must fit the LDS)
-    const bool split = !p.k8 && !p.gate_mode && p.mask_words <= kSplitMaskWords;
+    const bool split = splits_tiles(p, head_dim, block_m);
     if (block_m == 128) {
-        if (split && rows <= 65536) return d128 ? launch_fwd<128, 4, 1, 2, 2>(p, stream) : launch_fwd<64, 4, 1, 2, 3>(p, stream);
+        if (split) return d128 ? launch_fwd<128, 4, 1, 2, 2>(p, stream) : launch_fwd<64, 4, 1, 2, 3>(p, stream);
         if (d128 && two && p.seqlen > (p.k8 ? 65536 : p.causal ? 24576 : 3072)) return launch_fwd<128, 4, 2, 1, 5>(p, stream);
         return d128 ? launch_fwd<128, 4, 1, 1, 2>(p, stream) : launch_fwd<64, 4, 1, 1, 3>(p, stream);
     }
     if (block_m == 64 && d128) {
-        // (two shares of one head are only four waves, and 128 KiB of LDS: one workgroup per CU)
-        if (split && rows <= (p.group % 2 == 0 ? 45056 : 32768)) return two ? launch_fwd<128, 2, 2, 2, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 2>(p, stream);
+        if (split) return two ? launch_fwd<128, 2, 2, 2, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 2>(p, stream);
         return two ? launch_fwd<128, 2, 2, 1, 2>(p, stream) : launch_fwd<128, 2, 1, 1, 2>(p, stream);
     }
     if (block_m == 64) {
-        if (split && rows <= 65536) return launch_fwd<64, 2, 1, 2, 2>(p, stream);
+        if (split) return launch_fwd<64, 2, 1, 2, 2>(p, stream);
         return two && rows > 131072 ? launch_fwd<64, 2, 2, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 1, 2>(p, stream);
     }
     if (d128) return four ? launch_fwd<128, 1, 4, 1, 2>(p, stream) : two ? launch_fwd<128, 1, 2, 1, 2>(p, stream) : launch_fwd<128, 1, 1, 1, 2>(p, stream);

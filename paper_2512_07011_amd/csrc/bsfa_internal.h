@@ -50,8 +50,14 @@ struct FwdParams {
                                            // KV head, KV heads; set by the launch
 };
 
+// Shapes whose forward calls rewrite V into the workspace, if they are given one and take their key blocks one after
+// the other (rewrites_v; with the fp8 score product every call does).  The lines stand at launch_forward.
+constexpr bool v_rewrite_pays(int head_dim, int block_m, int seqlen) { return head_dim == 128 && block_m == 128 && seqlen > 12288; }
+bool rewrites_v(const FwdParams &p, int head_dim, int block_m);
+
 // Launches the forward kernel (calib == false) or its score/block-maximum half only
-// (calib == true: no V, no softmax, no output; block_max must be non-null).
+// (calib == true: no V, no softmax, no output; block_max must be non-null).  vt may be set where
+// rewrites_v says so or k8 is set.
 // Returns hipSuccess or the launch error; hipErrorInvalidValue for an unsupported
 // (head_dim, block_m) pair.
 hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool calib, hipStream_t stream);

@@ -112,6 +112,18 @@ def test_calibrate_topk_argument_checks(lib):
     assert lib.bsfa_calibrate_topk(ctypes.byref(good_problem(seqlens=0x1000)), FAKE, FAKE, 1, ks, 2, 0, out, FAKE, need, None) == -4
 
 
+def test_forward_workspace_is_asked_for_only_where_calls_use_it(lib):
+    """Rewritten V (128-row tiles of width 128 beyond 12288 tokens: whole 64-key blocks of 16-bit elements) and, with the
+    fp8 score product, V and an fp8 copy of K at any length."""
+    need = lambda **kw: lib.bsfa_forward_workspace_bytes(ctypes.byref(good_problem(**kw)))
+    assert need() == need(seqlen=12288) == 0
+    assert need(seqlen=131072, head_dim=64) == need(seqlen=131072, block_m=64) == need(seqlen=131072, block_m=32) == 0
+    v = lambda n: 2 * -(-n // 64) * 64 * 128 * 2
+    assert v(12289) <= need(seqlen=12289) <= v(12289) + 256
+    assert 3 * v(500) // 2 <= need(seqlen=500, qk_fp8=1) <= 3 * v(500) // 2 + 512
+    assert need(batch=0, seqlen=131072) == 0
+
+
 def test_query_build_and_status_strings(lib):
     tiles = binding.bsfa_query_build()
     assert (128, 64, 128) in tiles and (64, 64, 64) in tiles

@@ -284,17 +284,17 @@ def test_single_head_groups_gives_identical_results(oracle):
     parity.compare(q, k, v, tau, 128, 64, True, o1, s1.skip_mask, s1.block_max, lse_gpu=s1.lse)
 
 
-@pytest.mark.parametrize("case,dtype", [((1, 1152, 16, 8, 128, 128, 64), torch.bfloat16), ((2, 640, 4, 2, 64, 128, 64), torch.float16),
-                                        ((1, 900, 6, 2, 128, 128, 64), torch.bfloat16)])
+@pytest.mark.parametrize("case,dtype", [((1, 12416, 16, 8, 128, 128, 64), torch.bfloat16), ((2, 24704, 4, 2, 128, 128, 64), torch.float16),
+                                        ((1, 12900, 6, 2, 128, 128, 64), torch.bfloat16)])
 def test_workspace_path_is_bit_identical_to_in_place_v(case, dtype):
     """With a workspace V is first rewritten as transposed tiles and the second product reads it with
     full-width LDS reads; without one V is gathered in place with transposing reads.  Both feed the
     same numbers to the same MFMAs: outputs, masks and log-sum-exps must be equal bit for bit
-    (paired heads, single heads, ragged length, a workspace that is too small)."""
+    (single heads, paired heads, ragged length, a workspace that is too small), at lengths at which V is rewritten."""
     shp = synth.Shape(*case)
     q, k, v = (t.to(dtype).to(DEV) for t in synth.tiny(77, shp, n_boost=max(1, shp.m_kv // 3)))
-    if case[1] == 900:
-        q, k, v = (t[:, :870].contiguous() for t in (q, k, v))
+    if case[1] == 12900:
+        q, k, v = (t[:, :12870].contiguous() for t in (q, k, v))
     tau = binding.bsfa_calibrate(q, k, [0.5])[0].to(DEV)
     need = binding.forward_workspace_bytes(q, k)
     assert need >= v.numel() * 2
@@ -304,8 +304,10 @@ def test_workspace_path_is_bit_identical_to_in_place_v(case, dtype):
                      ("workspace_single", dict(workspace=ws, single_head_groups=True)),
                      ("in_place_single", dict(workspace=None, single_head_groups=True))):
         st = binding.alloc_stats(q, 128, 64, counts=True, skip_mask=True, lse=True)
+        ws.fill_(0xFF)
         out = binding.bsfa_forward(q, k, v, tau, skip_stats=st, **kw)
         torch.cuda.synchronize()
+        assert (ws != 0xFF).any() == (kw["workspace"] is not None)            # V was, or was not, rewritten
         res[name] = (out.clone(), st.skip_mask.clone(), st.lse.clone(), st.counts.clone())
     assert res["in_place"][3][..., 0].sum() > 0
     for name in ("workspace", "workspace_single", "in_place_single"):
@@ -314,6 +316,20 @@ def test_workspace_path_is_bit_identical_to_in_place_v(case, dtype):
     with pytest.raises(binding.BsfaError) as e:
         binding.bsfa_forward(q, k, v, tau, workspace=ws[:need - 1024])
     assert e.value.status == -5
+
+
+@pytest.mark.parametrize("case", [(1, 1152, 16, 8, 128, 128, 64), (1, 12416, 8, 2, 64, 128, 64), (1, 12416, 4, 2, 128, 128, 64), (1, 12416, 8, 2, 128, 64, 64)])
+def test_calls_that_take_v_in_place_leave_a_workspace_alone(case):
+    """Short calls, head_dim 64, split tiles, small tiles: a workspace they have no use for is neither written nor
+    checked for its size."""
+    b, n, hq, hkv, d, bm, bn = case
+    q, k, v = (torch.randn(b, n, h, d, device=DEV).to(torch.bfloat16) for h in (hq, hkv, hkv))
+    tau = torch.full((hq,), 2.0, device=DEV)
+    want = binding.bsfa_forward(q, k, v, tau, block_m=bm, workspace=None)
+    for size in (256, 1 << 25):
+        ws = torch.full((size,), 0xFF, dtype=torch.uint8, device=DEV)
+        assert torch.equal(binding.bsfa_forward(q, k, v, tau, block_m=bm, workspace=ws), want)
+        assert (ws == 0xFF).all()
 
 
 @pytest.mark.parametrize("qk_fp8", [False, True])
