@@ -58,9 +58,7 @@ def test_small_calls_agree_with_every_other_form(case):
             assert torch.equal(x, y)
     if n > 256:
         assert alone[2][..., 0].sum() > 0                   # something is skipped
-    times = 1 + 150000 // (b * hq * n * (1 if causal else 2))
-    if times * b * 4 > 60000:                               # (a single token: the batch would not fit a launch)
-        times = 60000 // (4 * b)
+    times = 1 + 150000 // (b * hq * n * (1 if causal else 2))    # (calls split tiles up to 65536 query rows over all heads)
     many = call(*(t.repeat(times, 1, 1, 1) for t in (q, k, v)), tau, bm, causal)
     for lo in (0, (times - 1) * b):
         out, lse, counts, mask = (x[lo:lo + b] for x in many)
@@ -91,14 +89,43 @@ def test_split_tiles_with_lengths_and_thresholds_per_tile(d, bm):
         assert torch.equal(mask[e, :, :tiles, :words], one[3][0]) and (mask[e, :, tiles:] == 0).all() and (mask[e, :, :tiles, words:] == 0).all()
 
 
-@pytest.mark.parametrize("hq, hkv, n, d, bm", [(32, 8, 2304, 128, 64), (32, 8, 4160, 64, 64), (32, 8, 2624, 64, 32), (8, 2, 1024, 128, 32),
-                                                 (4, 2, 24640, 128, 128)])
-def test_shared_heads_are_bit_identical(hq, hkv, n, d, bm):
+@pytest.mark.parametrize("hq, hkv, n, d, bm, causal, fp8, dtype", [
+    (32, 8, 2304, 128, 64, True, False, torch.bfloat16), (32, 8, 4160, 64, 64, True, False, torch.bfloat16),
+    (32, 8, 2624, 64, 32, True, False, torch.bfloat16), (8, 2, 1024, 128, 32, True, False, torch.bfloat16),
+    (4, 2, 1000, 128, 32, True, False, torch.float16),
+    (4, 2, 24640, 128, 128, True, False, torch.bfloat16),        # V from the workspace
+    (32, 8, 4096, 128, 128, False, False, torch.bfloat16), (8, 4, 5120, 128, 128, False, False, torch.float16),   # V in place
+    (4, 2, 65700, 128, 128, True, True, torch.bfloat16), (6, 3, 65610, 128, 128, True, True, torch.float16),      # fp8 scores
+])
+def test_shared_heads_are_bit_identical(hq, hkv, n, d, bm, causal, fp8, dtype):
     """Two and four heads to a workgroup against one, fast stages and all, on problems large enough to be sent there."""
-    q, k, v = make(1, n, hq, hkv, d, "bnhd", torch.bfloat16, n)
-    for tau in (binding.bsfa_calibrate(q, k, [0.6], block_m=bm)[0].to(DEV), torch.full((hq,), float("-inf"), device=DEV)):
-        for x, y in zip(call(q, k, v, tau, bm, True), call(q, k, v, tau, bm, True, single_head_groups=True)):
+    q, k, v = make(1, n, hq, hkv, d, "bnhd", dtype, n)
+    kw = dict(qk_fp8=fp8)
+    for tau in (binding.bsfa_calibrate(q, k, [0.6], causal=causal, block_m=bm, **kw)[0].to(DEV), torch.full((hq,), float("-inf"), device=DEV)):
+        shared, single = (call(q, k, v, tau, bm, causal, single_head_groups=x, **kw) for x in (False, True))
+        for x, y in zip(shared, single):
             assert torch.equal(x, y)
+        assert (shared[2][..., 0].sum() > 0) == bool(tau.isfinite().all())
+
+
+@pytest.mark.parametrize("hq, hkv, n", [(4, 2, 12700), (3, 1, 12416), (4, 2, 24641)])
+def test_rewritten_v_with_lengths(hq, hkv, n):
+    """Rewritten V with batch elements that end early, at block edges or are empty, and a workspace full of NaN: V in
+    place gives the same bits, rows behind an end stay untouched, empty elements count nothing (the pass over V clears
+    the counts)."""
+    lengths = [0, 1, 64, 6321, n - 1, n]
+    q, k, v = make(len(lengths), n, hq, hkv, 128, "bnhd", torch.bfloat16, n)
+    tau = torch.full((hq,), 3.3, device=DEV)
+    sl = torch.tensor(lengths, dtype=torch.int32, device=DEV)
+    ws = torch.full((binding.forward_workspace_bytes(q, k),), 0xFF, dtype=torch.uint8, device=DEV)
+    rewritten, in_place = (call(q, k, v, tau, 128, True, seqlens=sl, workspace=w) for w in (ws, None))
+    for x, y in zip(rewritten, in_place):
+        assert torch.equal(x, y)
+    assert (ws != 0xFF).any()
+    out, lse, counts, mask = rewritten
+    assert (counts[0] == 0).all() and (counts[-1, :, 0] > 0).all()
+    for e, m in enumerate(lengths):
+        assert (out[e, m:] == 7.0).all() and (lse[e, m:] == 7.0).all() and out[e, :m].isfinite().all()
 
 
 @pytest.mark.parametrize("hq, hkv, n, dtype", [(6, 2, 12500, torch.bfloat16), (3, 1, 24577, torch.float16), (4, 2, 24700, torch.bfloat16)])
