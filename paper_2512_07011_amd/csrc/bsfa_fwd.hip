@@ -50,8 +50,7 @@ struct ScoreTile {
 };
 
 // Waves per SIMD the registers are allocated for: two, or three at head_dim 64 where the LDS holds as many
-// workgroups of four waves (8K tokens, 32 heads of width 64: 306 us with two, 253 us with three; what the
-// 168 registers do not hold then lies outside the loop over full blocks).
+// workgroups of four waves (8K tokens, 32 heads of width 64, half skip: 306 us with two, 230 us with three).
 constexpr int min_waves(int d, int waves, int lds_bytes)
 {
     return d == 64 && waves * (160 * 1024 / (lds_bytes + 1024)) >= 12 && waves <= 4 ? 3 : 2;
@@ -288,7 +287,10 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     };
     
     constexpr int PD = 4;            // LDS operand reads are issued PD MFMAs ahead of their use (3 to 6 measure within 1 %)
-    constexpr int PDK = QK8 ? 2 : PD; // ... of the score operands (the fp8 ones are twice as wide and four in all)
+    // ... of the score operands: the fp8 ones are twice as wide and four in all; with three waves to a SIMD four of them
+    // are more than the 168 registers hold, and what is spilled comes back inside the loop behind a wait for every copy
+    // in flight (8K tokens, 32 heads of width 64, half skip: 256 us with four, 233 with three, 230 with two).
+    constexpr int PDK = QK8 || (!CALIB && min_waves(D, NW, KSP * (KR + VR) * TILE_BYTES) == 3) ? 2 : PD;
     // The first PDK score operands of a block are read one phase early (at the end of the previous
     // stage, behind its last MFMAs), so that the score MFMAs do not start with an LDS round trip.
     kop_t kpre[PDK];
