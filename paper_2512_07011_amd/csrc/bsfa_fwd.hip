@@ -917,9 +917,9 @@ static hipError_t launch_prepasses(const FwdParams &p, hipStream_t stream)
     return hipGetLastError();
 }
 
-// forward pass
+// forward pass; `spare` bytes of LDS more than a workgroup needs keep others off its CU
 template <int D, int NWH, int HP, int KSP, int KR>
-hipError_t launch_fwd(const FwdParams &params, hipStream_t stream)
+hipError_t launch_fwd(const FwdParams &params, hipStream_t stream, unsigned spare = 0)
 {
     FwdParams p = params;
     const dim3 grid(decompose<HP>(p)), threads(NWH * HP * KSP * 64);
@@ -934,7 +934,7 @@ hipError_t launch_fwd(const FwdParams &params, hipStream_t stream)
         const hipError_t e = launch_prepasses(p, stream);
         if (e != hipSuccess) return e;
     }
-#define BSFA_LAUNCH(F16, VT, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, KSP, KR, false, F16, VT, QK8>), grid, threads, 0, stream, p)
+#define BSFA_LAUNCH(F16, VT, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, KSP, KR, false, F16, VT, QK8>), grid, threads, spare, stream, p)
     if constexpr (WS) {
         if (p.k8) {
             if (p.f16) BSFA_LAUNCH(true, true, true);
@@ -990,9 +990,9 @@ hipError_t launch_scores(const FwdParams &params, hipStream_t stream)
 #define BSFA_SHAPES_7(F, S) F(128, 1, 4, 1, 2) F(128, 1, 2, 1, 2) F(128, 1, 1, 1, 2)
 #define BSFA_SHAPES_8(F, S) F(64, 1, 4, 1, 4) F(64, 1, 2, 1, 4) F(64, 1, 1, 1, 2) S(128, 1, 4, 2) S(128, 1, 2, 2) S(128, 1, 1, 2) \
                             S(64, 1, 4, 4) S(64, 1, 2, 4) S(64, 1, 1, 2)
-#define BSFA_EXTERN_F(D, N, H, P, K) extern template hipError_t launch_fwd<D, N, H, P, K>(const FwdParams &, hipStream_t);
+#define BSFA_EXTERN_F(D, N, H, P, K) extern template hipError_t launch_fwd<D, N, H, P, K>(const FwdParams &, hipStream_t, unsigned);
 #define BSFA_EXTERN_S(D, N, H, K) extern template hipError_t launch_scores<D, N, H, K>(const FwdParams &, hipStream_t);
-#define BSFA_DEFINE_F(D, N, H, P, K) template hipError_t launch_fwd<D, N, H, P, K>(const FwdParams &, hipStream_t);
+#define BSFA_DEFINE_F(D, N, H, P, K) template hipError_t launch_fwd<D, N, H, P, K>(const FwdParams &, hipStream_t, unsigned);
 #define BSFA_DEFINE_S(D, N, H, K) template hipError_t launch_scores<D, N, H, K>(const FwdParams &, hipStream_t);
 #if BSFA_PART == 0
 BSFA_SHAPES_1(BSFA_EXTERN_F, BSFA_EXTERN_S)
@@ -1011,33 +1011,50 @@ bool shape_supported(int head_dim, int block_m, int block_n)
     return block_m == 32 || block_m == 64 || block_m == 128;
 }
 
-// Which kernel a call gets.  Figures: bf16, 32 query heads over 8 KV heads, half skip, unless stated.
+// Which kernel a call gets.  Figures: us, bf16, 32 query heads over 8 KV heads, half skip, unless stated.
 //
-// `rows` -- query rows over all heads, twice as many without the causal mask -- is what the choice depends on: a
-// tile's key blocks are taken one after the other, so a call takes at least the longest tile's chain, and there
-// is work for the whole chip beside that chain only from rows of about 100 000 on (32 heads: 3K tokens).
-//  - Below that the key blocks of a tile are dealt to two sets of waves (KSP = 2): half the chain for the same
-//    work, at the price of a merge and of a K/V stream for each set.  1000 tokens 33.8 -> 20.9 us, 2048 tokens
-//    58 -> 46 us, 8K tokens of 4 heads 173 -> 90 us; at rows 73 600 (2300 tokens) it is 58 us against 53 us.
-//    (The line is drawn for half skip; dense it would lie higher: 2048 tokens 48 us split, 53 us not.)
+// `rows` -- query rows over all heads, twice as many without the causal mask -- is what most lines depend on: a
+// tile's key blocks are taken one after the other, so a call takes at least the longest tile's chain, and the chip
+// holds 512 workgroups of four waves (rows 65 536 in 128-row tiles).
+//  - Up to there the key blocks of a tile are dealt to two sets of waves (KSP = 2, splits_tiles): half the chain for
+//    the same work, at the price of a merge and of a K/V stream for each set.  One set against two, 128-row tiles:
+//    1000 tokens 33.8 / 20.9, 2048 tokens (rows 65 536) 43.9 / 43.1 and dense 52.0 / 50.1, 2125 tokens 44.1 / 51.4 and
+//    dense 54.6 / 59.8; at head_dim 64 2048 tokens 32.5 / 31.2, 2304 tokens 36.6 / 39.8; its 64-row tiles 2048 tokens
+//    32.3 / 31.2, 3072 tokens 48.4 / 54.0.  With few heads, whose chains are longer, two sets would still pay a little
+//    beyond (2 heads, 34K tokens 548 / 460, 49K tokens 918 / 950).  64-row tiles at head_dim 128 take it up to rows
+//    45 056 where heads share (1408 tokens 32.9 / 28.0; with 1792 tokens 41.2 / 37.5 and 2048 tokens 46.2 / 44.1 it would
+//    pay up to 65 536) and to 32 768 where they do not and a share is half a CU (12 heads over 4: 2730 tokens
+//    49.0 / 44.3, 3400 tokens 59.4 / 61.6).  32-row tiles, where up to four heads share a workgroup, are not split.
 //  - V is rewritten into the workspace only where the pass over it pays for itself, which takes its reuse by many
-//    query tiles: head_dim 128 beyond 12K tokens (in place against rewritten: 4096 tokens 126 / 131 us, 12K equal,
-//    32K 6.33 / 6.27 ms, 64K 25.3 / 25.0 ms).  At head_dim 64 it never does (8K tokens 256 / 268 us, 32K 3.69 /
-//    3.81 ms).  The fp8 score product is built for the rewritten V.
+//    query tiles: head_dim 128, 128-row tiles, beyond 12K tokens.  In place / rewritten, single heads: 8K tokens
+//    408 / 411, 12K 899 / 900, 16K 1569 / 1565, 32K 6075 / 6026 (dense 8166 / 8093); 64 heads over 8, whose reuse is
+//    twice that: 8K 814 / 810, 12K 1779 / 1760; 16 over 8: 12K 451 / 456, 24K 1724 / 1718; 8 over 8, the least
+//    reuse: 12K 238 / 247, 24K 876 / 881, 32K 1542 / 1549 and dense even.  At head_dim 64 it never paid (8K tokens
+//    256 / 268, 32K 3690 / 3810 with an earlier kernel) and is not built.  The fp8 score product is built for the
+//    rewritten V.
 //  - Heads of a GQA group that share a workgroup share one K/V stream in LDS.  128-row tiles have waves enough
 //    without that, and two independent workgroups on a CU hide each other's barriers: single heads against pairs,
-//    8K tokens 2.8 % faster (dense 0 %), 16K 3.3 % (-0.7 %), 24K 2.8 % (-0.6 %).  But they read twice as much from
-//    L2 for a launch that the card's power limits, and beyond the L2 they drift apart in sequences many times its
-//    size: dense 32K tokens 0 to 2 % slower than pairs (half skip 1 % faster), 128K 2.5 % slower at half skip.
-//    Without the mask, where all tiles are equally long, pairs are never behind (4096 tokens 2 %, 6144 1 %, 8K
-//    even at half skip and 0.5 % dense).  So heads are paired beyond 24K tokens, without the mask beyond 3K; with
-//    the fp8 score product, whose K stream is half as wide, beyond 64K (16K tokens 6 % faster single, 64K 2 %).
-//    With 64 rows at head_dim 128 two heads fill the CU's two waves per SIMD (8K tokens 654 -> 428 us), with 32 rows four (1358 -> 469 us; two
-//    heads 731 us).  At head_dim 64 the smaller tiles of single heads already do and sharing pays on long
-//    sequences only: 64 rows from rows 131 072 on (8K tokens 279 -> 271 us, 3K tokens 47 -> 55 us), 32 rows two
-//    heads always (2000 tokens 41 -> 34 us) and four from 81 920 on (8K tokens 368 -> 285 us, 2000: 34 -> 39 us).
-//  - The score half alone (calibration) has registers and LDS to spare and shares where it can; 128-row tiles
-//    from rows 262 144 on (6000 tokens 209 us either way, 32K tokens 3.50 ms in pairs).
+//    8K tokens 408 / 416 (dense 542 / 534), 20K 2406 / 2483 (3191 / 3182), 24K 3474 / 3553 (4575 / 4583), and more the
+//    more is skipped (24K, 90 %: 2444 / 2662).  But they read twice as much from L2 for a launch that the card's power
+//    limits: 32K dense 8186 / 8074, half skip 6195 / 6212; 128K 2.5 % slower at half skip.  So pairs beyond 24K
+//    tokens; with the fp8 score product, whose K stream is half as wide, beyond 64K (16K tokens 6 % faster single,
+//    64K 2 %).  Without the mask, where all tiles are equally long, beyond 3K (3072 tokens 128 / 147, 4096 209 / 207,
+//    16K dense 4008 / 3946).
+//    A causal call of 881 to 1024 tiles, nearly two for each of the 512 places, is the exception: from 8K tokens on
+//    pairs are faster there, unless most is skipped (single / pairs: 8 heads over 2, 16K tokens dense 569 / 521, half
+//    434 / 407, 90 % 289 / 305; 16 over 8, 8K tokens 295 / 272, 225 / 212, 156 / 166).
+//    With 64 rows at head_dim 128 two heads fill the CU's two waves per SIMD (8K tokens 654 single, 428 pairs), with
+//    32 rows four (1358 single, 731 pairs, 469 four).  At head_dim 64 the smaller tiles of single heads already do,
+//    and sharing pays on long sequences only: 64 rows from rows 131 072 on (single / pairs: 3072 tokens 48.8 / 50.6,
+//    4096 tokens 79.3 / 72.8, 8K 266 / 247), 32 rows two heads always (2000 tokens 41 single, 34 pairs) and four from
+//    81 920 on (two / four: 2304 tokens 39.9 / 42.5, 2624 tokens 49.2 / 47.9, 8K 363 / 262).
+//  - 128-row tiles of head_dim 64: the CU holds three workgroups.  For a causal call of 513 to 768 tiles, which all
+//    three would hold at once, two to a CU are faster beyond 4K tokens (three / two: 8 heads over 8, 12K tokens
+//    165.5 / 155.3; 2 heads, 49K tokens 624 / 590; 28 heads over 4, 3500 tokens 52.8 / 56.4).
+//  - The score half alone (calibration) has registers and LDS to spare and shares where it can.  128-row tiles from
+//    rows 262 144 on (whole calibrations, single / pairs: 8K tokens 268.9 / 270.3, 16K 913 / 904); 64-row tiles always
+//    (500 tokens 46.0 / 46.4, 16K 1106 / 922; head_dim 64 595 / 541); 32-row tiles four (16K single 1571, pairs 1093,
+//    four 919; head_dim 64 748, 682, 542; up to 1000 tokens all within 1 us).
 // Results do not depend on how heads share; the split does change the order of sums, so it must not depend on
 // single_head or on the workspace, between which results are equal bit for bit.
 static int64_t dispatch_rows(const FwdParams &p) { return (int64_t)p.batch * p.hq * p.seqlen * (p.causal ? 1 : 2); }
@@ -1076,8 +1093,11 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
     const bool split = splits_tiles(p, head_dim, block_m);
     if (block_m == 128) {
         if (split) return d128 ? launch_fwd<128, 4, 1, 2, 2>(p, stream) : launch_fwd<64, 4, 1, 2, 3>(p, stream);
-        if (d128 && two && p.seqlen > (p.k8 ? 65536 : p.causal ? 24576 : 3072)) return launch_fwd<128, 4, 2, 1, 5>(p, stream);
-        return d128 ? launch_fwd<128, 4, 1, 1, 2>(p, stream) : launch_fwd<64, 4, 1, 1, 3>(p, stream);
+        const bool filling = p.causal && !p.k8 && p.seqlen >= 8192 && rows > 112640 && rows <= 131072;
+        if (d128 && two && (filling || p.seqlen > (p.k8 ? 65536 : p.causal ? 24576 : 3072))) return launch_fwd<128, 4, 2, 1, 5>(p, stream);
+        if (d128) return launch_fwd<128, 4, 1, 1, 2>(p, stream);
+        const bool two_to_a_cu = p.causal && p.seqlen > 4096 && rows <= 98304;
+        return launch_fwd<64, 4, 1, 1, 3>(p, stream, two_to_a_cu ? 16384 : 0);       // (40 KiB and these: a third does not fit)
     }
     if (block_m == 64 && d128) {
         if (split) return two ? launch_fwd<128, 2, 2, 2, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 2>(p, stream);
@@ -1085,7 +1105,7 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
     }
     if (block_m == 64) {
         if (split) return launch_fwd<64, 2, 1, 2, 2>(p, stream);
-        return two && rows > 131072 ? launch_fwd<64, 2, 2, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 1, 2>(p, stream);
+        return two && rows >= 131072 ? launch_fwd<64, 2, 2, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 1, 2>(p, stream);
     }
     if (d128) return four ? launch_fwd<128, 1, 4, 1, 2>(p, stream) : two ? launch_fwd<128, 1, 2, 1, 2>(p, stream) : launch_fwd<128, 1, 1, 1, 2>(p, stream);
     return four && rows > 81920 ? launch_fwd<64, 1, 4, 1, 4>(p, stream) : two ? launch_fwd<64, 1, 2, 1, 4>(p, stream) : launch_fwd<64, 1, 1, 1, 2>(p, stream);

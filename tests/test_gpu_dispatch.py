@@ -93,6 +93,7 @@ def test_split_tiles_with_lengths_and_thresholds_per_tile(d, bm):
     (32, 8, 2304, 128, 64, True, False, torch.bfloat16), (32, 8, 4160, 64, 64, True, False, torch.bfloat16),
     (32, 8, 2624, 64, 32, True, False, torch.bfloat16), (8, 2, 1024, 128, 32, True, False, torch.bfloat16),
     (4, 2, 1000, 128, 32, True, False, torch.float16),
+    (12, 6, 9800, 128, 128, True, False, torch.bfloat16), (16, 8, 8192, 128, 128, True, False, torch.float16),    # 924 and 1024 tiles
     (4, 2, 24640, 128, 128, True, False, torch.bfloat16),        # V from the workspace
     (32, 8, 4096, 128, 128, False, False, torch.bfloat16), (8, 4, 5120, 128, 128, False, False, torch.float16),   # V in place
     (4, 2, 65700, 128, 128, True, True, torch.bfloat16), (6, 3, 65610, 128, 128, True, True, torch.float16),      # fp8 scores
@@ -106,6 +107,17 @@ def test_shared_heads_are_bit_identical(hq, hkv, n, d, bm, causal, fp8, dtype):
         for x, y in zip(shared, single):
             assert torch.equal(x, y)
         assert (shared[2][..., 0].sum() > 0) == bool(tau.isfinite().all())
+
+
+@pytest.mark.parametrize("b, hq, hkv, n", [(1, 6, 2, 11000), (2, 3, 3, 12300), (1, 1, 1, 98304)])
+def test_two_workgroups_to_a_cu_change_nothing(b, hq, hkv, n):
+    """Calls of head_dim 64 that keep the third workgroup off a CU against the same element in a batch that does not, bit
+    for bit."""
+    q, k, v = make(b, n, hq, hkv, 64, "bnhd", torch.bfloat16, n)
+    tau = binding.bsfa_calibrate(q, k, [0.5])[0].to(DEV)
+    few, many = call(q, k, v, tau, 128, True), call(*(t.repeat(2, 1, 1, 1) for t in (q, k, v)), tau, 128, True)
+    for x, y in zip(few, many):
+        assert torch.equal(x, y[:b]) and torch.equal(x, y[b:])
 
 
 @pytest.mark.parametrize("hq, hkv, n", [(4, 2, 12700), (3, 1, 12416), (4, 2, 24641)])
