@@ -185,10 +185,13 @@ def _dev_check(*ts):
 
 def _raw_stream(stream, device) -> int:
     """hipStream_t of ``stream``, or of torch's current stream on ``device`` (asked for without building a
-    stream object: 0.2 us instead of 1.9)."""
+    stream object where this torch can: 0.2 us instead of 1.9)."""
     if stream is not None:
         return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    try:
+        return torch._C._cuda_getCurrentRawStream(device.index)
+    except AttributeError:                     # (no public name)
+        return torch.cuda.current_stream(device).cuda_stream
 
 
 def bsfa_forward(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, thresholds: torch.Tensor,

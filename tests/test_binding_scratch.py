@@ -70,3 +70,11 @@ def test_scratch_belongs_to_the_call_and_to_its_stream(recorded):
     allocated_on = {t.data_ptr(): s for t, s in made}
     for ws, launched_on in lib.calls:
         assert allocated_on[ws] == launched_on
+
+
+def test_stream_without_the_quick_query(monkeypatch):
+    """Where torch lacks its unofficial query for the current stream, the public one answers."""
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: types.SimpleNamespace(cuda_stream=77))
+    assert binding._raw_stream(None, torch.device("cuda", 0)) == 77
+    assert binding._raw_stream(types.SimpleNamespace(cuda_stream=5), torch.device("cuda", 0)) == 5
