@@ -214,9 +214,10 @@ def bsfa_forward(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, thresholds: 
         _same_16bit("bsfa_forward", q, k, v, out)
     if thresholds.dtype != torch.float32 or not thresholds.is_contiguous():
         raise TypeError("bsfa_forward: thresholds must be contiguous float32")
+    _, _, Hq, _ = q.shape
     ts = thresholds.shape
     per_tile = len(ts) == 2
-    if len(ts) not in (1, 2) or ts[0] != q.shape[2] or (per_tile and ts[1] < 1):
+    if len(ts) not in (1, 2) or ts[0] != Hq or (per_tile and ts[1] < 1):
         raise ValueError("bsfa_forward: thresholds shape %s, expected [Hq] or [Hq, tiles]" % (tuple(ts),))
     if out is None:
         out = torch.empty_like(q)

@@ -78,3 +78,11 @@ def test_stream_without_the_quick_query(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: types.SimpleNamespace(cuda_stream=77))
     assert binding._raw_stream(None, torch.device("cuda", 0)) == 77
     assert binding._raw_stream(types.SimpleNamespace(cuda_stream=5), torch.device("cuda", 0)) == 5
+
+
+@pytest.mark.parametrize("shape", [(128, 128), (1, 128, 2)])
+def test_forward_refuses_tensors_that_are_not_four_dimensional(recorded, shape):
+    q = torch.zeros(shape, dtype=torch.bfloat16)
+    for tau in (torch.zeros(2), torch.zeros(128)):
+        with pytest.raises(ValueError):
+            binding.bsfa_forward(q, q, q, tau, out=q)
