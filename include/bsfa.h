@@ -85,8 +85,8 @@ typedef struct {
                                      counts. */
     int32_t single_head_groups;   /* optional tuning knob, 0 by default: the library decides how many query heads of
                                      a GQA group one workgroup handles together (their K/V stream in LDS is then
-                                     shared): up to four with small tiles, with block_m = 128 one, or two on
-                                     long sequences.
+                                     shared): up to four with small tiles, with block_m = 128 one, or two
+                                     where that is faster (long sequences above all).
                                      1: always one.  Results are identical either way. */
     int32_t gate_mode;            /* optional, bsfa_forward only.  0: the paper's gate (block maximum against the
                                      threshold, Section 4.1).  1: the running-maximum predicate the paper

@@ -30,8 +30,9 @@
 // operand is a plain 16-byte LDS read; without one it is gathered with the transposing read.
 //
 // What bounds it.  Long sequences: the matrix pipe at the clock the card holds under this load (a plain
-// library product reaches 1360 TFLOP/s here, this kernel 1.12 dense) and, in the stretch between the last
-// score MFMA and the first PV MFMA of a block, instruction issue.  Two workgroups of four waves on a CU
+// library product reaches 1360 TFLOP/s here, this kernel 1080 to 1150 dense, busy in 57 % of the cycles) and
+// instruction issue (the two waves of a SIMD issue in 81 % of the cycles together, in 91 % with single heads),
+// above all in the stretch between the last score MFMA and the first PV MFMA of a block.  Two workgroups of four waves on a CU
 // (HP = 1) run independently and hide that stretch for each other; eight waves that share a K/V stream
 // (HP = 2) all stand at the same barrier, but read half as much from L2 (see launch_forward for the line).
 // Short sequences: the chain of key blocks of the longest tile, about 1.6 us a block.
