@@ -1017,15 +1017,23 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 // `rows` -- query rows over all heads, twice as many without the causal mask -- is what most lines depend on: a
 // tile's key blocks are taken one after the other, so a call takes at least the longest tile's chain, and the chip
 // holds 512 workgroups of four waves (rows 65 536 in 128-row tiles).
-//  - Up to there the key blocks of a tile are dealt to two sets of waves (KSP = 2, splits_tiles): half the chain for
-//    the same work, at the price of a merge and of a K/V stream for each set.  One set against two, 128-row tiles:
-//    1000 tokens 33.8 / 20.9, 2048 tokens (rows 65 536) 43.9 / 43.1 and dense 52.0 / 50.1, 2125 tokens 44.1 / 51.4 and
-//    dense 54.6 / 59.8; at head_dim 64 2048 tokens 32.5 / 31.2, 2304 tokens 36.6 / 39.8; its 64-row tiles 2048 tokens
-//    32.3 / 31.2, 3072 tokens 48.4 / 54.0.  With few heads, whose chains are longer, two sets would still pay a little
-//    beyond (2 heads, 34K tokens 548 / 460, 49K tokens 918 / 950).  64-row tiles at head_dim 128 take it up to rows
-//    45 056 where heads share (1408 tokens 32.9 / 28.0; with 1792 tokens 41.2 / 37.5 and 2048 tokens 46.2 / 44.1 it would
-//    pay up to 65 536) and to 32 768 where they do not and a share is half a CU (12 heads over 4: 2730 tokens
-//    49.0 / 44.3, 3400 tokens 59.4 / 61.6).  32-row tiles, where up to four heads share a workgroup, are not split.
+//  - Up to there the key blocks of a tile may be dealt to two sets of waves (KSP = 2, splits_tiles): half the chain
+//    for the same work, at the price of a merge, of a K/V stream for each set, and of half the places: a split
+//    workgroup of eight waves has a CU to itself.  One set against two, 128-row tiles:
+//     * as long as every workgroup has a place: 256 tiles of 1000 tokens 25.3 / 22.4, of 2048 21 %, of 4096 26 %
+//       faster split; 512 tokens 15.6 / 15.4.  (Below that the merge costs more than the chain, 300 tokens 11.7 / 12.2,
+//       64 tokens 7.0 / 9.1, but a call then takes the host 11 us; and elements of a batch get the bits of a call of
+//       their own.)
+//     * with up to two workgroups to a place it takes a chain of 20 blocks or more: 8 x 1000 tokens of 8 heads
+//       (512 tiles) 26.2 / 30.7, 1536 tokens of 32 heads 33.8 / 31.2, 2048 tokens 43.9 / 43.1 (dense 52.0 / 50.1).
+//     * beyond that nothing is gained but for the longest chains (9 x 1536 tokens of 4 heads 24 % slower split, 2125
+//       tokens of 32 heads 44.1 / 51.4; 2 heads, 34K tokens 548 / 460), and from rows 65 536 on they are not split
+//       (2 heads, 49K tokens 918 / 950).
+//    64-row tiles at head_dim 64, two split workgroups to a CU, lie alike (2048 tokens 32.3 / 31.2, 3072 48.4 / 54.0);
+//    at head_dim 128 they are taken up to rows 45 056 where heads share (1408 tokens 32.9 / 28.0; with 1792 tokens
+//    41.2 / 37.5 and 2048 tokens 46.2 / 44.1 it would pay up to 65 536) and to 32 768 where they do not and a share is
+//    half a CU (12 heads over 4: 2730 tokens 49.0 / 44.3, 3400 tokens 59.4 / 61.6).  32-row tiles, where up to four
+//    heads share a workgroup, are not split.
 //  - V is rewritten into the workspace only where the pass over it pays for itself, which takes its reuse by many
 //    query tiles: head_dim 128, 128-row tiles, beyond 12K tokens.  In place / rewritten, single heads: 8K tokens
 //    408 / 411, 12K 899 / 900, 16K 1569 / 1565, 32K 6075 / 6026 (dense 8166 / 8093); 64 heads over 8, whose reuse is
@@ -1041,13 +1049,14 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    tokens; with the fp8 score product, whose K stream is half as wide, beyond 64K (16K tokens 6 % faster single,
 //    64K 2 %).  Without the mask, where all tiles are equally long, beyond 3K (3072 tokens 128 / 147, 4096 209 / 207,
 //    16K dense 4008 / 3946).
-//    A causal call of 881 to 1024 tiles, nearly two for each of the 512 places, is the exception: from 8K tokens on
+//    A causal call of 865 to 1024 tiles, nearly two for each of the 512 places, is the exception: from 8K tokens on
 //    pairs are faster there, unless most is skipped (single / pairs: 8 heads over 2, 16K tokens dense 569 / 521, half
 //    434 / 407, 90 % 289 / 305; 16 over 8, 8K tokens 295 / 272, 225 / 212, 156 / 166).
 //    With 64 rows at head_dim 128 two heads fill the CU's two waves per SIMD (8K tokens 654 single, 428 pairs), with
 //    32 rows four (1358 single, 731 pairs, 469 four).  At head_dim 64 the smaller tiles of single heads already do,
 //    and sharing pays on long sequences only: 64 rows from rows 131 072 on (single / pairs: 3072 tokens 48.8 / 50.6,
-//    4096 tokens 79.3 / 72.8, 8K 266 / 247), 32 rows two heads always (2000 tokens 41 single, 34 pairs) and four from
+//    4096 tokens 79.3 / 72.8, 8K 266 / 247; with elements of different lengths, whose rows are fewer than the call's,
+//    from 393 216 on: 2 x up to 5000 tokens 168 / 180, 3 x up to 5000 231 / 211), 32 rows two heads always (2000 tokens 41 single, 34 pairs) and four from
 //    81 920 on (two / four: 2304 tokens 39.9 / 42.5, 2624 tokens 49.2 / 47.9, 8K 363 / 262).
 //  - 128-row tiles of head_dim 64: the CU holds three workgroups.  For a causal call of 513 to 768 tiles, which all
 //    three would hold at once, two to a CU are faster beyond 4K tokens (three / two: 8 heads over 8, 12K tokens
@@ -1064,8 +1073,12 @@ static bool splits_tiles(const FwdParams &p, int head_dim, int block_m)
 {
     // (the comparison predicate depends on the order of the blocks; the mask words of a split tile must fit the LDS)
     if (block_m == 32 || p.k8 || p.gate_mode || p.mask_words > kSplitMaskWords) return false;
-    // (64 rows at head_dim 128: two shares of one head are only four waves, and 128 KiB of LDS: one workgroup per CU)
-    return dispatch_rows(p) <= (block_m == 64 && head_dim == 128 ? (p.group % 2 == 0 ? 45056 : 32768) : 65536);
+    const bool wide64 = block_m == 64 && head_dim == 128, shared = wide64 && p.group % 2 == 0;
+    if (dispatch_rows(p) > (wide64 ? (shared ? 45056 : 32768) : 65536)) return false;
+    // workgroups, with the empty ones that deal KV heads to XCDs, and the places that the chip has for them
+    const int64_t kv = (int64_t)p.batch * p.hkv, places = block_m == 64 && head_dim == 64 ? 512 : 256;
+    const int64_t wgs = (kv >= 8 ? (kv + 7) / 8 * 8 : kv) * (p.group / (shared ? 2 : 1)) * p.mq;
+    return wgs <= places || (p.causal && p.mkv >= (wgs <= 2 * places ? 20 : 64));
 }
 
 bool rewrites_v(const FwdParams &p, int head_dim, int block_m)
@@ -1094,10 +1107,10 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
     const bool split = splits_tiles(p, head_dim, block_m);
     if (block_m == 128) {
         if (split) return d128 ? launch_fwd<128, 4, 1, 2, 2>(p, stream) : launch_fwd<64, 4, 1, 2, 3>(p, stream);
-        const bool filling = p.causal && !p.k8 && p.seqlen >= 8192 && rows > 112640 && rows <= 131072;
+        const bool filling = p.causal && !p.seqlens && !p.k8 && p.seqlen >= 8192 && rows > 110592 && rows <= 131072;
         if (d128 && two && (filling || p.seqlen > (p.k8 ? 65536 : p.causal ? 24576 : 3072))) return launch_fwd<128, 4, 2, 1, 5>(p, stream);
         if (d128) return launch_fwd<128, 4, 1, 1, 2>(p, stream);
-        const bool two_to_a_cu = p.causal && p.seqlen > 4096 && rows <= 98304;
+        const bool two_to_a_cu = p.causal && !p.seqlens && p.seqlen > 4096 && rows > 65536 && rows <= 98304;
         return launch_fwd<64, 4, 1, 1, 3>(p, stream, two_to_a_cu ? 16384 : 0);       // (40 KiB and these: a third does not fit)
     }
     if (block_m == 64 && d128) {
@@ -1106,7 +1119,7 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
     }
     if (block_m == 64) {
         if (split) return launch_fwd<64, 2, 1, 2, 2>(p, stream);
-        return two && rows >= 131072 ? launch_fwd<64, 2, 2, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 1, 2>(p, stream);
+        return two && rows >= (p.seqlens ? 393216 : 131072) ? launch_fwd<64, 2, 2, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 1, 2>(p, stream);
     }
     if (d128) return four ? launch_fwd<128, 1, 4, 1, 2>(p, stream) : two ? launch_fwd<128, 1, 2, 1, 2>(p, stream) : launch_fwd<128, 1, 1, 1, 2>(p, stream);
     return four && rows > 81920 ? launch_fwd<64, 1, 4, 1, 4>(p, stream) : two ? launch_fwd<64, 1, 2, 1, 4>(p, stream) : launch_fwd<64, 1, 1, 1, 2>(p, stream);

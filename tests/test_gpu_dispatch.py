@@ -36,6 +36,8 @@ CASES = [
     (1, 1, 4, 2, 128, 128, True, "bnhd"), (1, 64, 4, 2, 128, 128, True, "bnhd"), (1, 65, 4, 2, 64, 128, True, "qkv"),
     (1, 127, 2, 2, 64, 64, True, "bnhd"), (2, 129, 4, 1, 128, 64, True, "bhnd"), (1, 193, 3, 1, 128, 64, True, "qkv"),
     (3, 1000, 8, 2, 128, 128, True, "qkv"), (1, 2047, 6, 2, 64, 64, True, "bnhd"), (2, 777, 4, 1, 64, 32, True, "bnhd"),
+    (1, 449, 4, 2, 128, 128, True, "bnhd"), (1, 512, 4, 2, 128, 128, True, "bnhd"), (1, 257, 2, 1, 64, 128, True, "qkv"), (1, 513, 8, 4, 128, 64, True, "bnhd"),
+    (1, 255, 3, 1, 128, 64, True, "bhnd"), (1, 193, 2, 2, 64, 64, True, "bnhd"), (1, 1217, 40, 8, 128, 128, True, "bnhd"), (1, 4100, 20, 4, 64, 64, True, "bnhd"),
     (1, 640, 4, 2, 128, 128, False, "bnhd"), (1, 320, 4, 2, 64, 64, False, "bhnd"), (2, 832, 6, 2, 128, 64, False, "bnhd"),
     (1, 960, 8, 2, 128, 32, False, "qkv"), (1, 512, 4, 1, 64, 32, False, "bnhd"), (1, 4096, 2, 1, 128, 128, False, "bnhd"),
 ]
@@ -65,6 +67,20 @@ def test_small_calls_agree_with_every_other_form(case):
         assert torch.equal(mask, alone[3]) and torch.equal(counts, alone[2])
         assert (out.float() - alone[0].float()).abs().max() <= 2.0 ** -7 * v.float().abs().max()
         assert (lse - alone[1]).abs().max() <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("b, n, hq, hkv, d, bm", [
+    (4096, 1, 8, 2, 128, 128), (12, 300, 8, 2, 128, 128), (8, 1000, 8, 2, 64, 128), (9, 512, 8, 2, 128, 64), (9, 700, 8, 2, 64, 64),  # many tiles
+    (9, 1536, 4, 2, 128, 128),                                                                                          # unevenly dealt to the XCDs
+])
+def test_short_prompts_are_not_split(b, n, hq, hkv, d, bm):
+    """Calls whose tiles gain nothing from two sets of waves give the bits of one set: those of the same elements in a
+    batch beyond the last line."""
+    q, k, v = make(b, n, hq, hkv, d, "bnhd", torch.bfloat16, n)
+    tau = torch.full((hq,), 2.5, device=DEV)
+    times = 2 + 200000 // (b * hq * n)
+    for x, y in zip(call(q, k, v, tau, bm, True), call(*(t.repeat(times, 1, 1, 1) for t in (q, k, v)), tau, bm, True)):
+        assert torch.equal(x, y[:b]) and torch.equal(x, y[-b:])
 
 
 @pytest.mark.parametrize("d, bm", [(128, 128), (64, 128), (128, 64), (64, 64)])
