@@ -1020,15 +1020,15 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //  - Up to there the key blocks of a tile may be dealt to two sets of waves (KSP = 2, splits_tiles): half the chain
 //    for the same work, at the price of a merge, of a K/V stream for each set, and of half the places: a split
 //    workgroup of eight waves has a CU to itself.  One set against two, 128-row tiles:
-//     * as long as every workgroup has a place: 256 tiles of 1000 tokens 25.3 / 22.4, of 2048 21 %, of 4096 26 %
-//       faster split; 512 tokens 15.6 / 15.4.  (Below that the merge costs more than the chain, 300 tokens 11.7 / 12.2,
-//       64 tokens 7.0 / 9.1, but a call then takes the host 11 us; and elements of a batch get the bits of a call of
-//       their own.)
+//     * as long as every workgroup has a place (8 heads over 2, 256 tiles): 1000 tokens 25.1 / 22.2, 2048 tokens
+//       37.6 / 31.7, 4096 tokens 66.9 / 53.1, 512 tokens dense 17.3 / 16.8.  (Below that the merge costs more than the
+//       chain, 300 tokens dense 12.3 / 12.6, 64 tokens 7.0 / 9.1, but a call then takes the host 11 us; and elements of
+//       a batch get the bits of a call of their own.)
 //     * with up to two workgroups to a place it takes a chain of 20 blocks or more: 8 x 1000 tokens of 8 heads
-//       (512 tiles) 26.2 / 30.7, 1536 tokens of 32 heads 33.8 / 31.2, 2048 tokens 43.9 / 43.1 (dense 52.0 / 50.1).
-//     * beyond that nothing is gained but for the longest chains (9 x 1536 tokens of 4 heads 24 % slower split, 2125
-//       tokens of 32 heads 44.1 / 51.4; 2 heads, 34K tokens 548 / 460), and from rows 65 536 on they are not split
-//       (2 heads, 49K tokens 918 / 950).
+//       (512 tiles) 27.3 / 31.7, 1536 tokens of 32 heads 33.8 / 31.2, 2048 tokens 43.9 / 43.1 (dense 52.0 / 50.1).
+//     * beyond that nothing is gained but for the longest chains (9 x 1536 tokens of 4 heads, whose KV heads lie
+//       unevenly on the XCDs, 35.4 / 46.4, 2125 tokens of 32 heads 44.1 / 51.4; 2 heads, 34K tokens 548 / 460), and
+//       from rows 65 536 on tiles are not split (2 heads, 49K tokens 918 / 950).
 //    64-row tiles at head_dim 64, two split workgroups to a CU, lie alike (2048 tokens 32.3 / 31.2, 3072 48.4 / 54.0);
 //    at head_dim 128 they are taken up to rows 45 056 where heads share (1408 tokens 32.9 / 28.0; with 1792 tokens
 //    41.2 / 37.5 and 2048 tokens 46.2 / 44.1 it would pay up to 65 536) and to 32 768 where they do not and a share is
