@@ -1,5 +1,5 @@
 // Device-side building blocks shared by the forward kernels of libbsfa.so (gfx950, wave64):
-// element types and MFMA wrappers, the swizzled LDS tile layout with its direct HBM -> LDS copies,
+// element types and MFMA wrappers, the LDS tile layout with its direct HBM -> LDS copies,
 // counters and barriers that leave those copies in flight, wave-level maxima, work decomposition.
 #pragma once
 #include "bsfa_internal.h"
@@ -68,74 +68,56 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 #define GLB_PTR(T, p) ((const __attribute__((address_space(1))) T *)(p))
 
 // ---- LDS tile layout --------------------------------------------------------------------
-// A K or V tile is 64 rows x D bf16, stored as 16-byte chunks, row-major, the chunk index
-// XOR-ed with a function of the row so that the operand gathers spread over the banks.  The
-// swizzle is applied on the global side of the copy (lane -> which chunk it fetches); the LDS
-// side of a direct copy is always linear (wave base + lane * 16 bytes).  Both swizzles only
-// touch chunk bits that the gather loops step through with XOR-able constants, so every
-// operand address is  (per-lane base) ^ (loop constant) + (immediate offset).
-template <int D> __device__ __forceinline__ int swz_k(int row)
+// A tile is stored as units of 1024 bytes, what one direct copy instruction of a wave writes (64 lanes x 16 bytes, in
+// lane order: the LDS side of a direct copy is linear), `pitch` bytes apart.  Of the tile's R rows, U units hold R / U
+// rows each: unit u the rows u, u + U, u + 2U, ...  So
+//     address(row, byte) = (row % U) * pitch + (row / U) * row_bytes + byte
+// is a per-lane base plus a constant for every operand a wave reads: all gathers are one base register and immediate
+// offsets.  The bytes a unit is longer than 1024 spread the rows that are read together over the banks: 16 for reads
+// of 16 bytes per row (16 rows at a time), 32 and 64 for the transposing reads of V (4 rows x 32 bytes from two places
+// 128 bytes apart at head_dim 128, 4 rows x 64 bytes at head_dim 64).
+// (An XOR of the chunk index with the row spreads them as well, but costs a vector instruction per operand address:
+// 14 a key block, and the registers for them.)
+constexpr int kUnit = 1024;
+constexpr int kPitch16 = kUnit + 16;                                   // K, transposed V, fp8 K
+constexpr int v_pitch(int d) { return d == 128 ? kUnit + 32 : kUnit + 64; }   // V in place
+
+// Byte offset (relative to the tile's first row) of the 16 bytes that a lane copies of unit `unit` of a tile of rows
+// of D elements; a unit `n` further starts n rows further.
+template <int D>
+__device__ __forceinline__ uint32_t unit_src_offset(int unit, int lane, int stride_n)
 {
-    return (D == 128) ? (row & 15) : ((row >> 1) & 7);
-}
-template <int D> __device__ __forceinline__ int swz_v(int row)
-{
-    return (D == 128) ? ((row & 7) << 1) : (((row >> 1) & 3) << 1);
+    constexpr int CPR = D / 8;          // 16-byte chunks of a row; rows of a unit: 64 / CPR; units: D / 8
+    return (uint32_t)((unit + (D / 8) * (lane / CPR)) * stride_n + 8 * (lane % CPR)) * 2u;
 }
 
-// Byte offset (relative to the tile's first row) of the chunk thread `tid` copies in
-// repetition r; rows at and beyond `rows` are fetched from row rows - 1.
-template <int D, int NT, bool ISV>
-__device__ __forceinline__ uint32_t chunk_src_offset(int r, int tid, int stride_n, int rows = 64)
+// Buffer descriptor of one tile: bytes at and beyond `bytes` are not read, their LDS bytes become 0.  That is all the
+// last key block of a sequence needs that does not fill it: its absent keys are hidden from every real row by the
+// causal mask and meet probabilities of 0 in the second product (Section 4.3's padding never shows).
+constexpr uint32_t kWholeTile = 0x7fffffffu;                           // (a tile is shorter: see launch_forward)
+__device__ __forceinline__ i32x4 tile_rsrc(const unsigned char *tile, uint32_t bytes)
 {
-    constexpr int CPR = D / 8;
-    const int sigma = r * NT + tid;
-    const int row = sigma / CPR, cp = sigma % CPR;
-    const int c = cp ^ (ISV ? swz_v<D>(row) : swz_k<D>(row));
-    return (uint32_t)(min(row, rows - 1) * stride_n + 8 * c) * 2u;
+    const uint64_t a = reinterpret_cast<uint64_t>(tile);
+    return i32x4{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xffffu), (int)bytes, 0x00020000};
 }
+// bytes of the first `rows` rows of a tile
+template <int D> __device__ __forceinline__ uint32_t row_bytes(int rows, int stride_n) { return (uint32_t)((rows - 1) * stride_n + D) * 2u; }
 
-// Asynchronous HBM -> LDS copy of one tile in NREP repetitions of NT x 16 bytes (NREP = 64 * D * 2 /
-// 16 / NT for a 64 x D tile of 16-bit elements); lds_tile is the byte address of the tile's slot.  Each lane fetches 16 bytes; the hardware writes them at M0 + lane * 16.  The tile's first
-// row is addressed through a scalar base (it is the same for the whole workgroup), each lane adds
-// its 32-bit byte offset (callers pass a base computed from workgroup-uniform values only; a base
-// the compiler cannot prove uniform is rejected at build time, the asm operand being a scalar pair).
-// Completion is tracked by vmcnt, which this kernel manages itself
-// (wait_vmcnt): the instruction is emitted through inline asm so that the compiler does not
-// serialise every later LDS read behind all copies in flight.
-// off: one lane offset per repetition, or a single one and `rep` bytes between the repetitions' bases.
-template <int NREP, int NT, int NOFF>
-__device__ __forceinline__ void tile_copy_async(const void *gtile, const uint32_t (&off)[NOFF], uint32_t rep,
-                                                uint32_t lds_tile, int wave)
+// One unit of an asynchronous HBM -> LDS copy: each lane fetches 16 bytes, the hardware writes them at M0 + lane * 16.
+// Repetition r of a wave's share of a tile goes to lds + r * LDS_STEP (lds: the wave's first unit) and is fetched `rep`
+// bytes behind the one before; `off` is this lane's running offset.  The instruction is emitted through inline asm so
+// that the compiler does not serialise every later LDS read behind all copies in flight: completion is tracked by
+// vmcnt, which the kernel manages itself (wait_vmcnt).  The one wait state between a write of M0 and the load is the
+// addition of `rep`, or a nop.
+template <int R, int LDS_STEP>
+__device__ __forceinline__ void unit_copy_async(uint32_t &off, uint32_t rep, i32x4 rsrc, uint32_t lds)
 {
-    static_assert(NOFF == NREP || NOFF == 1, "one offset, or one per repetition");
-#pragma unroll
-    for (int r = 0; r < NREP; ++r) {
-        const void *const base = NOFF == 1 ? static_cast<const unsigned char *>(gtile) + (size_t)(r * rep) : gtile;
-        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_tile + (uint32_t)(r * NT + wave * 64) * 16u);
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :
-                     : "s"(dst), "v"(off[NOFF == 1 ? 0 : r]), "s"(base)
-                     : "memory", "m0");
-    }
-}
-
-// The same copy for the last key block of a sequence that does not fill it: rows at and beyond
-// `rows` are fetched from row rows-1, which is the repeat-last-token padding of Section 4.3
-// (and keeps the copy inside the caller's buffers).  Same number of requests per lane as
-// tile_copy_async, so the vmcnt bookkeeping does not change.  The offsets are computed here, at
-// the one place per sequence that needs them, from the lane id (no long-lived registers).
-template <int D, int NT, bool ISV>
-__device__ __forceinline__ void tile_copy_async_clamped(const uint16_t *gtile, int stride_n, int rows,
-                                                        uint32_t lds_tile, int wave)
-{
-    int tid;                            // (volatile: keeps the lane id and the offsets from being hoisted out of the key loop)
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(tid));
-    tid += wave * 64;
-    uint32_t off[64 * (D / 8) / NT];
-#pragma unroll
-    for (int r = 0; r < 64 * (D / 8) / NT; ++r) off[r] = chunk_src_offset<D, NT, ISV>(r, tid, stride_n, rows);
-    tile_copy_async<64 * (D / 8) / NT, NT>(gtile, off, 0u, lds_tile, wave);
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds);
+    if constexpr (R == 0)
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds" : : "v"(off), "s"(dst), "s"(rsrc) : "memory", "m0");
+    else
+        asm volatile("s_add_u32 m0, %1, %2\n\tv_add_u32 %0, %3, %0\n\tbuffer_load_dwordx4 %0, %4, 0 offen lds"
+                     : "+v"(off) : "s"(dst), "n"(R * LDS_STEP), "s"(rep), "s"(rsrc) : "memory", "m0", "scc");
 }
 
 // s_waitcnt vmcnt(N) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14, no wait on the others)
@@ -181,6 +163,15 @@ __device__ __forceinline__ float wave_max_paired(float x)
                  __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 16)));
 }
 
+// The same scalar, unknown to the compiler.  Where both sides of a decision work on the accumulators, two one-sided
+// branches on values it cannot relate keep every accumulator in its registers; as two sides of one branch (or threaded
+// into one path with the next decision) they are given registers of their own, and hundreds are spilled.
+template <class T> __device__ __forceinline__ T opaque(T x)
+{
+    asm("" : "+s"(x));
+    return x;
+}
+
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order: a fully unrolled loop
 // whose body sees its index as a constant expression
 template <int... I, class F>
@@ -191,6 +182,11 @@ __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>
 template <int N, class F> __device__ __forceinline__ void static_for(F &&f)
 {
     static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
+// the same for LO .. HI - 1
+template <int LO, int HI, class F> __device__ __forceinline__ void static_range(F &&f)
+{
+    static_for<HI - LO>([&](auto n) { f(std::integral_constant<int, LO + decltype(n)::value>{}); });
 }
 
 // Work decomposition: a work item is (batch b, KV head, group of HP query heads, query tile i).

@@ -44,10 +44,11 @@ struct ScoreTile {
     f32x16 s[2];          // S^T: [32-key half], raw q.k (no 1/sqrt(d)); column = this lane's query
     float mx0;            // fp8 score product: lane maximum of s[0]
     float mx;             // row max of the lane's query, equal in lanes l and l^32
-    bool keep;            // gate decision of this wave's head (uniform over the head's waves)
-    bool any_keep;        // some head of the workgroup keeps the block (workgroup-uniform): V is fetched
+    uint32_t keep;        // gate decision of this wave's head (uniform over the head's waves; a number, so that it
+                          // and every branch on it are scalar)
+    uint32_t any_keep;    // some head of the workgroup keeps the block (workgroup-uniform): V is fetched
     float alpha;          // kept blocks: factor that rescales the accumulator, if ...
-    bool resc;            // ... the running maximum of some row of the wave has grown
+    uint64_t resc;        // ... the running maximum of some row of the wave has grown (the lanes whose row's has)
 };
 
 // Waves per SIMD the registers are allocated for: two, or three at head_dim 64 where the LDS holds as many
@@ -57,8 +58,11 @@ constexpr int min_waves(int d, int waves, int lds_bytes)
     return d == 64 && waves * (160 * 1024 / (lds_bytes + 1024)) >= 12 && waves <= 4 ? 3 : 2;
 }
 
+constexpr int k_slot_bytes(int d) { return d / 8 * kPitch16; }
+constexpr int v_slot_bytes(int d) { return d / 8 * v_pitch(d); }
+
 template <int D, int NWH, int HP, int KSP, int KR, bool CALIB, bool F16, bool VT, bool QK8>
-__global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * KSP, KSP * (KR + 2) * 128 * D)) bsfa_fwd_kernel(const FwdParams p)
+__global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * KSP, KSP * (KR * k_slot_bytes(D) + 2 * v_slot_bytes(D)))) bsfa_fwd_kernel(const FwdParams p)
 {
     typedef typename Elem<F16>::T el;                    // element type of Q, K, V, P, O
     typedef typename Elem<F16>::x8 bf16x8;               // (the vector names keep the default type's name)
@@ -76,14 +80,17 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     constexpr int NST = 64 * CPR / NT;                   // copy repetitions per 16-bit tile (V; K unless QK8)
     constexpr int NSTK = QK8 ? NST / 2 : NST;            // ... per K tile (fp8 tiles are half the bytes)
     static_assert(!QK8 || (D == 128 && NST >= 2), "fp8 score operands: head_dim 128, at most 512 threads");
-    constexpr int TILE_BYTES = BN * D * 2;
     constexpr int ROW_BYTES = D * 2;
+    constexpr int NWS = NT / 64;                         // waves that share one stream
+    constexpr int PITCH_V = VT ? kPitch16 : v_pitch(D);
+    constexpr int KSLOT = k_slot_bytes(D), VSLOT = v_slot_bytes(D);   // LDS bytes of a K and of a V tile
+    constexpr int SHARE = KR * KSLOT + (CALIB ? 0 : 2) * VSLOT;       // ... of a stream of tiles
     constexpr int R = KR + 1;        // K tiles are requested R blocks ahead
     constexpr int VR = CALIB ? 0 : 2;
     static_assert(64 * CPR % NT == 0, "every thread copies the same number of chunks");
     static_assert(NST >= 1 && (R < 4 || NSTK * (R - 3) < 64), "copy repetitions");
 
-    __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[KSP * (KR + VR) * TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[KSP * SHARE];
     __shared__ float lds_red[2][NW];                                  // the waves' block maxima, where somebody asks for them
     __shared__ __attribute__((aligned(8))) uint8_t lds_flag[2][NW];   // the waves' keep flags
     __shared__ uint32_t lds_mask[HP][KSP > 1 ? kSplitMaskWords : 1];  // KSP > 1: the tiles' skip masks, put together
@@ -97,8 +104,8 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     const int hsel = wave / NWH, wrow = wave % NWH;      // which head of the group, which 32-row slice
     const int team = wave_all / NWH;                     // the NWH waves that decide about a block together
     // V slots first: their gather offsets then fit the 16-bit immediate of the LDS reads
-    const uint32_t lds_v0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw) + ksel * (KR + VR) * TILE_BYTES;
-    const uint32_t lds_k0 = lds_v0 + VR * TILE_BYTES;
+    const uint32_t lds_v0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw) + ksel * SHARE;
+    const uint32_t lds_k0 = lds_v0 + VR * VSLOT;
     const uint32_t lds_flag0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint8_t *)lds_flag);
     const int h = h0 + hsel;
     const int l32 = lane & 31, hh = lane >> 5;
@@ -144,34 +151,34 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // threshold of this wave's head; tiles past the calibrated length use its last tile's (Section 4.3)
     const float tau_own = CALIB ? -INFINITY      // the score half takes no decisions
                                 : p.tau[p.tau_per_tile ? (int64_t)h * p.tau_tiles + min(i, p.tau_tiles - 1) : h];
-    // Source offsets of the copies.  Where a repetition covers a multiple of 16 rows (the period of the swizzles;
-    // and for tiles copied linearly) all repetitions share one lane offset and the scalar base advances.
-    constexpr bool ONE_OFF = (NT / CPR) % 16 == 0;
-    constexpr int NKO = QK8 || ONE_OFF ? 1 : NSTK, NVO = VT || ONE_OFF ? 1 : NST;
-    uint32_t koff[NKO], voff[NVO];
-#pragma unroll
-    for (int r = 0; r < NKO; ++r) koff[r] = QK8 ? (uint32_t)tid * 16u : chunk_src_offset<D, NT, false>(r, tid, (int)p.ksn);
-#pragma unroll
-    for (int r = 0; r < NVO; ++r) voff[r] = VT ? (uint32_t)tid * 16u : chunk_src_offset<D, NT, true>(r, tid, (int)p.vsn);
-    const uint32_t krep = QK8 ? NT * 16u : (uint32_t)(NT / CPR) * (uint32_t)p.ksn * 2u;      // bytes from one repetition to the next
-    const uint32_t vrep = VT ? NT * 16u : (uint32_t)(NT / CPR) * (uint32_t)p.vsn * 2u;
+    // source of this lane's part of a copy's first repetition, and the bytes from one repetition to the next
+    const uint32_t koff = QK8 ? (uint32_t)tid * 16u : unit_src_offset<D>(wave, lane, (int)p.ksn);
+    const uint32_t voff = VT ? (uint32_t)tid * 16u : unit_src_offset<D>(wave, lane, (int)p.vsn);
+    const uint32_t krep = NWS * (QK8 ? (uint32_t)kUnit : (uint32_t)p.ksn * 2u), vrep = NWS * (VT ? (uint32_t)kUnit : (uint32_t)p.vsn * 2u);
     // QK8: K comes from the workspace as fp8 tiles (64 rows of D bytes, swizzled for the operand reads)
     const uint8_t *k8base = QK8 ? p.k8 + ((int64_t)b * p.hkv + g) * p.mkv * (int64_t)(BN * D) : nullptr;
     const int64_t kstep = (int64_t)BN * p.ksn, vstep = VT ? (int64_t)(BN * D) : (int64_t)BN * p.vsn;
-    // K_t, whose first row is at `src`, into the ring slot at LDS byte address dst
+    // Requests of a tile: bytes of K_t and V_t of this wave's share that exist (0: block t lies behind the share's
+    // last), and the copies in pieces, one unit of this wave each.  Every stage requests a K tile, existing or not, so
+    // that the counts that the waits rely on are the same everywhere.
+    const bool last_partial = n_own > 0 && glob(n_own - 1) == partial_blk;
+    const uint32_t k_last = last_partial && !QK8 ? row_bytes<D>(partial_rows, (int)p.ksn) : kWholeTile;
+    const uint32_t v_last = last_partial && !VT ? row_bytes<D>(partial_rows, (int)p.vsn) : kWholeTile;      // (workspace tiles are padded already)
+    auto k_exist = [&](int t) { return t < n_own - 1 ? kWholeTile : t == n_own - 1 ? k_last : 0u; };
+    auto v_exist = [&](int t) { return t < n_own - 1 ? kWholeTile : v_last; };
+    const uint32_t k_wave = wave * kPitch16, v_wave = wave * PITCH_V;
+    auto k_unit = [&](auto rc, uint32_t &off, const i32x4 &rsrc, uint32_t slot) { unit_copy_async<decltype(rc)::value, NWS * kPitch16>(off, krep, rsrc, slot + k_wave); };
+    auto v_unit = [&](auto rc, uint32_t &off, const i32x4 &rsrc, uint32_t slot) { unit_copy_async<decltype(rc)::value, NWS * PITCH_V>(off, vrep, rsrc, slot + v_wave); };
+    // whole tiles: K_t, whose first row is at `src`, into the ring slot at LDS byte address dst; V_t into slot t & 1
     auto copy_k_from = [&](const unsigned char *src, int t, uint32_t dst) {
-        if constexpr (QK8) {
-            tile_copy_async<NSTK, NT>(src, koff, krep, dst, wave);                                  // (padded already)
-        } else {
-            if (glob(t) == partial_blk) tile_copy_async_clamped<D, NT, false>(reinterpret_cast<const uint16_t *>(src), (int)p.ksn, partial_rows, dst, wave);
-            else tile_copy_async<NSTK, NT>(src, koff, krep, dst, wave);
-        }
+        const i32x4 rsrc = tile_rsrc(src, k_exist(t));
+        uint32_t off = koff;
+        static_for<NSTK>([&](auto rc) { k_unit(rc, off, rsrc, dst); });
     };
-    // V_t, whose first row is at `src`, into slot t & 1
     auto copy_v_from = [&](const unsigned char *src, int t) {
-        const uint32_t dst = lds_v0 + (uint32_t)(t & 1) * TILE_BYTES;
-        if (!VT && glob(t) == partial_blk) tile_copy_async_clamped<D, NT, true>(reinterpret_cast<const uint16_t *>(src), (int)p.vsn, partial_rows, dst, wave);
-        else tile_copy_async<NST, NT>(src, voff, vrep, dst, wave);                                  // (workspace tiles are padded already)
+        const i32x4 rsrc = tile_rsrc(src, v_exist(t));
+        uint32_t off = voff;
+        static_for<NST>([&](auto rc) { v_unit(rc, off, rsrc, lds_v0 + (uint32_t)(t & 1) * VSLOT); });
     };
     const unsigned char *const k_bytes = QK8 ? reinterpret_cast<const unsigned char *>(k8base) : reinterpret_cast<const unsigned char *>(kbase) + ksel * kstep * 2;
     const unsigned char *const v_bytes = reinterpret_cast<const unsigned char *>(vbase) + ksel * vstep * 2;
@@ -180,42 +187,33 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     auto copy_k = [&](int t, uint32_t dst) { copy_k_from(k_bytes + t * kstep_b, t, dst); };
     auto copy_v = [&](int t) { copy_v_from(v_bytes + t * vstep_b, t); };
 
-    // Operand gather addresses (bytes inside a tile slot).
-    // K (A operand of S^T): lane reads key row 32*kb + l32, chunk (2s + hh) ^ swz_k(row).  The row
-    // swizzle does not depend on kb (32 is a multiple of its period) and 2s only occupies chunk
-    // bits 1.., so  addr(s, kb) = (ka_base ^ (s << 5)) + kb * 32 * ROW_BYTES.
-    // QK8: the tile holds fp8, 64 rows of 128 bytes, chunk index XOR-ed with (row >> 1) & 7; a lane
-    // reads row 32*kb + l32, head-dim bytes 64s + 32hh .. +31 as two b128 (chunks 4s + 2hh + {0, 1}):
-    // addr(s, kb, e) = (ka_base ^ (s << 6) ^ (e << 4)) + kb * 32 * 128.
-    const uint32_t ka_base = QK8 ? (uint32_t)(l32 * 128 + (((2 * hh) ^ ((l32 >> 1) & 7)) << 4))
-                                 : (uint32_t)(l32 * ROW_BYTES + ((hh ^ swz_k<D>(l32)) << 4));
+    // Operand gather addresses: bytes inside a tile slot, a base per lane plus constants (see the tile layout).
+    // K (A operand of S^T): lane reads key row 32*kb + l32, chunk 2s + hh:  ka_base + 512 kb + 32 s.
+    // QK8: rows of 128 bytes; lane reads row 32*kb + l32, head-dim bytes 64s + 32hh .. +31 as two b128:
+    // ka_base + 512 kb + 64 s + {0, 16}.
+    constexpr int UK = QK8 ? 8 : D / 8;                  // units of a K tile
+    const uint32_t ka_base = (uint32_t)((l32 % UK) * kPitch16 + (l32 / UK) * (QK8 ? 128 : ROW_BYTES) + (QK8 ? 32 : 16) * hh);
     // V (A operand of O^T, transposing read of 4 keys x 16 head-dim columns per 16 lanes): lane
     // reads row 16u + 4hh + (L >> 2) (+8 for the second half), 8 bytes.  Which head-dim column an
     // operand row stands for is free (it only permutes the rows of O^T, undone at the final
     // store): at D = 128 operand rows 0-15 of block x are columns 16x .. 16x+15 and rows 16-31 are
     // columns 64+16x .., which puts the two 16-lane groups of a read into different bank halves;
-    // at D = 64 rows 0-31 are columns 32x .. 32x+31.  The row swizzle has period 8 rows, so it does
-    // not depend on u or the +8, and x occupies chunk bits the swizzle only XORs, so
-    // addr(u, x, half) = (va_base ^ (x << XSH)) + (16u + 8*half) * ROW_BYTES.
+    // at D = 64 rows 0-31 are columns 32x .. 32x+31:
+    // va_base + 256 u + 2 X_COLS x + {0, V_HALF}.
     constexpr int G16_COLS = (D == 128) ? 64 : 16;       // column distance of the two 16-lane groups
     constexpr int X_COLS = (D == 128) ? 16 : 32;         // column step of x
-    constexpr int XSH = (D == 128) ? 5 : 6;              // log2(X_COLS * 2 bytes)
+    constexpr int V_HALF = (D == 128) ? 8 * v_pitch(D) : ROW_BYTES;   // eight rows further
     const int L = lane & 15, g16 = (lane >> 4) & 1;
-    const int vrow = 4 * hh + (L >> 2);
-    const int vcol = G16_COLS * g16 + 4 * (L & 3);
     // VT: the tile holds V^T, D rows of 64 keys (128 bytes), the keys of every 16-key step ordered
-    // so that the 8 keys a lane multiplies are contiguous, the 16-byte chunk index XOR-ed with
-    // (row >> 1) & 7.  Lane reads row 32x + l32, chunk 2u + hh, as one b128:
-    // addr(u, x) = (va_base ^ (u << 5)) + x * 32 * 128 -- conflict-free (16 lanes hit 16 distinct
-    // (row parity, chunk) slots), and at twice the LDS rate of the transposing reads.
-    const uint32_t va_base = VT ? (uint32_t)(l32 * 128 + ((hh ^ ((l32 >> 1) & 7)) << 4))
-                                : (uint32_t)(vrow * ROW_BYTES + (((vcol >> 3) ^ swz_v<D>(vrow)) << 4) + ((vcol >> 2) & 1) * 8);
+    // so that the 8 keys a lane multiplies are contiguous.  Lane reads row 32x + l32, chunk 2u + hh, as one b128,
+    // va_base + 256 x + 32 u: at about four times the LDS rate of the transposing reads.
+    const uint32_t va_base = VT ? (uint32_t)((l32 % 16) * kPitch16 + (l32 / 16) * 128 + 16 * hh)
+                                : (uint32_t)((4 * hh + (L >> 2)) * v_pitch(D) + 2 * G16_COLS * g16 + 8 * (L & 3));
 
     // All K tiles the ring holds are requested before anything else, and what follows block 0 (V_0, K_{R-1}) is left
     // in flight for the first stage: one trip to memory before the pipeline starts instead of two.
 #pragma unroll
-    for (int t = 0; t < KR; ++t)
-        if (t < n_own) copy_k(t, lds_k0 + (uint32_t)t * TILE_BYTES);
+    for (int t = 0; t < KR; ++t) copy_k(t, lds_k0 + (uint32_t)t * KSLOT);
 
     // Q_i^T as the B operand: lane holds query (32*wrow + l32), head-dim slice 16s + 8hh .. +7
     // (QK8: slice 64s + 32hh .. +31, rounded to fp8 here, once)
@@ -275,23 +273,21 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     auto khalf = [](int n) { return HALVES ? n / KSQ : n & 1; };
     // K operand n (k-step kst(n), 32-key half khalf(n)) of the tile at LDS byte address kaddr (+ka_base)
     auto k_operand = [&](uint32_t kaddr, int n) {
-        const int st = kst(n), kb = khalf(n);
         if constexpr (QK8) {
-            const uint32_t a_s = (kaddr ^ (uint32_t)(st << 6)) + kb * 32 * 128;
-            const i32x4 lo = *LDS_PTR(const i32x4, a_s);
-            const i32x4 hi = *LDS_PTR(const i32x4, a_s ^ 16u);
+            const uint32_t at = kaddr + (uint32_t)(512 * khalf(n) + 64 * kst(n));
+            const i32x4 lo = *LDS_PTR(const i32x4, at);
+            const i32x4 hi = *LDS_PTR(const i32x4, at + 16u);
             return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         } else {
-            const uint32_t a_s = kaddr ^ (uint32_t)(st << 5);
-            return *LDS_PTR(const bf16x8, a_s + kb * 32 * ROW_BYTES);
+            return *LDS_PTR(const bf16x8, kaddr + (uint32_t)(512 * khalf(n) + 32 * kst(n)));
         }
     };
-    
+
     constexpr int PD = 4;            // LDS operand reads are issued PD MFMAs ahead of their use (3 to 6 measure within 1 %)
     // ... of the score operands: the fp8 ones are twice as wide and four in all; with three waves to a SIMD four of them
     // are more than the 168 registers hold, and what is spilled comes back inside the loop behind a wait for every copy
     // in flight (8K tokens, 32 heads of width 64, half skip: 256 us with four, 233 with three, 230 with two).
-    constexpr int PDK = QK8 || (!CALIB && min_waves(D, NW, KSP * (KR + VR) * TILE_BYTES) == 3) ? 2 : PD;
+    constexpr int PDK = QK8 || (!CALIB && min_waves(D, NW, KSP * SHARE) == 3) ? 2 : PD;
     // The first PDK score operands of a block are read one phase early (at the end of the previous
     // stage, behind its last MFMAs), so that the score MFMAs do not start with an LDS round trip.
     kop_t kpre[PDK];
@@ -409,13 +405,13 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // hoisted in front of the PV MFMAs, where it would wait for the LDS read), and made scalar, so that the
     // branches on them are uniform.
     auto decide = [&](ScoreTile &t, const uint32_t (&flags)[HP]) {
-        bool own_head = false, any = false;
+        uint32_t own_head = 0, any = 0;
 #pragma unroll
         for (int x = 0; x < HP; ++x) {
             uint32_t f = flags[x];
             asm volatile("" : "+v"(f));
-            const bool kx = __builtin_amdgcn_readfirstlane((int)f) != 0;
-            any = any || kx;
+            const uint32_t kx = (uint32_t)__builtin_amdgcn_readfirstlane((int)f);
+            any |= kx;
             own_head = hsel == x ? kx : own_head;
         }
         t.keep = own_head;
@@ -423,11 +419,12 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     };
 
     // statistics of block j: decision of this wave's head, and its maximum if asked for
-    auto record = [&](bool keep, int jl, auto fast_tag) {
+    auto record = [&](uint32_t keep, int jl, auto fast_tag) {
         constexpr bool FAST = decltype(fast_tag)::value;
         const int j = glob(jl);
-        n_skipped += keep ? 0 : 1;
-        mask_word |= (keep ? 0u : 1u) << (j & 31);
+        const uint32_t skipped = keep == 0u ? 1u : 0u;
+        n_skipped += skipped;
+        mask_word |= skipped << (j & 31);
         if (CALIB || !FAST) {
             if (p.block_max && stat_lane) {
                 float bmax = NAN;
@@ -454,15 +451,22 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // leave both alone.  (A maximum that follows lazily would save most of the other rescales, 3 % on an 8K
     // prompt, but costs precision: against the row's own maximum the largest probabilities sit just below a power
     // of two, where rounding them to 16 bits is most exact.  Error against 64 bits 0.00199 -> 0.00214.)
+    // In two pieces and without a branch; `gate` is 0, or -inf to leave everything as it is.
+    auto softmax_max = [&](ScoreTile &t, float gate) {
+        const float mb = HP > 1 ? fmaf(t.mx, p.scale_log2, gate) : t.mx * p.scale_log2;
+        const bool grown = mb > m_run;
+        t.resc = __builtin_amdgcn_ballot_w64(grown);
+        const float m_new = grown ? mb : m_run;
+        t.alpha = m_run - m_new;
+        m_run = m_new;
+    };
+    auto softmax_alpha = [&](ScoreTile &t) {
+        t.alpha = __builtin_amdgcn_exp2f(t.alpha);
+        l_run *= t.alpha;
+    };
     auto softmax_begin = [&](ScoreTile &t) {
-        const float mb = t.mx * p.scale_log2;
-        t.resc = __builtin_amdgcn_ballot_w64(mb > m_run) != 0ull;
-        if (t.resc) {
-            const float m_new = fmaxf(m_run, mb);
-            t.alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-            l_run *= t.alpha;
-            m_run = m_new;
-        }
+        softmax_max(t, 0.f);
+        softmax_alpha(t);
     };
     auto softmax_exp = [&](ScoreTile &t, bf16x8 (&pb)[4]) {
         float psum = 0.f;
@@ -487,7 +491,6 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         kop_t a[NQK + PDK];
 #pragma unroll
         for (int n = 0; n < PDK; ++n) a[n] = kpre[n];
-        float psum0 = 0.f, psum1 = 0.f;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -501,9 +504,6 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
             for (int t = 0; t < EPM; t += 2) {
                 const int idx = n * EPM + t;
                 const bf16x2 pp = {(el)ex[t], (el)ex[t + 1]};
-                // row sum of the rounded values (the ones the second MFMA multiplies): p0 + p1 + acc
-                if (t & 2) psum1 = pair_sum(pp, psum1);
-                else psum0 = pair_sum(pp, psum0);
                 pb[idx >> 3][idx & 7] = pp[0];
                 pb[idx >> 3][(idx & 7) + 1] = pp[1];
             }
@@ -525,7 +525,23 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
             __builtin_amdgcn_sched_barrier(0);
         }
         pack(NQK - 1);
-        l_run += psum0 + psum1;
+    };
+    // Row sums of the rounded probabilities (the values the second MFMA multiplies).  The dot instructions run on the
+    // matrix pipe: measured beside 32x32x16 MFMAs, each run of them stops the pipe for 12 cycles and 4 per instruction,
+    // and a chain on one accumulator takes 8 per instruction.  So all sixteen together, on two accumulators, at a place
+    // where the pipe stands still anyway: behind the barrier, while the first V operands travel.
+    auto row_sum = [&](bf16x8 (&pb)[4]) {
+        asm volatile("" : "+v"(pb[0]), "+v"(pb[1]), "+v"(pb[2]), "+v"(pb[3]));
+        float ps[2] = {0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int t = 0; t < 8; t += 2) {
+                const bf16x2 pp = {pb[u][t], pb[u][t + 1]};
+                ps[(t >> 1) & 1] = pair_sum(pp, ps[(t >> 1) & 1]);
+            }
+        l_run += ps[0] + ps[1];
+        asm volatile("" : "+v"(l_run));
     };
 
     // O^T += V^T P^T for the V tile at LDS byte address `vt`; operand n = (k-step u = n / DB,
@@ -534,38 +550,45 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // happen soon after the barrier goes there in small pieces, beside the matrix pipe instead of in
     // front of it
     constexpr int NPV = 4 * DB;
-    auto pv = [&](const ScoreTile &t, const bf16x8 (&pb)[4], uint32_t vt, auto hook) {
-        const uint32_t vaddr = vt + va_base;
-        auto v_operand = [&](int n) {
-            const int u = n / DB, x = n % DB;
-            if constexpr (VT) return *LDS_PTR(const bf16x8, (vaddr ^ (uint32_t)(u << 5)) + x * 32 * 128);
-            const uint32_t a_x = (vaddr ^ (uint32_t)(x << XSH)) + u * 16 * ROW_BYTES;
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a_x));
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a_x + 8 * ROW_BYTES));
-            const s16x8 av = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            return __builtin_bit_cast(bf16x8, av);
-        };
-        bf16x8 a[NPV + PD];
+    auto v_operand = [&](uint32_t vaddr, int n) {
+        const int u = n / DB, x = n % DB;
+        if constexpr (VT) return *LDS_PTR(const bf16x8, vaddr + (uint32_t)(256 * x + 32 * u));
+        const uint32_t at = vaddr + (uint32_t)(256 * u + 2 * X_COLS * x);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, at));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, at + V_HALF));
+        const s16x8 av = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        return __builtin_bit_cast(bf16x8, av);
+    };
+    typedef bf16x8 vops_t[NPV + PD];
+    auto pv_reads = [&](vops_t &a, uint32_t vaddr) {
 #pragma unroll
-        for (int n = 0; n < PD; ++n) a[n] = v_operand(n);
+        for (int n = 0; n < PD; ++n) a[n] = v_operand(vaddr, n);
         __builtin_amdgcn_sched_barrier(0);
-        static_for<NPV>([&](auto nc) {
-            constexpr int n = decltype(nc)::value;
-            if constexpr (n + PD < NPV) a[n + PD] = v_operand(n + PD);
-            if constexpr (n < DB) {                   // the running maximum has grown: O^T follows, a block of it at a time
-                if (t.resc) {
+    };
+    auto pv_mfma = [&](auto nc, const ScoreTile &t, const bf16x8 (&pb)[4], vops_t &a, uint32_t vaddr, auto rescale) {
+        constexpr int n = decltype(nc)::value;
+        if constexpr (n + PD < NPV) a[n + PD] = v_operand(vaddr, n + PD);
+        if constexpr (decltype(rescale)::value) {             // the running maximum has grown: O^T follows, a block of it at a time
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) oacc[n][e] *= t.alpha;
-                }
-            }
-            oacc[n % DB] = mfma16(a[n], pb[n / DB], oacc[n % DB]);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int e = 0; e < 16; ++e) oacc[n][e] *= t.alpha;
+        }
+        oacc[n % DB] = mfma16(a[n], pb[n / DB], oacc[n % DB]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the first DB MFMAs, one for each block of O^T
+    auto pv_head = [&](const ScoreTile &t, const bf16x8 (&pb)[4], vops_t &a, uint32_t vaddr) {
+        if (t.resc != 0) static_for<DB>([&](auto nc) { pv_mfma(nc, t, pb, a, vaddr, std::true_type{}); });
+        if (opaque(t.resc) == 0) static_for<DB>([&](auto nc) { pv_mfma(nc, t, pb, a, vaddr, std::false_type{}); });
+    };
+    auto pv_tail = [&](const ScoreTile &t, const bf16x8 (&pb)[4], vops_t &a, uint32_t vaddr, auto hook) {
+        static_range<DB, NPV>([&](auto nc) {
+            pv_mfma(nc, t, pb, a, vaddr, std::false_type{});
             hook(nc);
             __builtin_amdgcn_sched_barrier(0);
         });
     };
 
-    uint32_t kring = (uint32_t)(1 % KR) * TILE_BYTES;     // ring offset of the K slot the next stage reads
+    uint32_t kring = (uint32_t)(1 % KR) * KSLOT;     // ring offset of the K slot the next stage reads
     // sources of the copies a stage requests, advanced by one block per stage: K_{j+R} and V_{j+1}
     const unsigned char *k_ahead = k_bytes + R * kstep_b;
     const unsigned char *v_ahead = v_bytes + vstep_b;
@@ -578,15 +601,15 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     auto stage = [&](ScoreTile &cur, ScoreTile &nxt, int j, auto fast_tag) {
         constexpr bool FAST = decltype(fast_tag)::value;
         bf16x8 pb[4];
-        const bool do_pv = !CALIB && cur.keep;
+        const uint32_t kept = CALIB ? 0u : opaque(cur.keep);
         // slot of K_{j+1}; K_{j+R} is requested into the same slot once block j+1 has left it
         // (R = KR + 1), so one ring position per stage is all the bookkeeping there is
         const uint32_t kt_next = lds_k0 + kring;
-        kring = (kring + TILE_BYTES == KR * TILE_BYTES) ? 0u : kring + TILE_BYTES;
+        kring = (kring + KSLOT == KR * KSLOT) ? 0u : kring + KSLOT;
         const unsigned char *const k_src = k_ahead, *const v_src = v_ahead;
         k_ahead += kstep_b;
         v_ahead += vstep_b;
-        if (do_pv) {
+        if (kept != 0u) {
             fused_exp_qk(cur, nxt, kt_next, pb);
         } else {
             qk_mfma(nxt, kt_next);
@@ -594,8 +617,8 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         reduce_scores(nxt, j + 1, fast_tag);
         // copies that must have landed before the barrier: V_j (if requested) and K_{j+2}; every
         // younger request (K_{j+3} .. K_{j+R-1}, issued after V_j) may stay in flight
-        if (R >= 4 && j - 1 + R < n_own) {
-            if (!CALIB && cur.any_keep) wait_vmcnt<NSTK>();
+        if constexpr (R >= 4) {
+            if (!CALIB && cur.any_keep != 0u) wait_vmcnt<NSTK>();
             else wait_vmcnt<(R >= 4 ? NSTK * (R - 3) : 0)>();
         } else {
             wait_vmcnt<0>();
@@ -610,48 +633,73 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         // PV MFMAs a few instructions at a time.
         auto la_decide = [&]() {
             if constexpr (!CALIB) decide(nxt, flags);
-            else nxt.keep = true;
+            else nxt.keep = 1u;
         };
         auto la_stats = [&]() {
             record(nxt.keep, j + 1, fast_tag);
         };
-        auto la_vcopy = [&]() {
-            if (!CALIB && nxt.any_keep) {
-                if constexpr (FAST) tile_copy_async<NST, NT>(v_src, voff, vrep, lds_v0 + (uint32_t)((j + 1) & 1) * TILE_BYTES, wave);
-                else copy_v_from(v_src, j + 1);           // a gateable block is never the partial one
-            }
-        };
-        auto la_kcopy = [&]() {
-            if (j + R < n_own) copy_k_from(k_src, j + R, kt_next);
-        };
-        auto la_softmax = [&]() {                        // running max and rescale factor, off the critical path
-            if (!CALIB && nxt.keep) {
-                if constexpr (FAST) nxt.mx = pair_max(nxt.mx);
-                softmax_begin(nxt);
-            }
-        };
-        if (do_pv) {
+        if (kept != 0u) {
             if constexpr (!CALIB) {
-                constexpr int HS = NPV / 8;               // MFMAs from one piece to the next
-                pv(cur, pb, lds_v0 + (uint32_t)(j & 1) * TILE_BYTES, [&](auto nc) {
-                    constexpr int n = decltype(nc)::value;
-                    if constexpr (n == HS) la_decide();
-                    if constexpr (n == 2 * HS) la_stats();
-                    if constexpr (n == 3 * HS) la_vcopy();
-                    if constexpr (n == 4 * HS) la_kcopy();
-                    if constexpr (n == 5 * HS) la_softmax();
-                    if constexpr (n == NPV - 2) prefetch_k(lds_k0 + kring);   // K_{j+2}: landed and visible since the barrier
-                });
+                const uint32_t vaddr = lds_v0 + (uint32_t)(j & 1) * VSLOT + va_base;
+                vops_t a;
+                pv_reads(a, vaddr);
+                row_sum(pb);
+                __builtin_amdgcn_sched_barrier(0);
+                pv_head(cur, pb, a, vaddr);
+                la_decide();
+                const i32x4 krs = tile_rsrc(k_src, k_exist(j + R));
+                // The copies are spread over the MFMAs: a run of them fills the queue in front of the memory pipe, and the
+                // wave then waits at the next one (40 to 60 cycles each) instead of issuing MFMAs.
+                constexpr int SLOTS = NPV - 2 - DB;           // hooks before the last operand reads
+                if (nxt.any_keep != 0u) {
+                    const i32x4 vrs = tile_rsrc(v_src, FAST ? kWholeTile : v_exist(j + 1));      // (a gateable block is never the partial one)
+                    uint32_t ko = koff, vo = voff;
+                    constexpr int PER = (NST + NSTK + SLOTS - 1) / SLOTS;
+                    pv_tail(cur, pb, a, vaddr, [&](auto nc) {
+                        constexpr int s = decltype(nc)::value - DB;
+                        static_range<s * PER, (s + 1) * PER>([&](auto cc) {
+                            constexpr int c = decltype(cc)::value;
+                            if constexpr (c < NST) v_unit(cc, vo, vrs, lds_v0 + (uint32_t)((j + 1) & 1) * VSLOT);
+                            else if constexpr (c < NST + NSTK) k_unit(std::integral_constant<int, c - NST>{}, ko, krs, kt_next);
+                        });
+                        if constexpr (s == SLOTS / 2 - 1) {
+                            if constexpr (FAST) nxt.mx = pair_max(nxt.mx);
+                        }
+                        if constexpr (s == SLOTS / 2) softmax_max(nxt, HP > 1 && nxt.keep == 0u ? -INFINITY : 0.f);
+                        if constexpr (s == SLOTS / 2 + 1) softmax_alpha(nxt);
+                        if constexpr (s == SLOTS - 1) la_stats();
+                        if constexpr (s == SLOTS) prefetch_k(lds_k0 + kring);   // K_{j+2}: landed and visible since the barrier
+                    });
+                }
+                if (opaque(nxt.any_keep) == 0u) {
+                    uint32_t ko = koff;
+                    constexpr int PER = (NSTK + SLOTS - 1) / SLOTS;
+                    pv_tail(cur, pb, a, vaddr, [&](auto nc) {
+                        constexpr int s = decltype(nc)::value - DB;
+                        static_range<s * PER, (s + 1) * PER>([&](auto cc) {
+                            if constexpr (decltype(cc)::value < NSTK) k_unit(cc, ko, krs, kt_next);
+                        });
+                        if constexpr (s == SLOTS - 1) la_stats();
+                        if constexpr (s == SLOTS) prefetch_k(lds_k0 + kring);
+                    });
+                }
             }
-        } else {
+        }
+        if (opaque(kept) == 0u) {
             // the operand reads first, so that they travel while the look-ahead is issued (where V is
             // gathered in place the registers do not allow it: there they come last)
             if constexpr (VT || CALIB) prefetch_k(lds_k0 + kring);
             __builtin_amdgcn_sched_barrier(0);
             la_decide();
-            la_softmax();
-            la_vcopy();
-            la_kcopy();
+            if constexpr (!CALIB) {
+                if (nxt.any_keep != 0u) {
+                    if constexpr (FAST) nxt.mx = pair_max(nxt.mx);
+                    softmax_max(nxt, HP > 1 && nxt.keep == 0u ? -INFINITY : 0.f);
+                    softmax_alpha(nxt);
+                    copy_v_from(v_src, j + 1);
+                }
+            }
+            copy_k_from(k_src, j + R, kt_next);
             la_stats();
             if constexpr (!(VT || CALIB)) prefetch_k(lds_k0 + kring);
         }
@@ -662,12 +710,16 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     auto last_stage = [&](ScoreTile &cur, int j) {
         if constexpr (!CALIB) {
             bf16x8 pb[4];
-            if (cur.keep) {
-                softmax_exp(cur, pb);
-            }
+            if (cur.keep != 0u) softmax_exp(cur, pb);
             wait_vmcnt<0>();
             wg_barrier();
-            if (cur.keep) pv(cur, pb, lds_v0 + (uint32_t)(j & 1) * TILE_BYTES, [](auto) {});
+            if (cur.keep != 0u) {
+                const uint32_t vaddr = lds_v0 + (uint32_t)(j & 1) * VSLOT + va_base;
+                vops_t a;
+                pv_reads(a, vaddr);
+                pv_head(cur, pb, a, vaddr);
+                pv_tail(cur, pb, a, vaddr, [](auto) {});
+            }
         }
     };
 
@@ -684,13 +736,13 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         uint32_t flags[HP];
         read_flags(flags, 0);
         decide(ta, flags);
-        if (KSP > 1 && n_own == 0) ta.keep = ta.any_keep = false;      // a share without blocks
-        if (ta.any_keep) copy_v(0);
-        if (ta.keep) softmax_begin(ta);
+        if (KSP > 1 && n_own == 0) ta.keep = ta.any_keep = 0u;         // a share without blocks
+        if (ta.any_keep != 0u) copy_v(0);
+        if (ta.keep != 0u) softmax_begin(ta);
     } else {
-        ta.keep = true;
+        ta.keep = 1u;
     }
-    if (R - 1 < n_own) copy_k(R - 1, lds_k0);              // the slot block 0 has just left
+    copy_k(R - 1, lds_k0);                                 // the slot block 0 has just left
     if (KSP == 1 || n_own > 0) record(ta.keep, 0, std::false_type{});
 
     // main loop, two stages per trip.  A pair runs the mask-free stages when both of its
@@ -719,6 +771,8 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         last_stage(ta, j);
     }
 
+    if constexpr (CALIB) wait_vmcnt<0>();                 // (the last requests: nothing is in flight when the LDS is given back)
+
     // ---- statistics ------------------------------------------------------------------------
     const int htid = tid - hsel * NWH * 64;               // thread index within the head's waves
     if (p.block_max && ksel == 0)
@@ -742,6 +796,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         constexpr int PER_WAVE = 64 * (16 * DB + 2);      // floats
         static_assert((KSP - 1) * NWH * HP * PER_WAVE * 4 <= (int)sizeof(lds_raw), "the tile slots hold the shares");
         float *const part = reinterpret_cast<float *>(lds_raw);
+        wait_vmcnt<0>();                                  // (the last requests of a share without blocks)
         wg_barrier();                                     // nobody reads the slots any more; the mask words are complete
         if (p.skip_mask && ksel == 0)
             for (int w = htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = lds_mask[hsel][w];
@@ -779,10 +834,11 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         // The wave's 32 rows go through LDS, so that a store instruction writes whole rows instead of 16 bytes of each
         // (32 rows of 16 bytes at a time the epilogue took 2.5 us of a workgroup at 128 x 128, all of it waiting for
         // addresses).  Their place is free: the K ring, which nobody reads after the barrier of the last stage, or the
-        // share this wave has just merged.  16-byte chunks are XOR-ed with the row as in the K tiles.
-        static_assert(KSP > 1 || NWH * HP * 32 * ROW_BYTES <= KR * TILE_BYTES, "the K ring holds the output rows");
+        // share this wave has just merged.  16-byte chunks are XOR-ed with the row, which spreads them over the banks.
+        static_assert(KSP > 1 || NWH * HP * 32 * ROW_BYTES <= KR * KSLOT, "the K ring holds the output rows");
         const uint32_t o_lds = KSP > 1 ? (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw) + wave * (64 * (16 * DB + 2) * 4)
                                        : lds_k0 + wave * (32 * ROW_BYTES);
+        auto swz_o = [](int row) { return D == 128 ? row & 15 : (row >> 1) & 7; };
         const uint32_t o_row = o_lds + l32 * ROW_BYTES + 8 * hh;
         asm volatile("" ::: "memory");              // (a merged share has been read; one wave's LDS accesses complete in order)
 #pragma unroll
@@ -795,7 +851,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
                 bf16x4 o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = (el)(oacc[x][4 * e4 + e] * inv);
-                *LDS_PTR(bf16x4, o_row + (((d0 >> 3) ^ swz_k<D>(l32)) << 4)) = o;
+                *LDS_PTR(bf16x4, o_row + (((d0 >> 3) ^ swz_o(l32)) << 4)) = o;
             }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_wave_barrier();
@@ -803,7 +859,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
 #pragma unroll
         for (int it = 0; it < 32 * CPR / 64; ++it) {
             const int row = it * (64 / CPR) + lane / CPR, c = lane % CPR;
-            const i32x4 o = *LDS_PTR(const i32x4, o_lds + row * ROW_BYTES + ((c ^ swz_k<D>(row)) << 4));
+            const i32x4 o = *LDS_PTR(const i32x4, o_lds + row * ROW_BYTES + ((c ^ swz_o(row)) << 4));
             const int token = (int)row0 + wrow * 32 + row;
             if (token < n_tok) *reinterpret_cast<i32x4 *>(op + (int64_t)token * p.osn + 8 * c) = o;   // (padding rows of the last tile are not stored)
         }
@@ -819,8 +875,8 @@ static __global__ void zero_counts_kernel(unsigned long long *c, int n)
 // V -> workspace, once per forward call: for every (batch, KV head, 64-key block) the tile V_j^T in
 // exactly the byte order the forward kernel wants in LDS (see its operand addresses): D rows of 64
 // keys; inside a 16-key step the keys are ordered 0-3, 8-11, 4-7, 12-15 (the 8 keys one lane of the
-// second MFMA multiplies are then 16 contiguous bytes); the 16-byte chunk index is XOR-ed with
-// (row >> 1) & 7.  Rows at and beyond the sequence end repeat the last token (Section 4.3), so the
+// second MFMA multiplies are then 16 contiguous bytes); unit r of 1024 bytes holds the rows r, r + 16, ... r + 112.
+// Rows at and beyond the sequence end repeat the last token (Section 4.3), so the
 // tile of a partial block holds finite values everywhere; blocks that lie entirely beyond the end
 // are never read and are not written.  One workgroup per tile, through LDS.
 static __global__ void __launch_bounds__(256) transpose_v_kernel(const FwdParams p)
@@ -844,8 +900,8 @@ static __global__ void __launch_bounds__(256) transpose_v_kernel(const FwdParams
     __syncthreads();
     uint16_t *dst = p.vt + (((int64_t)b * p.hkv + g) * p.mkv + j) * (int64_t)(BN * D);
     for (int sigma = tid; sigma < D * 8; sigma += 256) {
-        const int d = sigma >> 3, cphys = sigma & 7;
-        const int c = cphys ^ ((d >> 1) & 7);        // logical chunk: 16-key step c >> 1, lane half c & 1
+        const int d = (sigma >> 6) + 16 * ((sigma >> 3) & 7);
+        const int c = sigma & 7;                     // chunk: 16-key step c >> 1, lane half c & 1
         const int u = c >> 1, hh = c & 1;
         uint16_t w[8];
 #pragma unroll
@@ -859,7 +915,7 @@ static __global__ void __launch_bounds__(256) transpose_v_kernel(const FwdParams
 
 // K -> workspace as fp8 (e4m3, round to nearest even), once per call, for the fp8 score product: for
 // every (batch, KV head, 64-key block) a tile of 64 rows x 128 bytes in the byte order the forward
-// kernel wants in LDS (16-byte chunk index XOR-ed with (row >> 1) & 7).  Rows at and beyond the
+// kernel wants in LDS (unit r of 1024 bytes holds the rows r, r + 8, ... r + 56).  Rows at and beyond the
 // sequence end repeat the last token (Section 4.3).  head_dim 128 only.
 template <bool F16>
 __global__ void __launch_bounds__(256) quantize_k_kernel(const FwdParams p)
@@ -873,8 +929,8 @@ __global__ void __launch_bounds__(256) quantize_k_kernel(const FwdParams p)
     const uint16_t *src = p.k + (int64_t)b * p.ksb + (int64_t)g * p.ksh;
     uint8_t *dst = p.k8 + (((int64_t)b * p.hkv + g) * p.mkv + j) * (int64_t)(BN * D);
     for (int sigma = tid; sigma < BN * 8; sigma += 256) {
-        const int row = sigma >> 3, cphys = sigma & 7;
-        const int c = cphys ^ ((row >> 1) & 7);               // head-dim elements 16c .. 16c + 15
+        const int row = (sigma >> 6) + 8 * ((sigma >> 3) & 7);
+        const int c = sigma & 7;                              // head-dim elements 16c .. 16c + 15
         const int tok = min(j * BN + row, n_tok - 1);
         const uint16_t *e = src + (int64_t)tok * p.ksn + 16 * c;
         i32x4 o;
