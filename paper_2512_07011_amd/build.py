@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbsfa.so")
 # translation units: (source, extra flags).  bsfa_fwd.hip is compiled once per group of kernel instantiations.
-FWD_PARTS = 9
+FWD_PARTS = 11
 UNITS = [("bsfa_fwd.hip", ["-DBSFA_PART=%d" % i]) for i in range(FWD_PARTS)] + \
         [(s, []) for s in ("bsfa_select.hip", "bsfa_probe.hip", "bsfa_api.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

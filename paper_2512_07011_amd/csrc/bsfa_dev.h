@@ -189,11 +189,11 @@ template <int LO, int HI, class F> __device__ __forceinline__ void static_range(
     static_for<HI - LO>([&](auto n) { f(std::integral_constant<int, LO + decltype(n)::value>{}); });
 }
 
-// Work decomposition: a work item is (batch b, KV head, group of HP query heads, query tile i).
+// Work decomposition: a work item is (batch b, KV head, group of HP query heads, QT query tiles from i on).
 // With at least 8 (batch, KV head) pairs the pair is chosen by the low three bits of the
 // workgroup id, which is the XCD the hardware dispatches the group to, so that all groups
 // streaming one K/V sequence share one L2.  Heavy (late) query tiles first.
-template <int HP>
+template <int HP, int QT>
 __device__ __forceinline__ bool decode_work(const FwdParams &p, uint32_t w, int &b, int &g, int &h0, int &i)
 {
     const int pairs = p.batch * p.hkv;
@@ -215,7 +215,7 @@ __device__ __forceinline__ bool decode_work(const FwdParams &p, uint32_t w, int 
     b = (int)p.div_hkv.of((uint32_t)g);
     g -= b * p.hkv;
     h0 = g * p.group + (int)(rest - pl * (uint32_t)gsub) * HP;
-    i = p.mq - 1 - (int)idesc;
+    i = ((p.mq + QT - 1) / QT - 1 - (int)idesc) * QT;
     return true;
 }
 

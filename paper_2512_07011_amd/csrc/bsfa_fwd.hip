@@ -1,7 +1,8 @@
 // Block-Sparse FlashAttention forward kernel for gfx950 (MI355X), wave64, bf16 or fp16 MFMA.
 //
-// One workgroup = one query tile Q_i (B_M = 32 * NWH rows, NWH waves of 32 rows) of HP query heads
-// that share a KV head (GQA); it walks the reachable key blocks j in ascending order (Algorithm 1).
+// One workgroup = QT adjacent query tiles Q_i (B_M = 32 * NWH rows, NWH waves of 32 rows) of HP query heads
+// that share a KV head (GQA); it walks the reachable key blocks j in ascending order (Algorithm 1), each tile of
+// each head with decisions of its own.
 // With KSP > 1 the blocks are dealt to KSP sets of waves, each with a pipeline of its own, whose
 // results are put together at the end (small problems: see launch_forward).
 //   S_ij^T = K_j Q_i^T        32x32x16 MFMA, fp32 accumulate                      (Eq. 5)
@@ -31,8 +32,9 @@
 //
 // What bounds it.  Long sequences: the matrix pipe at the clock the card holds under this load (a plain
 // library product reaches 1360 TFLOP/s here, this kernel 1080 to 1150 dense, busy in 57 % of the cycles) and
-// instruction issue (the two waves of a SIMD issue in 81 % of the cycles together, in 91 % with single heads),
-// above all in the stretch between the last score MFMA and the first PV MFMA of a block.  Two workgroups of four waves on a CU
+// the issue of each wave: a stage takes a wave about 2900 cycles for 1024 of MFMA, whether a second one shares its
+// SIMD or not (a vector instruction 4.4 cycles, an exponential 8, a taken branch 30, dependent ones 8), so every
+// instruction in a wave's way counts, above all between the last score MFMA and the first PV MFMA of a block.  Two workgroups of four waves on a CU
 // (HP = 1) run independently and hide that stretch for each other; eight waves that share a K/V stream
 // (HP = 2) all stand at the same barrier, but read half as much from L2 (see launch_forward for the line).
 // Short sequences: the chain of key blocks of the longest tile, about 1.6 us a block.
@@ -61,8 +63,8 @@ constexpr int min_waves(int d, int waves, int lds_bytes)
 constexpr int k_slot_bytes(int d) { return d / 8 * kPitch16; }
 constexpr int v_slot_bytes(int d) { return d / 8 * v_pitch(d); }
 
-template <int D, int NWH, int HP, int KSP, int KR, bool CALIB, bool F16, bool VT, bool QK8>
-__global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * KSP, KSP * (KR * k_slot_bytes(D) + 2 * v_slot_bytes(D)))) bsfa_fwd_kernel(const FwdParams p)
+template <int D, int NWH, int HP, int QT, int KSP, int KR, bool CALIB, bool F16, bool VT, bool QK8>
+__global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * HP * QT * KSP, KSP * (KR * k_slot_bytes(D) + 2 * v_slot_bytes(D)))) bsfa_fwd_kernel(const FwdParams p)
 {
     typedef typename Elem<F16>::T el;                    // element type of Q, K, V, P, O
     typedef typename Elem<F16>::x8 bf16x8;               // (the vector names keep the default type's name)
@@ -70,8 +72,9 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     typedef typename Elem<F16>::x2 bf16x2;
     static_assert(KSP == 1 || (!CALIB && !VT && !QK8), "shares of the key blocks: V in place");
     static_assert(!VT || D == 128, "V from the workspace: head_dim 128");
-    constexpr int NW = NWH * HP * KSP;
-    constexpr int NT = NWH * HP * 64;                    // threads that share one stream of K and V tiles
+    constexpr int TEAMS = HP * QT;                       // (head, query tile) pairs of the workgroup: the NWH waves of one decide together
+    constexpr int NW = NWH * TEAMS * KSP;
+    constexpr int NT = NWH * TEAMS * 64;                  // threads that share one stream of K and V tiles
     constexpr int BM = NWH * 32;
     constexpr int BN = kBlockN;
     constexpr int KS = D / 16;       // MFMA k-steps over the head dim
@@ -93,23 +96,22 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[KSP * SHARE];
     __shared__ float lds_red[2][NW];                                  // the waves' block maxima, where somebody asks for them
     __shared__ __attribute__((aligned(8))) uint8_t lds_flag[2][NW];   // the waves' keep flags
-    __shared__ uint32_t lds_mask[HP][KSP > 1 ? kSplitMaskWords : 1];  // KSP > 1: the tiles' skip masks, put together
+    __shared__ uint32_t lds_mask[TEAMS][KSP > 1 ? kSplitMaskWords : 1];  // KSP > 1: the tiles' skip masks, put together
 
-    int b, g, h0, i;
-    if (!decode_work<HP>(p, blockIdx.x, b, g, h0, i)) return;
+    int b, g, h0, i0;
+    if (!decode_work<HP, QT>(p, blockIdx.x, b, g, h0, i0)) return;
     const int lane = threadIdx.x & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int ksel = KSP > 1 ? wave_all / (NWH * HP) : 0;   // which share of the key blocks: those with j % KSP == ksel
-    const int wave = KSP > 1 ? wave_all % (NWH * HP) : wave_all, tid = wave * 64 + lane;
-    const int hsel = wave / NWH, wrow = wave % NWH;      // which head of the group, which 32-row slice
-    const int team = wave_all / NWH;                     // the NWH waves that decide about a block together
+    const int ksel = KSP > 1 ? wave_all / (NWH * TEAMS) : 0;   // which share of the key blocks: those with j % KSP == ksel
+    const int wave = KSP > 1 ? wave_all % (NWH * TEAMS) : wave_all, tid = wave * 64 + lane;
+    const int tsel = wave / NWH, wrow = wave % NWH;      // which (head, query tile), which 32-row slice of it
+    const int team = wave_all / NWH;                     // ... and of which share: the NWH waves that decide about a block together
     // V slots first: their gather offsets then fit the 16-bit immediate of the LDS reads
     const uint32_t lds_v0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw) + ksel * SHARE;
     const uint32_t lds_k0 = lds_v0 + VR * VSLOT;
     const uint32_t lds_flag0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) uint8_t *)lds_flag);
-    const int h = h0 + hsel;
+    const int h = h0 + tsel / QT, i = i0 + tsel % QT;    // this wave's head and query tile
     const int l32 = lane & 31, hh = lane >> 5;
-    const bool stat_lane = (wrow == 0 && lane == 0);     // one lane per head writes statistics
 
     const int64_t row0 = (int64_t)i * BM;                 // first query row of the tile
     // tokens of this batch element; a sequence that does not fill its last query tile or key
@@ -118,30 +120,39 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // of padding only are not visited (the causal mask hides them from every real row).
     int n_tok = p.seqlen;
     if (p.seqlens) n_tok = min(max(__builtin_amdgcn_readfirstlane(p.seqlens[b]), 0), p.seqlen);
+    const bool real_tile = QT == 1 || row0 < n_tok;       // (with QT > 1 the last tiles of a workgroup may lie beyond the sequence)
+    const bool stat_lane = (wrow == 0 && lane == 0 && real_tile);   // one lane per head and tile writes statistics
     const int64_t stat_row = ((int64_t)b * p.hq + h) * p.mq + i;
-    if (row0 >= n_tok) {                                  // the tile lies beyond the sequence: empty statistics
-        const int htid = tid - hsel * NWH * 64;
-        if (p.block_max)
-            for (int jj = htid; jj < p.mkv; jj += NWH * 64) p.block_max[stat_row * p.mkv + jj] = NAN;
-        if (p.skip_mask)
-            for (int w = htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = 0u;
+    if ((int64_t)i0 * BM >= n_tok) {                      // the tiles lie beyond the sequence: empty statistics
+        const int htid = tid - tsel * NWH * 64;
+        if (i < p.mq && ksel == 0) {
+            if (p.block_max)
+                for (int jj = htid; jj < p.mkv; jj += NWH * 64) p.block_max[stat_row * p.mkv + jj] = NAN;
+            if (p.skip_mask)
+                for (int w = htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = 0u;
+        }
         return;
     }
     const int mkv_tok = (n_tok + BN - 1) / BN;
     const int partial_blk = (n_tok % BN) ? n_tok / BN : -1;   // the block that padding completes, if any
     const int partial_rows = n_tok % BN;
-    const int n_blk = p.causal ? min((int)((row0 + BM + BN - 1) / BN), mkv_tok) : mkv_tok;   // reachable blocks
-    // causal: blocks [0, n_gate) are gateable, [n_gate, n_blk) touch the boundary.
+    // reachable blocks: of this wave's tile, and of the workgroup's tiles together
+    auto reachable = [&](int tile) { return p.causal ? min((int)(((int64_t)tile * BM + BM + BN - 1) / BN), mkv_tok) : mkv_tok; };
+    const int n_tile = real_tile ? reachable(i) : 0, n_blk = QT == 1 ? n_tile : reachable(i0 + QT - 1);
+    // causal: blocks [0, n_gate) are gateable, [n_gate, n_tile) touch the boundary.
     // non-causal: blocks [own_lo, own_hi) overlap the tile's own tokens and bypass the gate.
     const int n_gate = p.causal ? (int)((row0 + 1) / BN) : 0;
     const int own_lo = (int)(row0 / BN), own_hi = (int)((row0 + BM + BN - 1) / BN);
+    // gateable for all tiles of the workgroup: blocks below all_lo and, without the mask, from all_hi on
+    const int all_lo = QT == 1 ? (p.causal ? n_gate : own_lo) : p.causal ? (int)(((int64_t)i0 * BM + 1) / BN) : (int)((int64_t)i0 * BM / BN);
+    const int all_hi = QT == 1 ? own_hi : min((int)(((int64_t)(i0 + QT) * BM + BN - 1) / BN), mkv_tok);
     // Block indices from here on: `j` counts the blocks of this wave's share, glob(j) is the key block it stands
     // for, own(x) is the number of its blocks below key block x.  All the same thing unless KSP > 1.
     auto glob = [&](int jl) { return KSP > 1 ? jl * KSP + ksel : jl; };
     auto own = [&](int x) { return KSP > 1 ? max(0, (x - ksel + KSP - 1) / KSP) : x; };
     const int n_own = own(n_blk), own_max = KSP > 1 ? (n_blk + KSP - 1) / KSP : n_own;
     if constexpr (KSP > 1) {
-        for (int w = threadIdx.x; w < HP * kSplitMaskWords; w += NW * 64) (&lds_mask[0][0])[w] = 0u;   // (a barrier follows before its first use)
+        for (int w = threadIdx.x; w < TEAMS * kSplitMaskWords; w += NW * 64) (&lds_mask[0][0])[w] = 0u;   // (a barrier follows before its first use)
     }
 
     const uint16_t *kbase = p.k + (int64_t)b * p.ksb + (int64_t)g * p.ksh;
@@ -150,6 +161,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
                                : p.v + (int64_t)b * p.vsb + (int64_t)g * p.vsh;
     // threshold of this wave's head; tiles past the calibrated length use its last tile's (Section 4.3)
     const float tau_own = CALIB ? -INFINITY      // the score half takes no decisions
+                          : !real_tile ? NAN     // (keeps nothing)
                                 : p.tau[p.tau_per_tile ? (int64_t)h * p.tau_tiles + min(i, p.tau_tiles - 1) : h];
     // source of this lane's part of a copy's first repetition, and the bytes from one repetition to the next
     const uint32_t koff = QK8 ? (uint32_t)tid * 16u : unit_src_offset<D>(wave, lane, (int)p.ksn);
@@ -351,8 +363,9 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
             return;
         }
         const bool gated = FAST ? true : is_gated(glob(j));
+        const bool there = QT == 1 || FAST || glob(j) < n_tile;   // (another tile of the workgroup may reach further)
         if constexpr (!FAST) {
-            if (p.causal && !gated) {
+            if (p.causal && !gated && there) {
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -368,8 +381,8 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
 #pragma unroll
             for (int e = 0; e < 16; ++e) mx = fmaxf(mx, t.s[kb][e]);
         t.mx = pair_max(mx);
-        bool ge = true;                                       // blocks that bypass the gate are kept
-        if (gated) {
+        bool ge = there;                                      // blocks that bypass the gate are kept
+        if (gated && there) {
             float stat = t.mx, unit = p.scale;                // natural score units (Eq. 5-6)
             if constexpr (!FAST) {
                 // the comparison predicate (Section 3): local row maximum minus the running row maximum
@@ -388,45 +401,46 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     };
 
     // the keep flags of team x of the workgroup for a block of parity par, as published before the last barrier
+    constexpr int FB = NWH * TEAMS;                       // flag bytes of a stream's waves
+    constexpr int FW = FB == 8 ? 2 : 1;                   // ... in words (one access)
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    typedef std::conditional_t<NWH == 4, uint32_t, std::conditional_t<NWH == 2, uint16_t, uint8_t>> flag_t;
-    auto read_team = [&](int x, int par) { return (uint32_t)*LDS_PTR(const flag_t, lds_flag0 + (uint32_t)(par * NW + x * NWH)); };
-    auto read_flags = [&](uint32_t (&flags)[HP], int par) {
-        if constexpr (HP == 2 && NWH == 4) {              // both heads in one read
-            const u32x2 f = *LDS_PTR(const u32x2, lds_flag0 + (uint32_t)(par * NW + ksel * HP * NWH));
+    typedef std::conditional_t<FB == 8, u32x2, std::conditional_t<FB == 4, uint32_t, std::conditional_t<FB == 2, uint16_t, uint8_t>>> flag_t;
+    static_assert(FB == 8 || FB == 4 || FB == 2 || FB == 1, "one access reads the flags of a stream");
+    auto read_flags = [&](uint32_t (&flags)[FW], int par) {
+        const flag_t f = *LDS_PTR(const flag_t, lds_flag0 + (uint32_t)(par * NW + ksel * FB));
+        if constexpr (FW == 2) {
             flags[0] = f[0];
             flags[1] = f[1];
         } else {
-#pragma unroll
-            for (int x = 0; x < HP; ++x) flags[x] = read_team(ksel * HP + x, par);
+            flags[0] = f;
         }
     };
     // Decisions from the read flags.  They are consumed here and not earlier (nothing computed from them may be
     // hoisted in front of the PV MFMAs, where it would wait for the LDS read), and made scalar, so that the
     // branches on them are uniform.
-    auto decide = [&](ScoreTile &t, const uint32_t (&flags)[HP]) {
-        uint32_t own_head = 0, any = 0;
+    auto decide = [&](ScoreTile &t, const uint32_t (&flags)[FW]) {
+        uint32_t w[FW];
 #pragma unroll
-        for (int x = 0; x < HP; ++x) {
+        for (int x = 0; x < FW; ++x) {
             uint32_t f = flags[x];
             asm volatile("" : "+v"(f));
-            const uint32_t kx = (uint32_t)__builtin_amdgcn_readfirstlane((int)f);
-            any |= kx;
-            own_head = hsel == x ? kx : own_head;
+            w[x] = (uint32_t)__builtin_amdgcn_readfirstlane((int)f);
         }
-        t.keep = own_head;
-        t.any_keep = any;
+        constexpr int PER = FW == 2 ? TEAMS / 2 : TEAMS;                // teams of a word
+        const uint32_t own_word = FW == 2 && tsel >= PER ? w[FW - 1] : w[0];
+        t.keep = PER == 1 ? own_word : (own_word >> (8 * NWH * (tsel % PER))) & ((1u << (8 * NWH % 32)) - 1u);
+        t.any_keep = w[0] | w[FW - 1];
     };
 
     // statistics of block j: decision of this wave's head, and its maximum if asked for
     auto record = [&](uint32_t keep, int jl, auto fast_tag) {
         constexpr bool FAST = decltype(fast_tag)::value;
         const int j = glob(jl);
-        const uint32_t skipped = keep == 0u ? 1u : 0u;
+        const uint32_t skipped = keep == 0u && (QT == 1 || FAST || j < n_tile) ? 1u : 0u;
         n_skipped += skipped;
         mask_word |= skipped << (j & 31);
         if (CALIB || !FAST) {
-            if (p.block_max && stat_lane) {
+            if (p.block_max && stat_lane && (QT == 1 || j < n_tile)) {
                 float bmax = NAN;
                 if (FAST || is_gated(j)) {
                     bmax = lds_red[jl & 1][team * NWH];
@@ -436,9 +450,9 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
                 p.block_max[stat_row * p.mkv + j] = bmax;
             }
         }
-        if ((j & 31) > 31 - KSP || j > n_blk - 1 - KSP) {      // the last block of a mask word, or of the tile
-            if (p.skip_mask && stat_lane) {
-                if constexpr (KSP > 1) atomicOr(&lds_mask[hsel][j >> 5], mask_word);
+        if ((j & 31) > 31 - KSP || j > n_blk - 1 - KSP) {      // the last block of a mask word, or of the workgroup's tiles
+            if (p.skip_mask && stat_lane && (QT == 1 || (j & ~31) < n_tile)) {
+                if constexpr (KSP > 1) atomicOr(&lds_mask[tsel][j >> 5], mask_word);
                 else p.skip_mask[stat_row * p.mask_words + (j >> 5)] = mask_word;
             }
             mask_word = 0;
@@ -453,7 +467,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // of two, where rounding them to 16 bits is most exact.  Error against 64 bits 0.00199 -> 0.00214.)
     // In two pieces and without a branch; `gate` is 0, or -inf to leave everything as it is.
     auto softmax_max = [&](ScoreTile &t, float gate) {
-        const float mb = HP > 1 ? fmaf(t.mx, p.scale_log2, gate) : t.mx * p.scale_log2;
+        const float mb = TEAMS > 1 ? fmaf(t.mx, p.scale_log2, gate) : t.mx * p.scale_log2;
         const bool grown = mb > m_run;
         t.resc = __builtin_amdgcn_ballot_w64(grown);
         const float m_new = grown ? mb : m_run;
@@ -595,9 +609,12 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // One pipeline stage: finish block j (`cur`), look ahead to block j+1 (`nxt`).
     // Block j+1 exists (the tile's last block is finished by last_stage).  FAST: it is gateable, so the
     // look-ahead has no mask and fewer conditionals.
-    // PRIO: heads that share a workgroup come out of the barrier together; of a SIMD's two waves the one still in its
-    // PV half goes first (32K tokens half skip 1.2 % faster, 128K 0.9 %, dense even; single heads 1 to 2 % slower with it).
-    constexpr bool PRIO = HP == 2 && NWH == 4 && !CALIB;
+    // PRIO: of a SIMD's two waves the one in its PV half goes first.  Where they come out of the same barrier (heads or
+    // tiles that share a workgroup) or wait for each other in the end (shares) the later half is over sooner: us without /
+    // with, half skip: 32K tokens 5913 / 5825, 28 heads over 4, 4096 tokens in 64-row tiles 117.5 / 114.8, 2 heads of width 64,
+    // 8192 tokens 67.0 / 65.0, fp8 scores 32K 4716 / 4689.  Two independent workgroups on a CU are better left alone (8K tokens
+    // 433.5 / 436.1), and so are three waves to a SIMD (28 heads of width 64, 8192 tokens in 32-row tiles 237 / 245).
+    constexpr bool PRIO = !CALIB && (KSP > 1 || QK8 || (TEAMS > 1 && D == 128));
     auto stage = [&](ScoreTile &cur, ScoreTile &nxt, int j, auto fast_tag) {
         constexpr bool FAST = decltype(fast_tag)::value;
         bf16x8 pb[4];
@@ -624,7 +641,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
             wait_vmcnt<0>();
         }
         wg_barrier();
-        uint32_t flags[HP] = {};
+        uint32_t flags[FW] = {};
         if constexpr (!CALIB) read_flags(flags, (j + 1) & 1);
         if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
         __builtin_amdgcn_sched_barrier(0);
@@ -665,7 +682,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
                         if constexpr (s == SLOTS / 2 - 1) {
                             if constexpr (FAST) nxt.mx = pair_max(nxt.mx);
                         }
-                        if constexpr (s == SLOTS / 2) softmax_max(nxt, HP > 1 && nxt.keep == 0u ? -INFINITY : 0.f);
+                        if constexpr (s == SLOTS / 2) softmax_max(nxt, TEAMS > 1 && nxt.keep == 0u ? -INFINITY : 0.f);
                         if constexpr (s == SLOTS / 2 + 1) softmax_alpha(nxt);
                         if constexpr (s == SLOTS - 1) la_stats();
                         if constexpr (s == SLOTS) prefetch_k(lds_k0 + kring);   // K_{j+2}: landed and visible since the barrier
@@ -694,7 +711,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
             if constexpr (!CALIB) {
                 if (nxt.any_keep != 0u) {
                     if constexpr (FAST) nxt.mx = pair_max(nxt.mx);
-                    softmax_max(nxt, HP > 1 && nxt.keep == 0u ? -INFINITY : 0.f);
+                    softmax_max(nxt, TEAMS > 1 && nxt.keep == 0u ? -INFINITY : 0.f);
                     softmax_alpha(nxt);
                     copy_v_from(v_src, j + 1);
                 }
@@ -733,7 +750,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     reduce_scores(ta, 0, std::false_type{});
     wg_barrier();                                       // flags visible, K_0 consumed
     if constexpr (!CALIB) {
-        uint32_t flags[HP];
+        uint32_t flags[FW];
         read_flags(flags, 0);
         decide(ta, flags);
         if (KSP > 1 && n_own == 0) ta.keep = ta.any_keep = 0u;         // a share without blocks
@@ -752,13 +769,13 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     // gate).  The remaining blocks take the general stages, one at a time.
     int j = 0;
     for (int seg = 0; seg < 2; ++seg) {
-        const int fast_end = (p.gate_mode || (!CALIB && p.block_max)) ? 0 : seg == 0 ? own(p.causal ? n_gate : own_lo) : (p.causal ? 0 : n_own);
+        const int fast_end = (p.gate_mode || (!CALIB && p.block_max)) ? 0 : seg == 0 ? own(all_lo) : (p.causal ? 0 : n_own);
         for (; j + 2 < fast_end; j += 2) {
             stage(ta, tb, j, std::true_type{});
             stage(tb, ta, j + 1, std::true_type{});
         }
         // up to the first block whose look-ahead block lies behind the own range
-        const int gen_end = (seg == 0 && !p.causal) ? min(own(own_hi) - 1, n_own - 1) : n_own - 1;
+        const int gen_end = (seg == 0 && !p.causal) ? min(own(all_hi) - 1, n_own - 1) : n_own - 1;
         for (; j < gen_end; ++j) {
             stage(ta, tb, j, std::false_type{});
             ta = tb;
@@ -774,12 +791,13 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
     if constexpr (CALIB) wait_vmcnt<0>();                 // (the last requests: nothing is in flight when the LDS is given back)
 
     // ---- statistics ------------------------------------------------------------------------
-    const int htid = tid - hsel * NWH * 64;               // thread index within the head's waves
-    if (p.block_max && ksel == 0)
-        for (int jj = n_blk + htid; jj < p.mkv; jj += NWH * 64) p.block_max[stat_row * p.mkv + jj] = NAN;
+    const int htid = tid - tsel * NWH * 64;               // thread index within the waves of a head and tile
+    const bool stat_tile = QT == 1 || i < p.mq;
+    if (p.block_max && ksel == 0 && stat_tile)
+        for (int jj = n_tile + htid; jj < p.mkv; jj += NWH * 64) p.block_max[stat_row * p.mkv + jj] = NAN;
     if constexpr (KSP == 1) {
-        if (p.skip_mask)
-            for (int w = ((n_blk + 31) >> 5) + htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = 0u;
+        if (p.skip_mask && stat_tile)
+            for (int w = ((n_tile + 31) >> 5) + htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = 0u;
     }
     if (p.counts && stat_lane) {
         unsigned long long *c = p.counts + ((int64_t)b * p.hq + h) * 3;
@@ -787,21 +805,21 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         atomicAdd(c + 0, (unsigned long long)n_skipped);
         if (ksel == 0) {
             atomicAdd(c + 1, (unsigned long long)gateable);
-            atomicAdd(c + 2, (unsigned long long)n_blk);
+            atomicAdd(c + 2, (unsigned long long)n_tile);
         }
     }
 
     // ---- the shares of a tile's key blocks put together: (m, l, O~) of every further share through LDS ----
     if constexpr (KSP > 1) {
         constexpr int PER_WAVE = 64 * (16 * DB + 2);      // floats
-        static_assert((KSP - 1) * NWH * HP * PER_WAVE * 4 <= (int)sizeof(lds_raw), "the tile slots hold the shares");
+        static_assert((KSP - 1) * NWH * TEAMS * PER_WAVE * 4 <= (int)sizeof(lds_raw), "the tile slots hold the shares");
         float *const part = reinterpret_cast<float *>(lds_raw);
         wait_vmcnt<0>();                                  // (the last requests of a share without blocks)
         wg_barrier();                                     // nobody reads the slots any more; the mask words are complete
-        if (p.skip_mask && ksel == 0)
-            for (int w = htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = lds_mask[hsel][w];
+        if (p.skip_mask && ksel == 0 && stat_tile)
+            for (int w = htid; w < p.mask_words; w += NWH * 64) p.skip_mask[stat_row * p.mask_words + w] = lds_mask[tsel][w];
         if (ksel > 0) {
-            float *const mine = part + ((ksel - 1) * NWH * HP + wave) * PER_WAVE + lane;
+            float *const mine = part + ((ksel - 1) * NWH * TEAMS + wave) * PER_WAVE + lane;
 #pragma unroll
             for (int x = 0; x < DB; ++x)
 #pragma unroll
@@ -813,7 +831,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         if (ksel > 0) return;
 #pragma unroll 1
         for (int sh = 1; sh < KSP; ++sh) {
-            const float *const its = part + ((sh - 1) * NWH * HP + wave) * PER_WAVE + lane;
+            const float *const its = part + ((sh - 1) * NWH * TEAMS + wave) * PER_WAVE + lane;
             const float m_its = its[16 * DB * 64], m_new = fmaxf(m_run, m_its);
             const float a_own = __builtin_amdgcn_exp2f(m_run - m_new), a_its = __builtin_amdgcn_exp2f(m_its - m_new);
             m_run = m_new;
@@ -835,7 +853,7 @@ __global__ void __launch_bounds__(NWH * HP * KSP * 64, min_waves(D, NWH * HP * K
         // (32 rows of 16 bytes at a time the epilogue took 2.5 us of a workgroup at 128 x 128, all of it waiting for
         // addresses).  Their place is free: the K ring, which nobody reads after the barrier of the last stage, or the
         // share this wave has just merged.  16-byte chunks are XOR-ed with the row, which spreads them over the banks.
-        static_assert(KSP > 1 || NWH * HP * 32 * ROW_BYTES <= KR * KSLOT, "the K ring holds the output rows");
+        static_assert(KSP > 1 || NWH * TEAMS * 32 * ROW_BYTES <= KR * KSLOT, "the K ring holds the output rows");
         const uint32_t o_lds = KSP > 1 ? (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)lds_raw) + wave * (64 * (16 * DB + 2) * 4)
                                        : lds_k0 + wave * (32 * ROW_BYTES);
         auto swz_o = [](int row) { return D == 128 ? row & 15 : (row >> 1) & 7; };
@@ -951,15 +969,15 @@ __global__ void __launch_bounds__(256) quantize_k_kernel(const FwdParams p)
 
 // the call's parameters with the divisors of the work decomposition (decode_work), and its workgroups (0: they do
 // not fit a launch)
-template <int HP> static unsigned decompose(FwdParams &p)
+template <int HP, int QT> static unsigned decompose(FwdParams &p)
 {
-    const long pairs = (long)p.batch * p.hkv, gsub = p.group / HP;
+    const long pairs = (long)p.batch * p.hkv, gsub = p.group / HP, mqg = (p.mq + QT - 1) / QT;
     const long per_tile = (pairs >= 8 ? (pairs + 7) / 8 : pairs) * gsub, wide = pairs >= 8 ? 8 : 1;
-    if (pairs <= 0 || per_tile <= 0 || per_tile * wide * p.mq > 0x7fffffffL) return 0u;
+    if (pairs <= 0 || per_tile <= 0 || per_tile * wide * mqg > 0x7fffffffL) return 0u;
     p.div_tile = fast_div((uint32_t)per_tile);
     p.div_gsub = fast_div((uint32_t)gsub);
     p.div_hkv = fast_div((uint32_t)p.hkv);
-    return (unsigned)(per_tile * wide * p.mq);
+    return (unsigned)(per_tile * wide * mqg);
 }
 
 // K -> workspace as fp8 tiles and V -> workspace as transposed tiles, as far as the call has room for them
@@ -975,11 +993,11 @@ static hipError_t launch_prepasses(const FwdParams &p, hipStream_t stream)
 }
 
 // forward pass; `spare` bytes of LDS more than a workgroup needs keep others off its CU
-template <int D, int NWH, int HP, int KSP, int KR>
+template <int D, int NWH, int HP, int QT, int KSP, int KR>
 hipError_t launch_fwd(const FwdParams &params, hipStream_t stream, unsigned spare = 0)
 {
     FwdParams p = params;
-    const dim3 grid(decompose<HP>(p)), threads(NWH * HP * KSP * 64);
+    const dim3 grid(decompose<HP, QT>(p)), threads(NWH * HP * QT * KSP * 64);
     if (grid.x == 0) return hipErrorInvalidValue;
     constexpr bool WS = NWH == 4 && KSP == 1 && D == 128;      // V (and fp8 K) from the workspace, if the call has one
     if (p.k8 && (!WS || !p.vt)) return hipErrorInvalidValue;
@@ -991,7 +1009,7 @@ hipError_t launch_fwd(const FwdParams &params, hipStream_t stream, unsigned spar
         const hipError_t e = launch_prepasses(p, stream);
         if (e != hipSuccess) return e;
     }
-#define BSFA_LAUNCH(F16, VT, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, KSP, KR, false, F16, VT, QK8>), grid, threads, spare, stream, p)
+#define BSFA_LAUNCH(F16, VT, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, QT, KSP, KR, false, F16, VT, QK8>), grid, threads, spare, stream, p)
     if constexpr (WS) {
         if (p.k8) {
             if (p.f16) BSFA_LAUNCH(true, true, true);
@@ -1011,15 +1029,15 @@ hipError_t launch_fwd(const FwdParams &params, hipStream_t stream, unsigned spar
 }
 
 // score / block-maximum half (calibration)
-template <int D, int NWH, int HP, int KR>
+template <int D, int NWH, int HP, int QT, int KR>
 hipError_t launch_scores(const FwdParams &params, hipStream_t stream)
 {
     FwdParams p = params;
-    const dim3 grid(decompose<HP>(p)), threads(NWH * HP * 64);
+    const dim3 grid(decompose<HP, QT>(p)), threads(NWH * HP * QT * 64);
     if (grid.x == 0) return hipErrorInvalidValue;
     constexpr bool FP8 = NWH == 4 && D == 128;
     if (p.k8 && !FP8) return hipErrorInvalidValue;     // fp8 score operands need the 128 x 64 tile and head_dim 128
-#define BSFA_LAUNCH(F16, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, 1, KR, true, F16, false, QK8>), grid, threads, 0, stream, p)
+#define BSFA_LAUNCH(F16, QK8) hipLaunchKernelGGL((bsfa_fwd_kernel<D, NWH, HP, QT, 1, KR, true, F16, false, QK8>), grid, threads, 0, stream, p)
     if constexpr (FP8) {
         if (p.k8) {
             const hipError_t e = launch_prepasses(p, stream);
@@ -1037,20 +1055,21 @@ hipError_t launch_scores(const FwdParams &params, hipStream_t stream)
 
 // The instantiations are spread over several translation units, compiled side by side from this one file:
 // BSFA_PART says which of them this one holds (0: the dispatch, none of them).
-// F(head_dim, waves per head, heads, shares of the key blocks, K ring), S(head_dim, waves per head, heads, K ring)
-#define BSFA_SHAPES_1(F, S) F(128, 4, 1, 1, 2) F(128, 4, 2, 1, 5)
-#define BSFA_SHAPES_2(F, S) F(128, 4, 1, 2, 2) F(64, 4, 1, 1, 3) F(64, 4, 1, 2, 3)
-#define BSFA_SHAPES_3(F, S) S(128, 4, 2, 4) S(128, 4, 1, 2) S(64, 4, 1, 3) S(128, 2, 2, 2) S(128, 2, 1, 2) S(64, 2, 2, 4) S(64, 2, 1, 2)
-#define BSFA_SHAPES_4(F, S) F(128, 2, 2, 1, 2) F(128, 2, 1, 1, 2)
-#define BSFA_SHAPES_5(F, S) F(128, 2, 2, 2, 2) F(128, 2, 1, 2, 2)
-#define BSFA_SHAPES_6(F, S) F(64, 2, 2, 1, 4) F(64, 2, 1, 1, 2) F(64, 2, 1, 2, 2)
-#define BSFA_SHAPES_7(F, S) F(128, 1, 4, 1, 2) F(128, 1, 2, 1, 2) F(128, 1, 1, 1, 2)
-#define BSFA_SHAPES_8(F, S) F(64, 1, 4, 1, 4) F(64, 1, 2, 1, 4) F(64, 1, 1, 1, 2) S(128, 1, 4, 2) S(128, 1, 2, 2) S(128, 1, 1, 2) \
-                            S(64, 1, 4, 4) S(64, 1, 2, 4) S(64, 1, 1, 2)
-#define BSFA_EXTERN_F(D, N, H, P, K) extern template hipError_t launch_fwd<D, N, H, P, K>(const FwdParams &, hipStream_t, unsigned);
-#define BSFA_EXTERN_S(D, N, H, K) extern template hipError_t launch_scores<D, N, H, K>(const FwdParams &, hipStream_t);
-#define BSFA_DEFINE_F(D, N, H, P, K) template hipError_t launch_fwd<D, N, H, P, K>(const FwdParams &, hipStream_t, unsigned);
-#define BSFA_DEFINE_S(D, N, H, K) template hipError_t launch_scores<D, N, H, K>(const FwdParams &, hipStream_t);
+// F(head_dim, waves per head and tile, heads, tiles, shares of the key blocks, K ring), S(head_dim, waves per head and tile, heads, tiles, K ring)
+#define BSFA_SHAPES_1(F, S) F(128, 4, 1, 1, 1, 2) F(128, 4, 2, 1, 1, 5)
+#define BSFA_SHAPES_2(F, S) F(128, 4, 1, 1, 2, 2) F(64, 4, 1, 1, 1, 3) F(64, 4, 1, 1, 2, 3)
+#define BSFA_SHAPES_3(F, S) S(128, 4, 2, 1, 4) S(128, 4, 1, 1, 2) S(64, 4, 1, 1, 3) S(128, 2, 2, 1, 2) S(128, 2, 1, 2, 2) S(64, 2, 2, 1, 4) S(64, 2, 1, 2, 4)
+#define BSFA_SHAPES_4(F, S) F(128, 2, 2, 1, 1, 2) F(128, 2, 1, 2, 1, 2)
+#define BSFA_SHAPES_5(F, S) F(128, 2, 1, 2, 2, 2) F(128, 2, 1, 1, 2, 2) F(64, 2, 1, 1, 4, 2)
+#define BSFA_SHAPES_6(F, S) F(64, 2, 2, 1, 1, 4) F(64, 2, 1, 2, 1, 4) F(64, 2, 1, 1, 1, 2) F(64, 2, 1, 1, 2, 2)
+#define BSFA_SHAPES_7(F, S) F(128, 1, 4, 1, 1, 2) F(128, 1, 2, 2, 1, 2) F(128, 1, 1, 4, 1, 2)
+#define BSFA_SHAPES_8(F, S) F(128, 1, 1, 4, 2, 2) F(128, 1, 1, 2, 2, 2) F(64, 1, 1, 2, 4, 2)
+#define BSFA_SHAPES_9(F, S) F(64, 1, 4, 1, 1, 4) F(64, 1, 2, 2, 1, 4) F(64, 1, 1, 4, 1, 4) F(64, 1, 1, 2, 2, 2)
+#define BSFA_SHAPES_10(F, S) S(128, 1, 4, 1, 2) S(128, 1, 2, 2, 2) S(128, 1, 1, 4, 2) S(64, 1, 4, 1, 4) S(64, 1, 2, 2, 4) S(64, 1, 1, 4, 4)
+#define BSFA_EXTERN_F(D, N, H, Q, P, K) extern template hipError_t launch_fwd<D, N, H, Q, P, K>(const FwdParams &, hipStream_t, unsigned);
+#define BSFA_EXTERN_S(D, N, H, Q, K) extern template hipError_t launch_scores<D, N, H, Q, K>(const FwdParams &, hipStream_t);
+#define BSFA_DEFINE_F(D, N, H, Q, P, K) template hipError_t launch_fwd<D, N, H, Q, P, K>(const FwdParams &, hipStream_t, unsigned);
+#define BSFA_DEFINE_S(D, N, H, Q, K) template hipError_t launch_scores<D, N, H, Q, K>(const FwdParams &, hipStream_t);
 #if BSFA_PART == 0
 BSFA_SHAPES_1(BSFA_EXTERN_F, BSFA_EXTERN_S)
 BSFA_SHAPES_2(BSFA_EXTERN_F, BSFA_EXTERN_S)
@@ -1060,6 +1079,8 @@ BSFA_SHAPES_5(BSFA_EXTERN_F, BSFA_EXTERN_S)
 BSFA_SHAPES_6(BSFA_EXTERN_F, BSFA_EXTERN_S)
 BSFA_SHAPES_7(BSFA_EXTERN_F, BSFA_EXTERN_S)
 BSFA_SHAPES_8(BSFA_EXTERN_F, BSFA_EXTERN_S)
+BSFA_SHAPES_9(BSFA_EXTERN_F, BSFA_EXTERN_S)
+BSFA_SHAPES_10(BSFA_EXTERN_F, BSFA_EXTERN_S)
 
 bool shape_supported(int head_dim, int block_m, int block_n)
 {
@@ -1073,7 +1094,7 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 // `rows` -- query rows over all heads, twice as many without the causal mask -- is what most lines depend on: a
 // tile's key blocks are taken one after the other, so a call takes at least the longest tile's chain, and the chip
 // holds 512 workgroups of four waves (rows 65 536 in 128-row tiles).
-//  - Up to there the key blocks of a tile may be dealt to two sets of waves (KSP = 2, splits_tiles): half the chain
+//  - Up to there the key blocks of a tile may be dealt to two sets of waves (KSP = 2, split_of): half the chain
 //    for the same work, at the price of a merge, of a K/V stream for each set, and of half the places: a split
 //    workgroup of eight waves has a CU to itself.  One set against two, 128-row tiles:
 //     * as long as every workgroup has a place (8 heads over 2, 256 tiles): 1000 tokens 25.1 / 22.2, 2048 tokens
@@ -1085,11 +1106,21 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //     * beyond that nothing is gained but for the longest chains (9 x 1536 tokens of 4 heads, whose KV heads lie
 //       unevenly on the XCDs, 35.4 / 46.4, 2125 tokens of 32 heads 44.1 / 51.4; 2 heads, 34K tokens 548 / 460), and
 //       from rows 65 536 on tiles are not split (2 heads, 49K tokens 918 / 950).
-//    64-row tiles at head_dim 64, two split workgroups to a CU, lie alike (2048 tokens 32.3 / 31.2, 3072 48.4 / 54.0);
-//    at head_dim 128 they are taken up to rows 45 056 where heads share (1408 tokens 32.9 / 28.0; with 1792 tokens
-//    41.2 / 37.5 and 2048 tokens 46.2 / 44.1 it would pay up to 65 536) and to 32 768 where they do not and a share is
-//    half a CU (12 heads over 4: 2730 tokens 49.0 / 44.3, 3400 tokens 59.4 / 61.6).  32-row tiles, where up to four
-//    heads share a workgroup, are not split.
+//  - Tiles of 64 and 32 rows: a workgroup takes several, so that it has the waves of a 128-row tile (narrow: of 64 rows) on
+//    one K/V stream.  What that leaves is the question above, with workgroups counted in 128 or in 64 rows (n128, n64; one
+//    set of waves on 128 rows / two on 128 / two on 64, at head_dim 64 four on 64 as well):
+//     * head_dim 128.  2 heads, 4800 tokens (n64 150) 76 / 56 / 46, 14 400 tokens (450) 211 / 148 / 126, 12 heads over 4, 2384
+//       tokens (456) 44 / 35.2 / 34.1; from n64 512 on a CU that holds two workgroups of 64 rows has a wave too few (2709 tokens,
+//       516: - / 39.1 / 43.0), and short chains gain less than the second workgroup costs (28 heads over 4, 1026 tokens, 476:
+//       22.9 / 21.4 / 23.8; 32 heads, 650 tokens, 352: 17.4 / 16.8 / 18.2): narrow up to 256 workgroups, up to 512 from 24 key
+//       blocks on.  Two on 128 as for 128-row tiles (8 over 8, 8000 tokens 129 / 115, 11 200 tokens 217 / 221).
+//     * head_dim 64 (one on 128 / two on 64 / four on 64; two workgroups of two sets on a CU, one of four).  2 heads, 4800
+//       tokens 59 / 35 / 28.5, 16K (512) 188 / 105 / 89; 8 over 8, 2632 tokens (336) - / 23.6 / 21.4, 4096 tokens (512, 64
+//       blocks) - / 32.2 / 32.6; 12 over 4, 784 tokens (156, 13 blocks) - / 10.6 / 11.2: four up to 256 workgroups from 16 key
+//       blocks on, up to 384 from 40, up to 512 from 96.  Two up to 512, up to 1024 from 18 blocks on (28 over 4, 1161 tokens
+//       18.7 / 14.6; 3 x 1000 tokens of 12 over 4, 16 blocks, 18.4 / 18.9), up to 1536 from 100 on (12 over 4, 7445 tokens
+//       101 / 98; 32 heads, 2776 tokens 41 / 46).
+//       32-row tiles of fewer than four key blocks are not split (as above; they were not before they shared workgroups).
 //  - V is rewritten into the workspace only where the pass over it pays for itself, which takes its reuse by many
 //    query tiles: head_dim 128, 128-row tiles, beyond 12K tokens.  In place / rewritten, single heads: 8K tokens
 //    408 / 411, 12K 899 / 900, 16K 1569 / 1565, 32K 6075 / 6026 (dense 8166 / 8093); 64 heads over 8, whose reuse is
@@ -1108,12 +1139,15 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    A causal call of 865 to 1024 tiles, nearly two for each of the 512 places, is the exception: from 8K tokens on
 //    pairs are faster there, unless most is skipped (single / pairs: 8 heads over 2, 16K tokens dense 569 / 521, half
 //    434 / 407, 90 % 289 / 305; 16 over 8, 8K tokens 295 / 272, 225 / 212, 156 / 166).
-//    With 64 rows at head_dim 128 two heads fill the CU's two waves per SIMD (8K tokens 654 single, 428 pairs), with
-//    32 rows four (1358 single, 731 pairs, 469 four).  At head_dim 64 the smaller tiles of single heads already do,
-//    and sharing pays on long sequences only: 64 rows from rows 131 072 on (single / pairs: 3072 tokens 48.8 / 50.6,
-//    4096 tokens 79.3 / 72.8, 8K 266 / 247; with elements of different lengths, whose rows are fewer than the call's,
-//    from 393 216 on: 2 x up to 5000 tokens 168 / 180, 3 x up to 5000 231 / 211), 32 rows two heads always (2000 tokens 41 single, 34 pairs) and four from
-//    81 920 on (two / four: 2304 tokens 39.9 / 42.5, 2624 tokens 49.2 / 47.9, 8K 363 / 262).
+//    Smaller tiles share a stream in any case: heads of a group where they can (two of 64 rows; four, or two and two tiles, of
+//    32), else adjacent query tiles, which costs at most 1.3 % more (8K tokens in 64-row tiles 414 / 419, of width 64 239 / 242,
+//    in 32-row tiles of width 64 254 / 247).  Before, a tile of an odd group was a workgroup of one or two waves on a stream of
+//    its own (tile alone / tiles together: 28 heads over 4, 4096 tokens in 64-row tiles 128 / 110, in 32-row tiles 255 / 119; 12
+//    over 4, 9151 tokens in 32-row tiles 570 / 254; width 64, 28 over 4, 8192 tokens 240 / 218, 355 / 222).
+//    A 64-row tile of width 64 is left alone where a sequence is no longer than that (300 x 60 tokens of 3 heads 8.0 / 10.9),
+//    and, with elements of different lengths, up to rows 262 144 (4 x up to 2000 tokens of 16 heads 28.9 / 31.0, 3 x up to 7000
+//    of 8 over 8 86 / 92; 2 x up to 5000 of 32 heads, rows 320 000, 155 / 143), unless three or more heads of an odd group read
+//    the same K and V (2 x up to 5000 of 12 over 4 85 / 79).
 //  - 128-row tiles of head_dim 64: the CU holds three workgroups.  For a causal call of 513 to 768 tiles, which all
 //    three would hold at once, two to a CU are faster beyond 4K tokens (three / two: 8 heads over 8, 12K tokens
 //    165.5 / 155.3; 2 heads, 49K tokens 624 / 590; 28 heads over 4, 3500 tokens 52.8 / 56.4).
@@ -1125,21 +1159,35 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 // single_head or on the workspace, between which results are equal bit for bit.
 static int64_t dispatch_rows(const FwdParams &p) { return (int64_t)p.batch * p.hq * p.seqlen * (p.causal ? 1 : 2); }
 
-static bool splits_tiles(const FwdParams &p, int head_dim, int block_m)
+// How a tile's key blocks are dealt, and for tiles of 64 and 32 rows how many query rows a workgroup takes (tiles of
+// 128 rows are a workgroup each).
+struct Split {
+    int shares;           // sets of waves that the key blocks of a tile are dealt to
+    bool narrow;          // 64 query rows to a workgroup instead of 128
+};
+static Split split_of(const FwdParams &p, int head_dim, int block_m)
 {
     // (the comparison predicate depends on the order of the blocks; the mask words of a split tile must fit the LDS)
-    if (block_m == 32 || p.k8 || p.gate_mode || p.mask_words > kSplitMaskWords) return false;
-    const bool wide64 = block_m == 64 && head_dim == 128, shared = wide64 && p.group % 2 == 0;
-    if (dispatch_rows(p) > (wide64 ? (shared ? 45056 : 32768) : 65536)) return false;
-    // workgroups, with the empty ones that deal KV heads to XCDs, and the places that the chip has for them
-    const int64_t kv = (int64_t)p.batch * p.hkv, places = block_m == 64 && head_dim == 64 ? 512 : 256;
-    const int64_t wgs = (kv >= 8 ? (kv + 7) / 8 * 8 : kv) * (p.group / (shared ? 2 : 1)) * p.mq;
-    return wgs <= places || (p.causal && p.mkv >= (wgs <= 2 * places ? 20 : 64));
+    if (p.k8 || p.gate_mode || p.mask_words > kSplitMaskWords) return {1, false};
+    // workgroups of 64 and of 128 rows, with the empty ones that deal KV heads to XCDs
+    const int64_t kv = (int64_t)p.batch * p.hkv, heads = (kv >= 8 ? (kv + 7) / 8 * 8 : kv) * p.group;
+    const int64_t n64 = heads * ((p.seqlen + 63) / 64), n128 = heads * ((p.seqlen + 127) / 128);
+    if (block_m < 128 && (block_m == 64 || p.mkv >= 4)) {
+        if (head_dim == 128) {
+            if (n64 <= 256 || (p.causal && n64 <= 512 && p.mkv >= 24)) return {2, true};
+        } else {
+            if (n64 <= 256 ? p.mkv >= 16 : p.causal && n64 <= 512 && p.mkv >= (n64 <= 384 ? 40 : 96)) return {4, true};
+            if (n64 <= 512 || (p.causal && n64 <= 1536 && p.mkv >= (n64 <= 1024 ? 18 : 100))) return {2, true};
+        }
+    }
+    if (block_m < 128 && (head_dim == 64 || (block_m == 32 && p.mkv < 4))) return {1, false};
+    const bool split = dispatch_rows(p) <= 65536 && (n128 <= 256 || (p.causal && p.mkv >= (n128 <= 512 ? 20 : 64)));
+    return {split ? 2 : 1, false};
 }
 
 bool rewrites_v(const FwdParams &p, int head_dim, int block_m)
 {
-    return v_rewrite_pays(head_dim, block_m, p.seqlen) && !splits_tiles(p, head_dim, block_m);
+    return v_rewrite_pays(head_dim, block_m, p.seqlen) && split_of(p, head_dim, block_m).shares == 1;
 }
 
 hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool calib, hipStream_t stream)
@@ -1152,33 +1200,36 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
     const bool d128 = head_dim == 128;
     if (calib) {
         if (block_m == 128)
-            return !d128 ? launch_scores<64, 4, 1, 3>(p, stream)
-                 : two && rows > 262144 ? launch_scores<128, 4, 2, 4>(p, stream) : launch_scores<128, 4, 1, 2>(p, stream);
+            return !d128 ? launch_scores<64, 4, 1, 1, 3>(p, stream)
+                 : two && rows > 262144 ? launch_scores<128, 4, 2, 1, 4>(p, stream) : launch_scores<128, 4, 1, 1, 2>(p, stream);
         if (block_m == 64)
-            return d128 ? (two ? launch_scores<128, 2, 2, 2>(p, stream) : launch_scores<128, 2, 1, 2>(p, stream))
-                        : (two ? launch_scores<64, 2, 2, 4>(p, stream) : launch_scores<64, 2, 1, 2>(p, stream));
-        return d128 ? (four ? launch_scores<128, 1, 4, 2>(p, stream) : two ? launch_scores<128, 1, 2, 2>(p, stream) : launch_scores<128, 1, 1, 2>(p, stream))
-                    : (four ? launch_scores<64, 1, 4, 4>(p, stream) : two ? launch_scores<64, 1, 2, 4>(p, stream) : launch_scores<64, 1, 1, 2>(p, stream));
+            return d128 ? (two ? launch_scores<128, 2, 2, 1, 2>(p, stream) : launch_scores<128, 2, 1, 2, 2>(p, stream))
+                        : (two ? launch_scores<64, 2, 2, 1, 4>(p, stream) : launch_scores<64, 2, 1, 2, 4>(p, stream));
+        return d128 ? (four ? launch_scores<128, 1, 4, 1, 2>(p, stream) : two ? launch_scores<128, 1, 2, 2, 2>(p, stream) : launch_scores<128, 1, 1, 4, 2>(p, stream))
+                    : (four ? launch_scores<64, 1, 4, 1, 4>(p, stream) : two ? launch_scores<64, 1, 2, 2, 4>(p, stream) : launch_scores<64, 1, 1, 4, 4>(p, stream));
     }
-    const bool split = splits_tiles(p, head_dim, block_m);
+    const Split split = split_of(p, head_dim, block_m);
     if (block_m == 128) {
-        if (split) return d128 ? launch_fwd<128, 4, 1, 2, 2>(p, stream) : launch_fwd<64, 4, 1, 2, 3>(p, stream);
+        if (split.shares == 2) return d128 ? launch_fwd<128, 4, 1, 1, 2, 2>(p, stream) : launch_fwd<64, 4, 1, 1, 2, 3>(p, stream);
         const bool filling = p.causal && !p.seqlens && !p.k8 && p.seqlen >= 8192 && rows > 110592 && rows <= 131072;
-        if (d128 && two && (filling || p.seqlen > (p.k8 ? 65536 : p.causal ? 24576 : 3072))) return launch_fwd<128, 4, 2, 1, 5>(p, stream);
-        if (d128) return launch_fwd<128, 4, 1, 1, 2>(p, stream);
+        if (d128 && two && (filling || p.seqlen > (p.k8 ? 65536 : p.causal ? 24576 : 3072))) return launch_fwd<128, 4, 2, 1, 1, 5>(p, stream);
+        if (d128) return launch_fwd<128, 4, 1, 1, 1, 2>(p, stream);
         const bool two_to_a_cu = p.causal && !p.seqlens && p.seqlen > 4096 && rows > 65536 && rows <= 98304;
-        return launch_fwd<64, 4, 1, 1, 3>(p, stream, two_to_a_cu ? 16384 : 0);       // (40 KiB and these: a third does not fit)
-    }
-    if (block_m == 64 && d128) {
-        if (split) return two ? launch_fwd<128, 2, 2, 2, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 2>(p, stream);
-        return two ? launch_fwd<128, 2, 2, 1, 2>(p, stream) : launch_fwd<128, 2, 1, 1, 2>(p, stream);
+        return launch_fwd<64, 4, 1, 1, 1, 3>(p, stream, two_to_a_cu ? 16384 : 0);       // (41 KiB and these: a third does not fit)
     }
     if (block_m == 64) {
-        if (split) return launch_fwd<64, 2, 1, 2, 2>(p, stream);
-        return two && rows >= (p.seqlens ? 393216 : 131072) ? launch_fwd<64, 2, 2, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 1, 2>(p, stream);
+        if (d128 && split.narrow) return launch_fwd<128, 2, 1, 1, 2, 2>(p, stream);
+        if (d128 && split.shares == 2) return launch_fwd<128, 2, 1, 2, 2, 2>(p, stream);
+        if (d128) return two ? launch_fwd<128, 2, 2, 1, 1, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 1, 2>(p, stream);
+        if (split.shares > 1) return split.shares == 4 ? launch_fwd<64, 2, 1, 1, 4, 2>(p, stream) : launch_fwd<64, 2, 1, 1, 2, 2>(p, stream);
+        if ((p.seqlens && rows <= 262144 && (two || p.group == 1)) || (!two && p.mq == 1)) return launch_fwd<64, 2, 1, 1, 1, 2>(p, stream);
+        return two ? launch_fwd<64, 2, 2, 1, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 2, 1, 4>(p, stream);
     }
-    if (d128) return four ? launch_fwd<128, 1, 4, 1, 2>(p, stream) : two ? launch_fwd<128, 1, 2, 1, 2>(p, stream) : launch_fwd<128, 1, 1, 1, 2>(p, stream);
-    return four && rows > 81920 ? launch_fwd<64, 1, 4, 1, 4>(p, stream) : two ? launch_fwd<64, 1, 2, 1, 4>(p, stream) : launch_fwd<64, 1, 1, 1, 2>(p, stream);
+    if (d128 && split.narrow) return launch_fwd<128, 1, 1, 2, 2, 2>(p, stream);
+    if (d128 && split.shares == 2) return launch_fwd<128, 1, 1, 4, 2, 2>(p, stream);
+    if (d128) return four ? launch_fwd<128, 1, 4, 1, 1, 2>(p, stream) : two ? launch_fwd<128, 1, 2, 2, 1, 2>(p, stream) : launch_fwd<128, 1, 1, 4, 1, 2>(p, stream);
+    if (split.shares > 1) return split.shares == 4 ? launch_fwd<64, 1, 1, 2, 4, 2>(p, stream) : launch_fwd<64, 1, 1, 2, 2, 2>(p, stream);
+    return four ? launch_fwd<64, 1, 4, 1, 1, 4>(p, stream) : two ? launch_fwd<64, 1, 2, 2, 1, 4>(p, stream) : launch_fwd<64, 1, 1, 4, 1, 4>(p, stream);
 }
 
 #elif BSFA_PART == 1
@@ -1197,6 +1248,10 @@ BSFA_SHAPES_6(BSFA_DEFINE_F, BSFA_DEFINE_S)
 BSFA_SHAPES_7(BSFA_DEFINE_F, BSFA_DEFINE_S)
 #elif BSFA_PART == 8
 BSFA_SHAPES_8(BSFA_DEFINE_F, BSFA_DEFINE_S)
+#elif BSFA_PART == 9
+BSFA_SHAPES_9(BSFA_DEFINE_F, BSFA_DEFINE_S)
+#elif BSFA_PART == 10
+BSFA_SHAPES_10(BSFA_DEFINE_F, BSFA_DEFINE_S)
 #endif
 
 }  // namespace bsfa

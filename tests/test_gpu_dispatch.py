@@ -136,6 +136,21 @@ def test_two_workgroups_to_a_cu_change_nothing(b, hq, hkv, n):
         assert torch.equal(x, y[:b]) and torch.equal(x, y[b:])
 
 
+# tiles of 64 and 32 rows: two and four of them to a workgroup (a last one that lacks some, tiles that end in different
+# blocks, with and without the mask), two and four shares of their key blocks
+SMALL_TILES = [
+    (1, 1090, 4, 2, 64, 32, True, "bnhd"), (1, 1217, 3, 1, 64, 64, True, "qkv"), (1, 1024, 2, 1, 64, 64, False, "bnhd"), (1, 1152, 3, 1, 64, 32, False, "bhnd"),
+    (1, 1600, 3, 1, 128, 64, True, "bnhd"), (1, 2079, 5, 1, 128, 32, True, "bnhd"), (1, 1345, 28, 4, 128, 32, True, "qkv"), (1, 1473, 28, 4, 128, 64, True, "bnhd"),
+    (1, 225, 3, 1, 128, 32, True, "bnhd"), (1, 193, 1, 1, 64, 32, True, "bnhd"), (1, 161, 5, 1, 64, 32, True, "bhnd"), (3, 129, 3, 3, 128, 64, True, "bnhd"),
+    (2, 320, 3, 1, 128, 64, False, "bnhd"), (1, 576, 5, 5, 128, 32, False, "qkv"), (1, 1600, 12, 4, 64, 64, True, "bnhd"), (1, 1792, 28, 4, 64, 32, True, "bnhd"),
+]
+
+
+@pytest.mark.parametrize("case", SMALL_TILES)
+def test_small_tiles_agree_with_every_other_form(case):
+    test_small_calls_agree_with_every_other_form(case)
+
+
 @pytest.mark.parametrize("hq, hkv, n", [(4, 2, 12700), (3, 1, 12416), (4, 2, 24641)])
 def test_rewritten_v_with_lengths(hq, hkv, n):
     """Rewritten V with batch elements that end early, at block edges or are empty, and a workspace full of NaN: V in
