@@ -98,8 +98,8 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     __shared__ __attribute__((aligned(8))) uint8_t lds_flag[2][NW];   // the waves' keep flags
     __shared__ uint32_t lds_mask[TEAMS][KSP > 1 ? kSplitMaskWords : 1];  // KSP > 1: the tiles' skip masks, put together
 
-    int b, g, h0, i0;
-    if (!decode_work<HP, QT>(p, blockIdx.x, b, g, h0, i0)) return;
+    int b, g, h0, i0, n_tok;
+    if (!decode_work<HP, QT, BM * QT>(p, blockIdx.x, b, g, h0, i0, n_tok)) return;
     const int lane = threadIdx.x & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ksel = KSP > 1 ? wave_all / (NWH * TEAMS) : 0;   // which share of the key blocks: those with j % KSP == ksel
@@ -114,12 +114,10 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     const int l32 = lane & 31, hh = lane >> 5;
 
     const int64_t row0 = (int64_t)i * BM;                 // first query row of the tile
-    // tokens of this batch element; a sequence that does not fill its last query tile or key
+    // n_tok: tokens of this batch element; a sequence that does not fill its last query tile or key
     // block behaves as if padded by repeating its last token (Section 4.3): loads of rows
     // beyond the end read row n_tok - 1 instead, padded rows are not stored, and key blocks made
     // of padding only are not visited (the causal mask hides them from every real row).
-    int n_tok = p.seqlen;
-    if (p.seqlens) n_tok = min(max(__builtin_amdgcn_readfirstlane(p.seqlens[b]), 0), p.seqlen);
     const bool real_tile = QT == 1 || row0 < n_tok;       // (with QT > 1 the last tiles of a workgroup may lie beyond the sequence)
     const bool stat_lane = (wrow == 0 && lane == 0 && real_tile);   // one lane per head and tile writes statistics
     const int64_t stat_row = ((int64_t)b * p.hq + h) * p.mq + i;

@@ -151,6 +151,30 @@ def test_small_tiles_agree_with_every_other_form(case):
     test_small_calls_agree_with_every_other_form(case)
 
 
+@pytest.mark.parametrize("hq, hkv, d, bm, n, lengths", [
+    (4, 2, 128, 128, 500, [500, 500, 0, 131, 64]), (6, 3, 64, 64, 700, [700, 0, 1, 63, 699, 128]), (16, 8, 128, 64, 640, [640, 17, 320, 321]),
+    (3, 1, 128, 32, 450, [450, 33, 32]), (8, 8, 64, 32, 200, [0, 200, 64] * 8), (5, 5, 64, 128, 300, [300, 1, 256, 300, 255]), (2, 1, 128, 128, 260, [0, 0]),
+])
+def test_every_tile_of_elements_with_lengths_is_counted_off(hq, hkv, d, bm, n, lengths):
+    """Work items of batches whose elements end early, with pairs of element and KV head that fill the XCDs or do not, one and
+    many to an XCD (more than 16 too): outputs, masks and counts of every element are those of a call of its own (out and lse up
+    to rounding, where only one of the two splits its tiles; bounds as above), what lies beyond its end is untouched or empty."""
+    q, k, v = make(len(lengths), n, hq, hkv, d, "bnhd", torch.bfloat16, n)
+    tau = torch.full((hq,), 2.0, device=DEV)
+    out, lse, counts, mask = call(q, k, v, tau, bm, True, seqlens=torch.tensor(lengths, dtype=torch.int32, device=DEV))
+    for e, m in enumerate(lengths):
+        assert (out[e, m:] == 7.0).all() and (lse[e, m:] == 7.0).all()
+        if m == 0:
+            assert (counts[e] == 0).all() and (mask[e] == 0).all()
+            continue
+        one = call(*(t[e:e + 1, :m] for t in (q, k, v)), tau, bm, True)
+        tiles, words = one[3].shape[2:]
+        assert torch.equal(counts[e], one[2][0]) and torch.equal(mask[e, :, :tiles, :words], one[3][0])
+        assert (mask[e, :, tiles:] == 0).all() and (mask[e, :, :tiles, words:] == 0).all()
+        assert (out[e, :m].float() - one[0][0].float()).abs().max() <= 2.0 ** -7 * v.float().abs().max()
+        assert (lse[e, :m] - one[1][0]).abs().max() <= 2.0 ** -8
+
+
 @pytest.mark.parametrize("hq, hkv, n", [(4, 2, 12700), (3, 1, 12416), (4, 2, 24641)])
 def test_rewritten_v_with_lengths(hq, hkv, n):
     """Rewritten V with batch elements that end early, at block edges or are empty, and a workspace full of NaN: V in
