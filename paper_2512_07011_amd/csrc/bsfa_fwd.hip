@@ -302,8 +302,10 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     // stage, behind its last MFMAs), so that the score MFMAs do not start with an LDS round trip.
     kop_t kpre[PDK];
     auto prefetch_k = [&](uint32_t kt) {
+        uint32_t at = kt + ka_base;
+        asm("" : "+v"(at));                                // (else every operand gets a base of its own, and an addition)
 #pragma unroll
-        for (int n = 0; n < PDK; ++n) kpre[n] = k_operand(kt + ka_base, n);
+        for (int n = 0; n < PDK; ++n) kpre[n] = k_operand(at, n);
     };
 
     auto half_max = [&](ScoreTile &t, int n) {              // after MFMA n, once s[0] is complete
@@ -430,13 +432,21 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
         t.any_keep = w[0] | w[FW - 1];
     };
 
+    // The mask word of block j, its last: counted, and written if somebody asks for the mask.  mask_word is a shift register
+    // (bit j % 32 of a word comes in at the top, 32 / KSP times a word), so it is never cleared and stays scalar.
+    auto flush_mask = [&](int j) {
+        const uint32_t word = mask_word >> (32 - KSP * ((j & 31) / KSP + 1));
+        n_skipped += (unsigned)__builtin_popcount(word);
+        if (p.skip_mask && stat_lane && (QT == 1 || (j & ~31) < n_tile)) {
+            if constexpr (KSP > 1) atomicOr(&lds_mask[tsel][j >> 5], word);
+            else p.skip_mask[stat_row * p.mask_words + (j >> 5)] = word;
+        }
+    };
     // statistics of block j: decision of this wave's head, and its maximum if asked for
     auto record = [&](uint32_t keep, int jl, auto fast_tag) {
         constexpr bool FAST = decltype(fast_tag)::value;
         const int j = glob(jl);
-        const uint32_t skipped = keep == 0u && (QT == 1 || FAST || j < n_tile) ? 1u : 0u;
-        n_skipped += skipped;
-        mask_word |= skipped << (j & 31);
+        mask_word = (mask_word >> KSP) | (keep == 0u && (QT == 1 || FAST || j < n_tile) ? 1u << (32 - KSP + ksel) : 0u);
         if (CALIB || !FAST) {
             if (p.block_max && stat_lane && (QT == 1 || j < n_tile)) {
                 float bmax = NAN;
@@ -448,12 +458,8 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
                 p.block_max[stat_row * p.mkv + j] = bmax;
             }
         }
-        if ((j & 31) > 31 - KSP || j > n_blk - 1 - KSP) {      // the last block of a mask word, or of the workgroup's tiles
-            if (p.skip_mask && stat_lane && (QT == 1 || (j & ~31) < n_tile)) {
-                if constexpr (KSP > 1) atomicOr(&lds_mask[tsel][j >> 5], mask_word);
-                else p.skip_mask[stat_row * p.mask_words + (j >> 5)] = mask_word;
-            }
-            mask_word = 0;
+        if constexpr (!CALIB) {
+            if ((j & 31) > 31 - KSP) flush_mask(j);
         }
     };
 
@@ -789,6 +795,7 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     if constexpr (CALIB) wait_vmcnt<0>();                 // (the last requests: nothing is in flight when the LDS is given back)
 
     // ---- statistics ------------------------------------------------------------------------
+    if (!CALIB && n_own > 0 && (glob(n_own - 1) & 31) <= 31 - KSP) flush_mask(glob(n_own - 1));     // the last word, begun
     const int htid = tid - tsel * NWH * 64;               // thread index within the waves of a head and tile
     const bool stat_tile = QT == 1 || i < p.mq;
     if (p.block_max && ksel == 0 && stat_tile)
