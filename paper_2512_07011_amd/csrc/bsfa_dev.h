@@ -204,7 +204,8 @@ __device__ __forceinline__ int row_sum16(int x)
 // Work decomposition: a work item is (batch b, KV head, group of HP query heads, QT query tiles from i on).
 // With at least 8 (batch, KV head) pairs the pair is chosen by the low three bits of the
 // workgroup id, which is the XCD the hardware dispatches the group to, so that all groups
-// streaming one K/V sequence share one L2.  Heavy (late) query tiles first.
+// streaming one K/V sequence share one L2.  Heavy (late) query tiles first; which places the first workgroups share a
+// CU in, turned_places says.
 //
 // Where batch elements have lengths of their own, only the work items that exist are counted off, late tiles first
 // (the others follow, for their empty statistics): consecutive workgroups are dealt to the parts of an XCD in turn, and
@@ -213,13 +214,18 @@ __device__ __forceinline__ int row_sum16(int x)
 // With c the tiles of each pair, S(t) = sum of max(0, c - t) items lie in the rows of tiles from t up.  Item x is in row
 // t = the last with S(t) > x; the pairs that row holds are those with S(c) <= x (a lane each), and with their number k
 // S(t) = sum of their c - k t.
-template <int HP, int QT, int ROWS>
+template <int HP, int QT, int ROWS, int PLACES>
 __device__ __forceinline__ bool decode_work(const FwdParams &p, uint32_t w, int &b, int &g, int &h0, int &i, int &n_tok)
 {
     const int pairs = p.batch * p.hkv;
     const int gsub = p.group / HP;               // head groups per KV head (HP: 1, 2 or 4)
     const int npx = pairs >= 8 ? (pairs + 7) >> 3 : pairs;                               // pairs of an XCD
-    const uint32_t v = pairs >= 8 ? w >> 3 : w;
+    uint32_t v = pairs >= 8 ? w >> 3 : w;
+    if constexpr (PLACES > 1) {                  // (selects: branches would put a load's way in front of the loads below)
+        uint32_t to = p.turn[0] + p.turn[1] - 1 - v;
+        if constexpr (PLACES > 2) to = v < p.turn[1] ? to : p.turn[1] + p.turn[2] - 1 - v;
+        v = (v >= p.turn[0]) & (v < p.turn[PLACES - 1]) ? to : v;
+    }
     const int tiles = (p.mq + QT - 1) / QT;
     int pl, t;
     uint32_t sub;

@@ -39,6 +39,7 @@
 // (HP = 2) all stand at the same barrier, but read half as much from L2 (see launch_forward for the line).
 // Short sequences: the chain of key blocks of the longest tile, about 1.6 us a block.
 #include "bsfa_dev.h"
+#include <algorithm>
 
 namespace bsfa {
 
@@ -59,6 +60,9 @@ constexpr int min_waves(int d, int waves, int lds_bytes)
 {
     return d == 64 && waves * (160 * 1024 / (lds_bytes + 1024)) >= 12 && waves <= 4 ? 3 : 2;
 }
+
+// Workgroups a CU holds, as far as decode_work asks: tiles that are split are left as they are (turned_places)
+constexpr int places_of(int d, int waves, int shares) { return shares > 1 || waves != 4 ? 1 : d == 64 ? 3 : 2; }
 
 constexpr int k_slot_bytes(int d) { return d / 8 * kPitch16; }
 constexpr int v_slot_bytes(int d) { return d / 8 * v_pitch(d); }
@@ -99,7 +103,7 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     __shared__ uint32_t lds_mask[TEAMS][KSP > 1 ? kSplitMaskWords : 1];  // KSP > 1: the tiles' skip masks, put together
 
     int b, g, h0, i0, n_tok;
-    if (!decode_work<HP, QT, BM * QT>(p, blockIdx.x, b, g, h0, i0, n_tok)) return;
+    if (!decode_work<HP, QT, BM * QT, CALIB ? 1 : places_of(D, NWH * HP * QT, KSP)>(p, blockIdx.x, b, g, h0, i0, n_tok)) return;
     const int lane = threadIdx.x & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ksel = KSP > 1 ? wave_all / (NWH * TEAMS) : 0;   // which share of the key blocks: those with j % KSP == ksel
@@ -982,6 +986,7 @@ template <int HP, int QT> static unsigned decompose(FwdParams &p)
     p.div_tile = fast_div((uint32_t)per_tile);
     p.div_gsub = fast_div((uint32_t)gsub);
     p.div_hkv = fast_div((uint32_t)p.hkv);
+    p.turn[0] = p.turn[1] = p.turn[2] = 0;
     return (unsigned)(per_tile * wide * mqg);
 }
 
@@ -997,6 +1002,25 @@ static hipError_t launch_prepasses(const FwdParams &p, hipStream_t stream)
     return hipGetLastError();
 }
 
+// Where a CU holds two or three workgroups and a causal call has no more than fill these places twice, the second and
+// the third workgroup of every CU are dealt the other way round, so that the longest tiles share their CU with the
+// shortest of the rest and not with the next longest.  In order / turned, us, bf16, half skip (dense): head_dim 64,
+// 64-row tiles, 2 x 4096 tokens of 12 heads over 4 (768 workgroups) 58.5 / 57.3 (73.8 / 67.7), 12 000 tokens (1128) 210 / 201,
+// 4096 tokens of 28 over 4 (896) 63.4 / 61.6; 32-row tiles, 3500 tokens of 32 over 8 57.0 / 54.5; head_dim 128, 32 over 8,
+// 2300 tokens (576) 47.4 / 46.7 (56.8 / 56.0), 4096 tokens (1024) 113.9 / 111.3 (148.2 / 141.4); 28 over 4, 4096 tokens in
+// 64-row tiles 105.8 / 103.5; at worst even (3500 tokens of 32 heads half skip 90.7 / 91.4, dense 117.1 / 112.1).  With more
+// than that, what is dealt first is soon forgotten (6000 tokens of 32 heads 226 / 226), and tiles that are split are as short
+// as the call allows (2300 tokens of 12 over 4, head_dim 64, 29.3 / 31.8).
+static void turned_places(FwdParams &p, unsigned workgroups, int places)
+{
+    const bool xcd = (int64_t)p.batch * p.hkv >= 8;        // (as decode_work counts them)
+    const unsigned n = xcd ? workgroups / 8 : workgroups, cus = xcd ? 32 : 256;
+    if (places == 1 || !p.causal || p.seqlens || n <= cus || n > 2 * places * cus) return;
+    p.turn[0] = cus;
+    p.turn[1] = std::min(n, 2 * cus);
+    p.turn[2] = std::min(n, places * cus);
+}
+
 // forward pass; `spare` bytes of LDS more than a workgroup needs keep others off its CU
 template <int D, int NWH, int HP, int QT, int KSP, int KR>
 hipError_t launch_fwd(const FwdParams &params, hipStream_t stream, unsigned spare = 0)
@@ -1004,6 +1028,7 @@ hipError_t launch_fwd(const FwdParams &params, hipStream_t stream, unsigned spar
     FwdParams p = params;
     const dim3 grid(decompose<HP, QT>(p)), threads(NWH * HP * QT * KSP * 64);
     if (grid.x == 0) return hipErrorInvalidValue;
+    turned_places(p, grid.x, std::min(places_of(D, NWH * HP * QT, KSP), spare ? 2 : 3));
     constexpr bool WS = NWH == 4 && KSP == 1 && D == 128;      // V (and fp8 K) from the workspace, if the call has one
     if (p.k8 && (!WS || !p.vt)) return hipErrorInvalidValue;
     if (p.counts && !(WS && p.vt)) {                   // (the pass over V clears them)
@@ -1106,8 +1131,10 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //       37.6 / 31.7, 4096 tokens 66.9 / 53.1, 512 tokens dense 17.3 / 16.8.  (Below that the merge costs more than the
 //       chain, 300 tokens dense 12.3 / 12.6, 64 tokens 7.0 / 9.1, but a call then takes the host 11 us; and elements of
 //       a batch get the bits of a call of their own.)
-//     * with up to two workgroups to a place it takes a chain of 20 blocks or more: 8 x 1000 tokens of 8 heads
-//       (512 tiles) 27.3 / 31.7, 1536 tokens of 32 heads 33.8 / 31.2, 2048 tokens 43.9 / 43.1 (dense 52.0 / 50.1).
+//     * with up to two workgroups to a place it takes a chain of 20 blocks or more (8 x 1000 tokens of 8 heads, 512 tiles,
+//       27.3 / 31.7; 2 x 2048 tokens of 12 over 4, 384, 35.9 / 35.4, dense 42.8 / 39.1; 3000 tokens of 16 over 8, 384,
+//       48.4 / 41.5), and of 32 where nearly every place is taken (turned_places: 1700 tokens of 32 heads, 448 tiles,
+//       32.8 / 36.6, dense 38.4 / 39.7; 2048 tokens 41.2 / 41.1, dense 48.2 / 47.1).
 //     * beyond that nothing is gained but for the longest chains (9 x 1536 tokens of 4 heads, whose KV heads lie
 //       unevenly on the XCDs, 35.4 / 46.4, 2125 tokens of 32 heads 44.1 / 51.4; 2 heads, 34K tokens 548 / 460), and
 //       from rows 65 536 on tiles are not split (2 heads, 49K tokens 918 / 950).
@@ -1186,7 +1213,7 @@ static Split split_of(const FwdParams &p, int head_dim, int block_m)
         }
     }
     if (block_m < 128 && (head_dim == 64 || (block_m == 32 && p.mkv < 4))) return {1, false};
-    const bool split = dispatch_rows(p) <= 65536 && (n128 <= 256 || (p.causal && p.mkv >= (n128 <= 512 ? 20 : 64)));
+    const bool split = dispatch_rows(p) <= 65536 && (n128 <= 256 || (p.causal && p.mkv >= (n128 <= 400 ? 20 : n128 <= 512 ? 32 : 64)));
     return {split ? 2 : 1, false};
 }
 

@@ -48,6 +48,8 @@ struct FwdParams {
     int mask_words;
     FastDiv div_tile, div_gsub, div_hkv;   // work decomposition (decode_work): work items per query tile, head groups per
                                            // KV head, KV heads; set by the launch
+    uint32_t turn[3];                // workgroups turn[0] .. turn[1] - 1 of an XCD, and from there to turn[2] - 1, take their
+                                     // work items in reverse (decode_work); set by the launch
 };
 
 // Shapes whose forward calls rewrite V into the workspace, if they are given one and take their key blocks one after

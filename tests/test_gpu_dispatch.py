@@ -136,6 +136,20 @@ def test_two_workgroups_to_a_cu_change_nothing(b, hq, hkv, n):
         assert torch.equal(x, y[:b]) and torch.equal(x, y[b:])
 
 
+@pytest.mark.parametrize("b, n, hq, hkv, d, bm", [
+    (1, 2100, 32, 8, 128, 128), (1, 2300, 28, 4, 128, 128), (1, 900, 40, 8, 128, 128), (11, 260, 3, 3, 128, 128), (1, 4160, 28, 4, 128, 64), (3, 500, 16, 8, 128, 32),
+    (11, 1000, 3, 3, 64, 64), (1, 3000, 28, 4, 64, 64), (2, 6000, 12, 4, 64, 64), (16, 130, 16, 8, 64, 64), (1, 1100, 64, 8, 64, 128), (1, 11000, 6, 2, 64, 128), (9, 420, 12, 4, 64, 32),
+])
+def test_turned_places_change_nothing(b, n, hq, hkv, d, bm):
+    """Calls whose workgroups fill the chip once or twice, with KV heads that fill the XCDs or do not, against the same call
+    with lengths, whose work items are counted off in another way and never turned, bit for bit."""
+    q, k, v = make(b, n, hq, hkv, d, "bnhd", torch.bfloat16, n)
+    tau = torch.full((hq,), 2.0, device=DEV)
+    plain, counted = call(q, k, v, tau, bm, True), call(q, k, v, tau, bm, True, seqlens=torch.full((b,), n, dtype=torch.int32, device=DEV))
+    for x, y in zip(plain, counted):
+        assert torch.equal(x, y)
+
+
 # tiles of 64 and 32 rows: two and four of them to a workgroup (a last one that lacks some, tiles that end in different
 # blocks, with and without the mask), two and four shares of their key blocks
 SMALL_TILES = [
