@@ -31,7 +31,7 @@
 // operand is a plain 16-byte LDS read; without one it is gathered with the transposing read.
 //
 // What bounds it.  Long sequences: the matrix pipe at the clock the card holds under this load (a plain
-// library product reaches 1360 TFLOP/s here, this kernel 1080 to 1150 dense, busy in 57 % of the cycles) and
+// library product reaches 1360 TFLOP/s here, this kernel 1060 to 1190 dense, busy in 58 to 65 % of the cycles) and
 // the issue of each wave: a stage takes a wave about 2900 cycles for 1024 of MFMA, whether a second one shares its
 // SIMD or not (a vector instruction 4.4 cycles, an exponential 8, a taken branch 30, dependent ones 8), so every
 // instruction in a wave's way counts, above all between the last score MFMA and the first PV MFMA of a block.  Two workgroups of four waves on a CU
@@ -158,7 +158,7 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     }
 
     const uint16_t *kbase = p.k + (int64_t)b * p.ksb + (int64_t)g * p.ksh;
-    // VT: V comes from the workspace, one pre-transposed, pre-swizzled 64-key tile after the other
+    // VT: V comes from the workspace, one transposed 64-key tile after the other, unit by unit
     const uint16_t *vbase = VT ? p.vt + ((int64_t)b * p.hkv + g) * p.mkv * (int64_t)(BN * D)
                                : p.v + (int64_t)b * p.vsb + (int64_t)g * p.vsh;
     // threshold of this wave's head; tiles past the calibrated length use its last tile's (Section 4.3)
@@ -169,7 +169,7 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     const uint32_t koff = QK8 ? (uint32_t)tid * 16u : unit_src_offset<D>(wave, lane, (int)p.ksn);
     const uint32_t voff = VT ? (uint32_t)tid * 16u : unit_src_offset<D>(wave, lane, (int)p.vsn);
     const uint32_t krep = NWS * (QK8 ? (uint32_t)kUnit : (uint32_t)p.ksn * 2u), vrep = NWS * (VT ? (uint32_t)kUnit : (uint32_t)p.vsn * 2u);
-    // QK8: K comes from the workspace as fp8 tiles (64 rows of D bytes, swizzled for the operand reads)
+    // QK8: K comes from the workspace as fp8 tiles (64 rows of D bytes, unit by unit)
     const uint8_t *k8base = QK8 ? p.k8 + ((int64_t)b * p.hkv + g) * p.mkv * (int64_t)(BN * D) : nullptr;
     const int64_t kstep = (int64_t)BN * p.ksn, vstep = VT ? (int64_t)(BN * D) : (int64_t)BN * p.vsn;
     // Requests of a tile: bytes of K_t and V_t of this wave's share that exist (0: block t lies behind the share's
@@ -220,7 +220,9 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     const int L = lane & 15, g16 = (lane >> 4) & 1;
     // VT: the tile holds V^T, D rows of 64 keys (128 bytes), the keys of every 16-key step ordered
     // so that the 8 keys a lane multiplies are contiguous.  Lane reads row 32x + l32, chunk 2u + hh, as one b128,
-    // va_base + 256 x + 32 u: at about four times the LDS rate of the transposing reads.
+    // va_base + 256 x + 32 u: at about four times the LDS rate of the transposing reads.  (The lanes of a phase of a read come
+    // from both 16-row halves of the block, which lie half the banks apart, and meet conflicts: 16 % of the cycles at 128K dense.
+    // Halves a multiple of all the banks apart have none and are no faster: 32K 5812 / 5816 us, dense 7668 / 7653, fp8 4295 / 4318.)
     const uint32_t va_base = VT ? (uint32_t)((l32 % 16) * kPitch16 + (l32 / 16) * 128 + 16 * hh)
                                 : (uint32_t)((4 * hh + (L >> 2)) * v_pitch(D) + 2 * G16_COLS * g16 + 8 * (L & 3));
 
