@@ -250,8 +250,7 @@ __device__ __forceinline__ bool decode_work(const FwdParams &p, uint32_t w, int 
         const bool in_row = valid && above <= x;
         const int k = __builtin_popcountll(__builtin_amdgcn_ballot_w64(in_row)), sum = row_sum16(in_row ? c : 0);
         if (sum <= x) return false;              // (only where pairs do not fill the XCDs)
-        // (exact: below 2^24, and a quotient that is not whole is at least 1/16 from the next one)
-        t = (int)(((float)(sum - x - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)k));
+        t = counted_row(sum, x, k);
         const int at = x - (sum - k * (t + 1));  // which of the row's pairs: those longer than t, in order
         const bool longer = in_row && c > t;
         const uint64_t m = __builtin_amdgcn_ballot_w64(longer);

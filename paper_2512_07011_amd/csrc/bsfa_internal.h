@@ -24,6 +24,11 @@ inline FastDiv fast_div(uint32_t d)               // 1 <= d < 2^31
     return {(uint32_t)(((1ull << (31 + s)) + d - 1) / d), 31 + s};
 }
 
+// Work items counted off (decode_work): rows of k items each lie above item x, `sum` items in all if they went down to row
+// 0; the row that item x is in.  Whole numbers: a product with a reciprocal of 32 bits is off by a row from about two
+// million items on (15 to a row), which no sequence that fits the card's memory has, but nothing else keeps out.
+__host__ __device__ inline int counted_row(int sum, int x, int k) { return (int)((uint32_t)(sum - x - 1) / (uint32_t)k); }
+
 struct FwdParams {
     const uint16_t *q, *k, *v;       // bf16 or fp16 bit patterns (f16 says which)
     uint16_t *out;
