@@ -224,7 +224,7 @@ __device__ __forceinline__ bool decode_work(const FwdParams &p, uint32_t w, int 
     if constexpr (PLACES > 1) {                  // (selects: branches would put a load's way in front of the loads below)
         uint32_t to = p.turn[0] + p.turn[1] - 1 - v;
         if constexpr (PLACES > 2) to = v < p.turn[1] ? to : p.turn[1] + p.turn[2] - 1 - v;
-        v = (v >= p.turn[0]) & (v < p.turn[PLACES - 1]) ? to : v;
+        v = ((v >= p.turn[0]) & (v < p.turn[PLACES - 1])) ? to : v;
     }
     const int tiles = (p.mq + QT - 1) / QT;
     int pl, t;
