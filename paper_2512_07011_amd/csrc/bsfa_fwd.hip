@@ -1136,7 +1136,11 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //     * with up to two workgroups to a place it takes a chain of 20 blocks or more (8 x 1000 tokens of 8 heads, 512 tiles,
 //       27.3 / 31.7; 2 x 2048 tokens of 12 over 4, 384, 35.9 / 35.4, dense 42.8 / 39.1; 3000 tokens of 16 over 8, 384,
 //       48.4 / 41.5), and of 32 where nearly every place is taken (turned_places: 1700 tokens of 32 heads, 448 tiles,
-//       32.8 / 36.6, dense 38.4 / 39.7; 2048 tokens 41.2 / 41.1, dense 48.2 / 47.1).
+//       32.8 / 36.6, dense 38.4 / 39.7; 2048 tokens 41.2 / 41.1, dense 48.2 / 47.1), at head_dim 64 of 28 (1900 tokens of 28 over
+//       4, 420 tiles, half skip 26.2 / 26.4, dense 31.5 / 29.9; 1700 tokens of 32 heads, 27 blocks, 25.3 / 26.0, 28.5 / 28.4).
+//       Elements of different lengths leave places free and are not turned: 20 blocks there too (2 x up to 1900 tokens of 14
+//       over 2 33.1 / 28.6, head_dim 64 27.1 / 21.7; 4 x up to 1700 of 8 over 8 33.0 / 27.7), unless every XCD has a single
+//       element's KV head, and that of the longest as many tiles as without lengths (4 x up to 1700 of 8 over 2 34.6 / 35.9).
 //     * beyond that nothing is gained but for the longest chains (9 x 1536 tokens of 4 heads, whose KV heads lie
 //       unevenly on the XCDs, 35.4 / 46.4, 2125 tokens of 32 heads 44.1 / 51.4; 2 heads, 34K tokens 548 / 460), and
 //       from rows 65 536 on tiles are not split (2 heads, 49K tokens 918 / 950).
@@ -1215,7 +1219,8 @@ static Split split_of(const FwdParams &p, int head_dim, int block_m)
         }
     }
     if (block_m < 128 && (head_dim == 64 || (block_m == 32 && p.mkv < 4))) return {1, false};
-    const bool split = dispatch_rows(p) <= 65536 && (n128 <= 256 || (p.causal && p.mkv >= (n128 <= 400 ? 20 : n128 <= 512 ? 32 : 64)));
+    const int taken = p.seqlens && kv != 8 ? 20 : head_dim == 64 ? 28 : 32;      // the line where nearly every place is taken
+    const bool split = dispatch_rows(p) <= 65536 && (n128 <= 256 || (p.causal && p.mkv >= (n128 <= 400 ? 20 : n128 <= 512 ? taken : 64)));
     return {split ? 2 : 1, false};
 }
 
