@@ -1091,7 +1091,7 @@ hipError_t launch_scores(const FwdParams &params, hipStream_t stream)
 #define BSFA_SHAPES_1(F, S) F(128, 4, 1, 1, 1, 2) F(128, 4, 2, 1, 1, 5)
 #define BSFA_SHAPES_2(F, S) F(128, 4, 1, 1, 2, 2) F(64, 4, 1, 1, 1, 3) F(64, 4, 1, 1, 2, 3)
 #define BSFA_SHAPES_3(F, S) S(128, 4, 2, 1, 4) S(128, 4, 1, 1, 2) S(64, 4, 1, 1, 3) S(128, 2, 2, 1, 2) S(128, 2, 1, 2, 2) S(64, 2, 2, 1, 4) S(64, 2, 1, 2, 4)
-#define BSFA_SHAPES_4(F, S) F(128, 2, 2, 1, 1, 2) F(128, 2, 1, 2, 1, 2)
+#define BSFA_SHAPES_4(F, S) F(128, 2, 2, 1, 1, 2) F(128, 2, 1, 2, 1, 2) F(128, 2, 1, 1, 1, 2)
 #define BSFA_SHAPES_5(F, S) F(128, 2, 1, 2, 2, 2) F(128, 2, 1, 1, 2, 2) F(64, 2, 1, 1, 4, 2)
 #define BSFA_SHAPES_6(F, S) F(64, 2, 2, 1, 1, 4) F(64, 2, 1, 2, 1, 4) F(64, 2, 1, 1, 1, 2) F(64, 2, 1, 1, 2, 2)
 #define BSFA_SHAPES_7(F, S) F(128, 1, 4, 1, 1, 2) F(128, 1, 2, 2, 1, 2) F(128, 1, 1, 4, 1, 2)
@@ -1151,7 +1151,9 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //       tokens (456) 44 / 35.2 / 34.1; from n64 512 on a CU that holds two workgroups of 64 rows has a wave too few (2709 tokens,
 //       516: - / 39.1 / 43.0), and short chains gain less than the second workgroup costs (28 heads over 4, 1026 tokens, 476:
 //       22.9 / 21.4 / 23.8; 32 heads, 650 tokens, 352: 17.4 / 16.8 / 18.2): narrow up to 256 workgroups, up to 512 from 24 key
-//       blocks on.  Two on 128 as for 128-row tiles (8 over 8, 8000 tokens 129 / 115, 11 200 tokens 217 / 221).
+//       blocks on.  Two on 128 as for 128-row tiles (8 over 8, 8000 tokens 129 / 115, 11 200 tokens 217 / 221), but for chains of
+//       fewer than 8 blocks (one on 64 / one on 128 / two on 128: 64 x 100 tokens of 3 heads 9.2 / 9.4 / 10.7, of 4 over 2 - / 8.9 /
+//       10.8, 8 x 250 of 12 over 4 11.4 / 12.1 / 12.5; 8 blocks, 4 x 450 of 12 over 4 15.0 / 15.2 / 14.5).
 //     * head_dim 64 (one on 128 / two on 64 / four on 64; two workgroups of two sets on a CU, one of four).  2 heads, 4800
 //       tokens 59 / 35 / 28.5, 16K (512) 188 / 105 / 89; 8 over 8, 2632 tokens (336) - / 23.6 / 21.4, 4096 tokens (512, 64
 //       blocks) - / 32.2 / 32.6; 12 over 4, 784 tokens (156, 13 blocks) - / 10.6 / 11.2: four up to 256 workgroups from 16 key
@@ -1182,6 +1184,12 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    in 32-row tiles of width 64 254 / 247).  Before, a tile of an odd group was a workgroup of one or two waves on a stream of
 //    its own (tile alone / tiles together: 28 heads over 4, 4096 tokens in 64-row tiles 128 / 110, in 32-row tiles 255 / 119; 12
 //    over 4, 9151 tokens in 32-row tiles 570 / 254; width 64, 28 over 4, 8192 tokens 240 / 218, 355 / 222).
+//    A 64-row tile of width 128 is left alone where every tile has a place, and where a sequence is a single tile (alone / with
+//    the next: 24 x 190 tokens of 6 over 2, 432 tiles, 10.8 / 11.9; 300 x 60 of 3 over 1, 904, 14.0 / 16.5; 64 x 130 of 3 heads, 576,
+//    12.6 / 11.7), and with elements of different lengths, which leave places free, up to 768 tiles, from 8 key blocks on 1024,
+//    from 12 on 1152 (4 x up to 900 tokens of 16 heads, 960, 21.1 / 23.4; 3 x up to 3000 of 8, 1128, 50.0 / 56.1; 8 x up to 500 of 12
+//    over 4, 768, 15.1 / 16.7, of 16, 1024, 16.5 / 17.2; 16 x up to 300, 960, 15.1 / 13.3; 4 x up to 600 of 28 over 4, 1120, 19.6 / 18.8;
+//    3 x up to 2000 of 16, 1536, 43.2 / 43.3; 2 x up to 5000, 2528, 164 / 126).
 //    A 64-row tile of width 64 is left alone where a sequence is no longer than that (300 x 60 tokens of 3 heads 8.0 / 10.9),
 //    and, with elements of different lengths, up to rows 262 144 (4 x up to 2000 tokens of 16 heads 28.9 / 31.0, 3 x up to 7000
 //    of 8 over 8 86 / 92; 2 x up to 5000 of 32 heads, rows 320 000, 155 / 143), unless three or more heads of an odd group read
@@ -1197,6 +1205,13 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 // single_head or on the workspace, between which results are equal bit for bit.
 static int64_t dispatch_rows(const FwdParams &p) { return (int64_t)p.batch * p.hq * p.seqlen * (p.causal ? 1 : 2); }
 
+// workgroups of one head and `rows` query rows, with the empty ones that deal KV heads to XCDs
+static int64_t workgroups_of(const FwdParams &p, int rows)
+{
+    const int64_t kv = (int64_t)p.batch * p.hkv, heads = (kv >= 8 ? (kv + 7) / 8 * 8 : kv) * p.group;
+    return heads * ((p.seqlen + rows - 1) / rows);
+}
+
 // How a tile's key blocks are dealt, and for tiles of 64 and 32 rows how many query rows a workgroup takes (tiles of
 // 128 rows are a workgroup each).
 struct Split {
@@ -1207,9 +1222,7 @@ static Split split_of(const FwdParams &p, int head_dim, int block_m)
 {
     // (the comparison predicate depends on the order of the blocks; the mask words of a split tile must fit the LDS)
     if (p.k8 || p.gate_mode || p.mask_words > kSplitMaskWords) return {1, false};
-    // workgroups of 64 and of 128 rows, with the empty ones that deal KV heads to XCDs
-    const int64_t kv = (int64_t)p.batch * p.hkv, heads = (kv >= 8 ? (kv + 7) / 8 * 8 : kv) * p.group;
-    const int64_t n64 = heads * ((p.seqlen + 63) / 64), n128 = heads * ((p.seqlen + 127) / 128);
+    const int64_t kv = (int64_t)p.batch * p.hkv, n64 = workgroups_of(p, 64), n128 = workgroups_of(p, 128);
     if (block_m < 128 && (block_m == 64 || p.mkv >= 4)) {
         if (head_dim == 128) {
             if (n64 <= 256 || (p.causal && n64 <= 512 && p.mkv >= 24)) return {2, true};
@@ -1220,8 +1233,17 @@ static Split split_of(const FwdParams &p, int head_dim, int block_m)
     }
     if (block_m < 128 && (head_dim == 64 || (block_m == 32 && p.mkv < 4))) return {1, false};
     const int taken = p.seqlens && kv != 8 ? 20 : head_dim == 64 ? 28 : 32;      // the line where nearly every place is taken
-    const bool split = dispatch_rows(p) <= 65536 && (n128 <= 256 || (p.causal && p.mkv >= (n128 <= 400 ? 20 : n128 <= 512 ? taken : 64)));
+    const bool split = dispatch_rows(p) <= 65536 && ((n128 <= 256 && (block_m == 128 || p.mkv >= 8)) || (p.causal && p.mkv >= (n128 <= 400 ? 20 : n128 <= 512 ? taken : 64)));
     return {split ? 2 : 1, false};
+}
+
+// Whether a 64-row tile that shares its workgroup with no other head is left alone, and not put together with the next one:
+// where that takes no more rounds of workgroups (`one`, `pair`: places of the chip for tiles alone and for pairs); with
+// elements of different lengths, whose workgroups are fewer than that, up to `lengths` tiles and where there is no next one.
+static bool tile_alone(const FwdParams &p, int64_t one, int64_t pair, int64_t lengths)
+{
+    const int64_t n64 = workgroups_of(p, 64), n128 = workgroups_of(p, 128);
+    return p.seqlens ? n64 <= lengths || p.seqlen <= 64 : (n64 + one - 1) / one <= (n128 + pair - 1) / pair;
 }
 
 bool rewrites_v(const FwdParams &p, int head_dim, int block_m)
@@ -1259,7 +1281,8 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
     if (block_m == 64) {
         if (d128 && split.narrow) return launch_fwd<128, 2, 1, 1, 2, 2>(p, stream);
         if (d128 && split.shares == 2) return launch_fwd<128, 2, 1, 2, 2, 2>(p, stream);
-        if (d128) return two ? launch_fwd<128, 2, 2, 1, 1, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 1, 2>(p, stream);
+        if (d128 && two) return launch_fwd<128, 2, 2, 1, 1, 2>(p, stream);
+        if (d128) return tile_alone(p, 512, 512, p.mkv >= 12 ? 1152 : p.mkv >= 8 ? 1024 : 768) ? launch_fwd<128, 2, 1, 1, 1, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 1, 2>(p, stream);
         if (split.shares > 1) return split.shares == 4 ? launch_fwd<64, 2, 1, 1, 4, 2>(p, stream) : launch_fwd<64, 2, 1, 1, 2, 2>(p, stream);
         if ((p.seqlens && rows <= 262144 && (two || p.group == 1)) || (!two && p.mq == 1)) return launch_fwd<64, 2, 1, 1, 1, 2>(p, stream);
         return two ? launch_fwd<64, 2, 2, 1, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 2, 1, 4>(p, stream);

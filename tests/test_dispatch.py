@@ -12,3 +12,18 @@ from tests import dispatch
 ])
 def test_split_where_nearly_every_place_is_taken(b, n, hq, hkv, d, seqlens, shares):
     assert dispatch.forward(b, n, hq, hkv, d, 128, seqlens=seqlens).shares == shares
+
+
+@pytest.mark.parametrize("b, n, hq, hkv, seqlens, tiles, shares", [
+    (64, 100, 3, 3, False, 1, 1), (8, 250, 12, 4, False, 1, 1), (24, 190, 6, 2, False, 1, 1), (300, 60, 3, 1, False, 1, 1), (2000, 10, 3, 3, False, 1, 1),
+    (4, 900, 16, 16, True, 1, 1), (3, 3000, 8, 8, True, 1, 1), (8, 500, 12, 4, True, 1, 1), (8, 500, 16, 16, True, 1, 1), (32, 200, 3, 1, True, 1, 1),
+    (64, 130, 3, 3, False, 2, 1), (4, 600, 28, 4, True, 2, 1), (16, 300, 12, 4, True, 2, 1), (2, 5000, 16, 16, True, 2, 1), (4, 450, 12, 4, False, 2, 2),
+])
+def test_64_row_tiles_of_width_128(b, n, hq, hkv, seqlens, tiles, shares):
+    """Tiles of an odd group: alone or with the next one in a workgroup."""
+    x = dispatch.forward(b, n, hq, hkv, 128, 64, seqlens=seqlens)
+    assert (x.tiles, x.shares) == (tiles, shares)
+
+
+def test_short_chains_of_shared_heads_are_not_split():
+    assert dispatch.forward(64, 100, 4, 2, 128, 64)[3:6] == (2, 1, 1) and dispatch.forward(40, 200, 3, 1, 128, 32).shares == 1
