@@ -1190,10 +1190,14 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    from 12 on 1152 (4 x up to 900 tokens of 16 heads, 960, 21.1 / 23.4; 3 x up to 3000 of 8, 1128, 50.0 / 56.1; 8 x up to 500 of 12
 //    over 4, 768, 15.1 / 16.7, of 16, 1024, 16.5 / 17.2; 16 x up to 300, 960, 15.1 / 13.3; 4 x up to 600 of 28 over 4, 1120, 19.6 / 18.8;
 //    3 x up to 2000 of 16, 1536, 43.2 / 43.3; 2 x up to 5000, 2528, 164 / 126).
-//    A 64-row tile of width 64 is left alone where a sequence is no longer than that (300 x 60 tokens of 3 heads 8.0 / 10.9),
-//    and, with elements of different lengths, up to rows 262 144 (4 x up to 2000 tokens of 16 heads 28.9 / 31.0, 3 x up to 7000
-//    of 8 over 8 86 / 92; 2 x up to 5000 of 32 heads, rows 320 000, 155 / 143), unless three or more heads of an odd group read
-//    the same K and V (2 x up to 5000 of 12 over 4 85 / 79).
+//    A 64-row tile of width 64 of an odd group likewise (four alone or three pairs to a CU), in sequences of four tiles or
+//    fewer also where both take more rounds (64 x 130 tokens of 3 heads, 576 tiles, 8.4 / 9.3; 1000 tokens of 40 over 8, 640,
+//    16.9 / 18.5, dense 19.5 / 20.4; 300 x 60 of 3 heads 8.0 / 11.3; 200 x 180, 1800, 15.1 / 18.5; 150 x 250, 1824, 16.1 / 18.5;
+//    100 x 250, 1248, 14.2 / 13.6; 300 x 90, 3600, 24.6 / 25.3).  With elements of different lengths a tile is left alone up to rows
+//    262 144 where heads are even or on their own (4 x up to 2000 tokens of 16 heads 28.9 / 31.0, 3 x up to 7000 of 8 over 8
+//    86 / 92; 2 x up to 5000 of 32 heads, rows 320 000, 155 / 143), and where three or more heads of an odd group read the same K and
+//    V up to rows 196 608 and 40 key blocks (16 x up to 300 tokens of 28 over 4 15.7 / 18.5; 4 x up to 900 of 12 over 4 16.0 / 18.2; 6 x
+//    up to 2500 41.8 / 43.3; 2 x up to 3000 of 28 over 4 72.2 / 70.5, 2 x up to 5000 of 12 over 4 83 / 78).
 //  - 128-row tiles of head_dim 64: the CU holds three workgroups.  For a causal call of 513 to 768 tiles, which all
 //    three would hold at once, two to a CU are faster beyond 4K tokens (three / two: 8 heads over 8, 12K tokens
 //    165.5 / 155.3; 2 heads, 49K tokens 624 / 590; 28 heads over 4, 3500 tokens 52.8 / 56.4).
@@ -1284,8 +1288,10 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
         if (d128 && two) return launch_fwd<128, 2, 2, 1, 1, 2>(p, stream);
         if (d128) return tile_alone(p, 512, 512, p.mkv >= 12 ? 1152 : p.mkv >= 8 ? 1024 : 768) ? launch_fwd<128, 2, 1, 1, 1, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 1, 2>(p, stream);
         if (split.shares > 1) return split.shares == 4 ? launch_fwd<64, 2, 1, 1, 4, 2>(p, stream) : launch_fwd<64, 2, 1, 1, 2, 2>(p, stream);
-        if ((p.seqlens && rows <= 262144 && (two || p.group == 1)) || (!two && p.mq == 1)) return launch_fwd<64, 2, 1, 1, 1, 2>(p, stream);
-        return two ? launch_fwd<64, 2, 2, 1, 1, 4>(p, stream) : launch_fwd<64, 2, 1, 2, 1, 4>(p, stream);
+        if (two) return p.seqlens && rows <= 262144 ? launch_fwd<64, 2, 1, 1, 1, 2>(p, stream) : launch_fwd<64, 2, 2, 1, 1, 4>(p, stream);
+        const bool alone = p.seqlens ? p.mq == 1 || (p.group == 1 ? rows <= 262144 : rows <= 196608 && p.mkv <= 40)
+                                     : tile_alone(p, 1024, 768, 0) && (p.mq <= 4 || workgroups_of(p, 64) <= 1024);
+        return alone ? launch_fwd<64, 2, 1, 1, 1, 2>(p, stream) : launch_fwd<64, 2, 1, 2, 1, 4>(p, stream);
     }
     if (d128 && split.narrow) return launch_fwd<128, 1, 1, 2, 2, 2>(p, stream);
     if (d128 && split.shares == 2) return launch_fwd<128, 1, 1, 4, 2, 2>(p, stream);

@@ -27,3 +27,14 @@ def test_64_row_tiles_of_width_128(b, n, hq, hkv, seqlens, tiles, shares):
 
 def test_short_chains_of_shared_heads_are_not_split():
     assert dispatch.forward(64, 100, 4, 2, 128, 64)[3:6] == (2, 1, 1) and dispatch.forward(40, 200, 3, 1, 128, 32).shares == 1
+
+
+@pytest.mark.parametrize("b, n, hq, hkv, seqlens, tiles, shares", [
+    (64, 130, 3, 3, False, 1, 1), (1, 1000, 40, 8, False, 1, 1), (200, 180, 3, 1, False, 1, 1), (150, 250, 3, 1, False, 1, 1),
+    (16, 300, 28, 4, True, 1, 1), (4, 900, 12, 4, True, 1, 1), (32, 200, 28, 4, True, 1, 1), (300, 60, 3, 3, False, 1, 1), (4, 2000, 16, 16, True, 1, 1),
+    (100, 250, 3, 1, False, 2, 1), (2, 5000, 12, 4, True, 2, 1), (2, 4096, 12, 4, False, 2, 1), (4, 500, 12, 4, False, 1, 2),
+])
+def test_64_row_tiles_of_width_64(b, n, hq, hkv, seqlens, tiles, shares):
+    """Tiles of an odd group: alone or with the next one in a workgroup."""
+    x = dispatch.forward(b, n, hq, hkv, 64, 64, seqlens=seqlens)
+    assert (x.tiles, x.shares) == (tiles, shares)
