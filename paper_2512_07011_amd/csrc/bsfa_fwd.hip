@@ -1093,9 +1093,9 @@ hipError_t launch_scores(const FwdParams &params, hipStream_t stream)
 #define BSFA_SHAPES_3(F, S) S(128, 4, 2, 1, 4) S(128, 4, 1, 1, 2) S(64, 4, 1, 1, 3) S(128, 2, 2, 1, 2) S(128, 2, 1, 2, 2) S(64, 2, 2, 1, 4) S(64, 2, 1, 2, 4)
 #define BSFA_SHAPES_4(F, S) F(128, 2, 2, 1, 1, 2) F(128, 2, 1, 2, 1, 2) F(128, 2, 1, 1, 1, 2)
 #define BSFA_SHAPES_5(F, S) F(128, 2, 1, 2, 2, 2) F(128, 2, 1, 1, 2, 2) F(64, 2, 1, 1, 4, 2)
-#define BSFA_SHAPES_6(F, S) F(64, 2, 2, 1, 1, 4) F(64, 2, 1, 2, 1, 4) F(64, 2, 1, 1, 1, 2) F(64, 2, 1, 1, 2, 2)
+#define BSFA_SHAPES_6(F, S) F(64, 1, 2, 1, 1, 2) F(128, 1, 2, 1, 1, 2) F(64, 2, 2, 1, 1, 4) F(64, 2, 1, 2, 1, 4) F(64, 2, 1, 1, 1, 2) F(64, 2, 1, 1, 2, 2)
 #define BSFA_SHAPES_7(F, S) F(128, 1, 4, 1, 1, 2) F(128, 1, 2, 2, 1, 2) F(128, 1, 1, 4, 1, 2)
-#define BSFA_SHAPES_8(F, S) F(128, 1, 1, 4, 2, 2) F(128, 1, 1, 2, 2, 2) F(64, 1, 1, 2, 4, 2)
+#define BSFA_SHAPES_8(F, S) F(64, 1, 1, 2, 1, 2) F(64, 1, 1, 1, 1, 2) F(128, 1, 1, 4, 2, 2) F(128, 1, 1, 2, 2, 2) F(64, 1, 1, 2, 4, 2)
 #define BSFA_SHAPES_9(F, S) F(64, 1, 4, 1, 1, 4) F(64, 1, 2, 2, 1, 4) F(64, 1, 1, 4, 1, 4) F(64, 1, 1, 2, 2, 2)
 #define BSFA_SHAPES_10(F, S) S(128, 1, 4, 1, 2) S(128, 1, 2, 2, 2) S(128, 1, 1, 4, 2) S(64, 1, 4, 1, 4) S(64, 1, 2, 2, 4) S(64, 1, 1, 4, 4)
 #define BSFA_EXTERN_F(D, N, H, Q, P, K) extern template hipError_t launch_fwd<D, N, H, Q, P, K>(const FwdParams &, hipStream_t, unsigned);
@@ -1198,6 +1198,13 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    86 / 92; 2 x up to 5000 of 32 heads, rows 320 000, 155 / 143), and where three or more heads of an odd group read the same K and
 //    V up to rows 196 608 and 40 key blocks (16 x up to 300 tokens of 28 over 4 15.7 / 18.5; 4 x up to 900 of 12 over 4 16.0 / 18.2; 6 x
 //    up to 2500 41.8 / 43.3; 2 x up to 3000 of 28 over 4 72.2 / 70.5, 2 x up to 5000 of 12 over 4 83 / 78).
+//    A workgroup of several 32-row tiles has waves without one where a sequence is a single tile: heads alone share there (one
+//    tile / several: 2000 x 10 tokens of 4 over 2 41.4 / 47.1, of width 64 21.7 / 30.3; width 64, of 3 heads 24.4 / 40.2, 300 x 30 tokens
+//    6.2 / 10.3; four heads or, up to 1024 heads, two: 64 x 20 of 8 over 2 6.3 / 5.4, 300 x 30 10.0 / 10.8).  Tiles of width 64 of an odd
+//    group are put together in twos or fours as 64-row tiles are alone or together: (twos / fours: 64 x 130 tokens of 3 heads 7.8 / 9.1,
+//    1000 of 40 over 8 17.5 / 19.1, 200 x 180 of 3 over 1 15.8 / 18.7, 100 x 250 14.9 / 13.5), with elements of different lengths up to
+//    rows 81 920 or six key blocks (4 x up to 900 tokens of 16 heads 17.1 / 18.3, 3 x up to 3000 of 8 40.1 / 42.8, 16 x up to 300 of 28 over
+//    4 16.2 / 18.4; 8 x up to 500 15.2 / 14.3, 2 x up to 5000 of 12 over 4 87 / 80).
 //  - 128-row tiles of head_dim 64: the CU holds three workgroups.  For a causal call of 513 to 768 tiles, which all
 //    three would hold at once, two to a CU are faster beyond 4K tokens (three / two: 8 heads over 8, 12K tokens
 //    165.5 / 155.3; 2 heads, 49K tokens 624 / 590; 28 heads over 4, 3500 tokens 52.8 / 56.4).
@@ -1295,9 +1302,15 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
     }
     if (d128 && split.narrow) return launch_fwd<128, 1, 1, 2, 2, 2>(p, stream);
     if (d128 && split.shares == 2) return launch_fwd<128, 1, 1, 4, 2, 2>(p, stream);
+    const bool one_tile = p.mq == 1;                       // (then a workgroup of several tiles would have waves without one)
+    if (d128 && two && !four && one_tile) return launch_fwd<128, 1, 2, 1, 1, 2>(p, stream);
     if (d128) return four ? launch_fwd<128, 1, 4, 1, 1, 2>(p, stream) : two ? launch_fwd<128, 1, 2, 2, 1, 2>(p, stream) : launch_fwd<128, 1, 1, 4, 1, 2>(p, stream);
     if (split.shares > 1) return split.shares == 4 ? launch_fwd<64, 1, 1, 2, 4, 2>(p, stream) : launch_fwd<64, 1, 1, 2, 2, 2>(p, stream);
-    return four ? launch_fwd<64, 1, 4, 1, 1, 4>(p, stream) : two ? launch_fwd<64, 1, 2, 2, 1, 4>(p, stream) : launch_fwd<64, 1, 1, 4, 1, 4>(p, stream);
+    if (two && one_tile && (!four || workgroups_of(p, 64) <= 1024)) return launch_fwd<64, 1, 2, 1, 1, 2>(p, stream);
+    if (two) return four ? launch_fwd<64, 1, 4, 1, 1, 4>(p, stream) : launch_fwd<64, 1, 2, 2, 1, 4>(p, stream);
+    if (one_tile) return launch_fwd<64, 1, 1, 1, 1, 2>(p, stream);
+    const bool narrow = p.seqlens ? rows <= 81920 || p.mkv <= 6 : tile_alone(p, 1024, 768, 0) && (p.mkv <= 4 || workgroups_of(p, 64) <= 1024);
+    return narrow ? launch_fwd<64, 1, 1, 2, 1, 2>(p, stream) : launch_fwd<64, 1, 1, 4, 1, 4>(p, stream);
 }
 
 #elif BSFA_PART == 1

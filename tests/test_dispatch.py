@@ -38,3 +38,15 @@ def test_64_row_tiles_of_width_64(b, n, hq, hkv, seqlens, tiles, shares):
     """Tiles of an odd group: alone or with the next one in a workgroup."""
     x = dispatch.forward(b, n, hq, hkv, 64, 64, seqlens=seqlens)
     assert (x.tiles, x.shares) == (tiles, shares)
+
+
+@pytest.mark.parametrize("b, n, hq, hkv, d, seqlens, heads, tiles", [
+    (2000, 10, 4, 2, 128, False, 2, 1), (2000, 10, 4, 2, 64, False, 2, 1), (300, 30, 4, 2, 64, False, 2, 1), (2000, 10, 3, 1, 64, False, 1, 1), (300, 30, 3, 3, 64, True, 1, 1),
+    (64, 20, 8, 2, 64, False, 2, 1), (300, 30, 8, 2, 64, False, 4, 1),
+    (64, 130, 3, 3, 64, False, 1, 2), (4, 900, 12, 4, 64, True, 1, 2), (3, 3000, 8, 8, 64, True, 1, 2), (16, 300, 28, 4, 64, True, 1, 2), (200, 180, 3, 1, 64, False, 1, 2),
+    (100, 250, 3, 1, 64, False, 1, 4), (8, 500, 28, 4, 64, True, 1, 4), (1, 8192, 28, 4, 64, False, 1, 4), (300, 60, 4, 2, 64, False, 2, 2), (2000, 10, 3, 1, 128, False, 1, 4),
+])
+def test_32_row_tiles(b, n, hq, hkv, d, seqlens, heads, tiles):
+    """Heads and adjacent tiles of a workgroup, where key blocks are not dealt to several sets of waves."""
+    x = dispatch.forward(b, n, hq, hkv, d, 32, seqlens=seqlens)
+    assert (x.heads, x.tiles, x.shares) == (heads, tiles, 1)

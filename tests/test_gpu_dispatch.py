@@ -160,6 +160,20 @@ SMALL_TILES = [
 ]
 
 
+# tiles alone in a workgroup, in twos and in fours, and heads alone where a sequence is a single tile of 32 rows: the kernels
+# of few or short sequences
+FEW_TILES = [
+    (12, 300, 6, 2, 128, 64, True, "qkv"), (30, 250, 3, 3, 128, 64, True, "bnhd"), (24, 250, 6, 2, 64, 64, True, "qkv"), (48, 192, 3, 1, 128, 64, False, "bnhd"),
+    (2, 31, 4, 2, 128, 32, True, "bnhd"), (2, 32, 4, 2, 64, 32, True, "qkv"), (3, 1, 6, 3, 64, 32, True, "bnhd"), (2, 30, 8, 2, 64, 32, True, "bnhd"),
+    (1, 100, 3, 1, 64, 32, True, "bnhd"), (2, 97, 5, 1, 64, 32, True, "qkv"), (3, 128, 3, 3, 64, 32, False, "bnhd"),
+]
+
+
+@pytest.mark.parametrize("case", FEW_TILES)
+def test_few_tiles_agree_with_every_other_form(case):
+    test_small_calls_agree_with_every_other_form(case)
+
+
 @pytest.mark.parametrize("case", SMALL_TILES)
 def test_small_tiles_agree_with_every_other_form(case):
     test_small_calls_agree_with_every_other_form(case)
