@@ -227,9 +227,13 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
                                 : (uint32_t)((4 * hh + (L >> 2)) * v_pitch(D) + 2 * G16_COLS * g16 + 8 * (L & 3));
 
     // All K tiles the ring holds are requested before anything else, and what follows block 0 (V_0, K_{R-1}) is left
-    // in flight for the first stage: one trip to memory before the pipeline starts instead of two.
+    // in flight for the first stage: one trip to memory before the pipeline starts instead of two.  A longer ring leaves out
+    // what does not exist, which the only tile of a short sequence would wait for (us with / without the requests: 2000 x 10
+    // tokens of 8 heads of width 64, ring of 3, 106.7 / 94.8, 300 x 60 21.9 / 20.2, ring of 4 34.7 / 33.5); with two slots the
+    // branch costs more than that (100 x 250 tokens of 3 heads 23.5 / 24.1), and a branch for each tile of four, too (58.0 / 58.5).
 #pragma unroll
-    for (int t = 0; t < KR; ++t) copy_k(t, lds_k0 + (uint32_t)t * KSLOT);
+    for (int t = 0; t < KR; ++t)
+        if (KR == 2 || t == 0 || n_own > (t < 2 ? 1 : 2)) copy_k(t, lds_k0 + (uint32_t)t * KSLOT);
 
     // Q_i^T as the B operand: lane holds query (32*wrow + l32), head-dim slice 16s + 8hh .. +7
     // (QK8: slice 64s + 32hh .. +31, rounded to fp8 here, once)
