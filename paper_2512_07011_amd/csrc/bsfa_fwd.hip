@@ -306,8 +306,11 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     constexpr int PD = 4;            // LDS operand reads are issued PD MFMAs ahead of their use (3 to 6 measure within 1 %)
     // ... of the score operands: the fp8 ones are twice as wide and four in all; with three waves to a SIMD four of them
     // are more than the 168 registers hold, and what is spilled comes back inside the loop behind a wait for every copy
-    // in flight (8K tokens, 32 heads of width 64, half skip: 256 us with four, 233 with three, 230 with two).
-    constexpr int PDK = QK8 || (!CALIB && min_waves(D, NW, KSP * SHARE) == 3) ? 2 : PD;
+    // in flight (8K tokens, 32 heads of width 64, half skip: 256 us with four, 233 with three, 230 with two).  The score half
+    // alone has four waves on a SIMD to hide the reads, and at head_dim 128 the LDS is as busy as the matrix pipe there: fewer
+    // reads at a time (a calibration on 6000 tokens of 32 heads over 8, four / two, us: 32-row tiles 159.0 / 155.8, 64-row tiles
+    // 144.5 / 141.7, 128-row tiles 140.0 / 137.7; 3000 tokens of 3 heads 36.2 / 35.6; at worst 5000 tokens of 32 heads 102.8 / 104.1).
+    constexpr int PDK = QK8 || (CALIB ? D == 128 : min_waves(D, NW, KSP * SHARE) == 3) ? 2 : PD;
     // The first PDK score operands of a block are read one phase early (at the end of the previous
     // stage, behind its last MFMAs), so that the score MFMAs do not start with an LDS round trip.
     kop_t kpre[PDK];
