@@ -1097,7 +1097,7 @@ hipError_t launch_scores(const FwdParams &params, hipStream_t stream)
 // F(head_dim, waves per head and tile, heads, tiles, shares of the key blocks, K ring), S(head_dim, waves per head and tile, heads, tiles, K ring)
 #define BSFA_SHAPES_1(F, S) F(128, 4, 1, 1, 1, 2) F(128, 4, 2, 1, 1, 5)
 #define BSFA_SHAPES_2(F, S) F(128, 4, 1, 1, 2, 2) F(64, 4, 1, 1, 1, 3) F(64, 4, 1, 1, 2, 3)
-#define BSFA_SHAPES_3(F, S) S(128, 4, 2, 1, 4) S(128, 4, 1, 1, 2) S(64, 4, 1, 1, 3) S(128, 2, 2, 1, 2) S(128, 2, 1, 2, 2) S(64, 2, 2, 1, 4) S(64, 2, 1, 2, 4)
+#define BSFA_SHAPES_3(F, S) S(128, 4, 2, 1, 4) S(128, 4, 1, 1, 2) S(64, 4, 1, 1, 3) S(128, 2, 2, 1, 2) S(128, 2, 1, 2, 2) S(64, 2, 2, 1, 4) S(64, 2, 1, 2, 4) S(128, 2, 1, 1, 2) S(64, 2, 1, 1, 2)
 #define BSFA_SHAPES_4(F, S) F(128, 2, 2, 1, 1, 2) F(128, 2, 1, 2, 1, 2) F(128, 2, 1, 1, 1, 2)
 #define BSFA_SHAPES_5(F, S) F(128, 2, 1, 2, 2, 2) F(128, 2, 1, 1, 2, 2) F(64, 2, 1, 1, 4, 2)
 #define BSFA_SHAPES_6(F, S) F(64, 1, 2, 1, 1, 2) F(128, 1, 2, 1, 1, 2) F(64, 2, 2, 1, 1, 4) F(64, 2, 1, 2, 1, 4) F(64, 2, 1, 1, 1, 2) F(64, 2, 1, 1, 2, 2)
@@ -1218,7 +1218,9 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //  - The score half alone (calibration) has registers and LDS to spare and shares where it can.  128-row tiles from
 //    rows 262 144 on (whole calibrations, single / pairs: 8K tokens 268.9 / 270.3, 16K 913 / 904); 64-row tiles always
 //    (500 tokens 46.0 / 46.4, 16K 1106 / 922; head_dim 64 595 / 541); 32-row tiles four (16K single 1571, pairs 1093,
-//    four 919; head_dim 64 748, 682, 542; up to 1000 tokens all within 1 us).
+//    four 919; head_dim 64 748, 682, 542; up to 1000 tokens all within 1 us).  64-row tiles of an odd group are alone up to 256
+//    tiles, at head_dim 64 and in sequences of up to four 512 (589 tokens of 12 over 4, 120 tiles, alone / in twos 16.5 / 17.3, head_dim 64 14.8 / 15.8; 800 of 28
+//    over 4, 364, 19.0 / 18.8, 16.6 / 16.8; 8 x 200 of 12 over 4, 384, 21.1 / 21.5, 20.1 / 20.8).
 // Results do not depend on how heads share; the split does change the order of sums, so it must not depend on
 // single_head or on the workspace, between which results are equal bit for bit.
 static int64_t dispatch_rows(const FwdParams &p) { return (int64_t)p.batch * p.hq * p.seqlen * (p.causal ? 1 : 2); }
@@ -1281,6 +1283,8 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
         if (block_m == 128)
             return !d128 ? launch_scores<64, 4, 1, 1, 3>(p, stream)
                  : two && rows > 262144 ? launch_scores<128, 4, 2, 1, 4>(p, stream) : launch_scores<128, 4, 1, 1, 2>(p, stream);
+        if (block_m == 64 && !two && workgroups_of(p, 64) <= (d128 && p.mq > 4 ? 256 : 512))
+            return d128 ? launch_scores<128, 2, 1, 1, 2>(p, stream) : launch_scores<64, 2, 1, 1, 2>(p, stream);
         if (block_m == 64)
             return d128 ? (two ? launch_scores<128, 2, 2, 1, 2>(p, stream) : launch_scores<128, 2, 1, 2, 2>(p, stream))
                         : (two ? launch_scores<64, 2, 2, 1, 4>(p, stream) : launch_scores<64, 2, 1, 2, 4>(p, stream));

@@ -50,3 +50,11 @@ def test_32_row_tiles(b, n, hq, hkv, d, seqlens, heads, tiles):
     """Heads and adjacent tiles of a workgroup, where key blocks are not dealt to several sets of waves."""
     x = dispatch.forward(b, n, hq, hkv, d, 32, seqlens=seqlens)
     assert (x.heads, x.tiles, x.shares) == (heads, tiles, 1)
+
+
+@pytest.mark.parametrize("b, n, hq, hkv, d, tiles", [
+    (1, 589, 12, 4, 128, 1), (1, 589, 12, 4, 64, 1), (16, 100, 3, 1, 128, 1), (8, 200, 12, 4, 64, 1), (8, 200, 12, 4, 128, 1), (1, 800, 28, 4, 128, 2), (1, 3000, 28, 4, 64, 2),
+])
+def test_score_half_of_64_row_tiles(b, n, hq, hkv, d, tiles):
+    x = dispatch.scores(b, n, hq, hkv, d, 64)
+    assert x.score and (x.heads, x.tiles) == (1, tiles)

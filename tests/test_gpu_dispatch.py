@@ -257,6 +257,33 @@ def test_order_statistics_on_both_selections(b, n, n_levels, equal):
             assert float(got[l, h]) == want, (h, f)
 
 
+# (b, n, hq, hkv, d, bm): score kernels with a tile, two and four of them, with and without other heads, to a workgroup
+SCORES = [
+    (1, 589, 12, 4, 128, 64), (1, 300, 3, 3, 64, 64), (2, 65, 5, 1, 128, 64), (1, 1100, 28, 4, 128, 64), (1, 1700, 28, 4, 64, 64), (1, 193, 4, 2, 128, 64), (1, 200, 4, 2, 64, 64),
+    (1, 450, 3, 1, 128, 32), (1, 290, 3, 1, 64, 32), (1, 161, 4, 2, 128, 32), (1, 161, 4, 2, 64, 32), (1, 450, 8, 2, 128, 32), (2, 225, 8, 2, 64, 32), (1, 700, 3, 1, 128, 128),
+    (1, 700, 3, 1, 64, 128), (1, 8300, 32, 8, 128, 128),
+]
+
+
+@pytest.mark.parametrize("b, n, hq, hkv, d, bm", SCORES)
+def test_every_score_kernel_gives_the_forward_kernels_maxima(b, n, hq, hkv, d, bm):
+    """Order statistics of a calibration against a sort of the block maxima that a forward call dumps, bit for bit, without and
+    with lengths (of which every element but the first is shorter)."""
+    q, k, _ = make(b, n, hq, hkv, d, "bnhd", torch.float16, n)
+    fr = [0.0, 0.125, 0.5, 0.75, 1.0]
+    for lengths in (None, torch.tensor([n] + [max(1, n // 2 - 3)] * (b - 1), dtype=torch.int32, device=DEV)):
+        got = binding.bsfa_calibrate(q, k, fr, block_m=bm, seqlens=lengths)
+        st = binding.alloc_stats(q, bm, 64, counts=False, block_max=True)
+        binding.bsfa_forward(q, k, k, torch.full((hq,), float("-inf"), device=DEV), skip_stats=st, block_m=bm, seqlens=lengths)
+        for h in range(hq):
+            x = st.block_max[:, h].reshape(-1)
+            x = torch.sort(x[~x.isnan()])[0].cpu()
+            for l, f in enumerate(fr):
+                r = int(f * len(x))
+                want = float("-inf") if r == 0 else float("inf") if r >= len(x) else float(x[r])
+                assert float(got[l, h]) == want, (h, f)
+
+
 def test_running_maximum_over_large_score_ranges():
     """Rows whose maximum grows with every block, only in the first one, and hardly at all, with scores of several
     hundred: finite, and equal to softmax in 64 bits (2e-2, the bound of every parity test; for lse the rounding of P
