@@ -100,3 +100,11 @@ def scores(b, n, hq, hkv, d, bm, causal=True):
     rc = lib.bsfa_calibrate_topk(ctypes.byref(p), a, a, int(causal), ctypes.byref(k), 1, 0, a, a, ctypes.c_size_t(1 << 50), None)
     assert rc == -6 and b"selection launch failed" in lib.bsfa_last_error()
     return _noted(lib, 0)
+
+
+def instantiated():
+    """The first seven members of a Launch, for every form that the library holds."""
+    src = open(os.path.join(build.CSRC, "bsfa_fwd.hip")).read()
+    lists = "".join(re.findall(r"#define BSFA_SHAPES_\d+\(F, S\)(.*)", src))
+    forward_forms = {(False, *map(int, x)) for x in re.findall(r"F\((\d+), (\d), (\d), (\d), (\d), (\d)\)", lists)}
+    return forward_forms | {(True, *map(int, x[:4]), 1, int(x[4])) for x in re.findall(r"S\((\d+), (\d), (\d), (\d), (\d)\)", lists)}

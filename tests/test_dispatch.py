@@ -3,6 +3,7 @@ the claims that tests on the GPU make about the kernels their calls are sent to.
 import pytest
 
 from tests import dispatch
+from tests import test_gpu_dispatch as on_gpu
 
 
 @pytest.mark.parametrize("b, n, hq, hkv, d, seqlens, shares", [
@@ -58,3 +59,30 @@ def test_32_row_tiles(b, n, hq, hkv, d, seqlens, heads, tiles):
 def test_score_half_of_64_row_tiles(b, n, hq, hkv, d, tiles):
     x = dispatch.scores(b, n, hq, hkv, d, 64)
     assert x.score and (x.heads, x.tiles) == (1, tiles)
+
+
+@pytest.mark.parametrize("hq, hkv, n, d, bm, causal, fp8, dtype", on_gpu.SHARED_HEADS)
+def test_shared_heads_are_compared_with_single_ones(hq, hkv, n, d, bm, causal, fp8, dtype):
+    kw = dict(causal=causal, qk_fp8=fp8, workspace=True)
+    shared, single = dispatch.forward(1, n, hq, hkv, d, bm, **kw), dispatch.forward(1, n, hq, hkv, d, bm, single_head=True, **kw)
+    assert shared.heads > 1 and single.heads == 1 and shared.shares == single.shares == 1
+
+
+@pytest.mark.parametrize("b, n, hq, hkv, d, bm", on_gpu.TURNED)
+def test_turned_places_are_compared_with_places_in_order(b, n, hq, hkv, d, bm):
+    plain, counted = dispatch.forward(b, n, hq, hkv, d, bm), dispatch.forward(b, n, hq, hkv, d, bm, seqlens=True)
+    assert plain.turn[1] > plain.turn[0] > 0 and counted.turn == (0, 0, 0) and plain.shares == counted.shares == 1
+
+
+def test_every_kernel_is_run_by_the_comparisons_of_forms():
+    """Every instantiated form, by the calls that are compared with each other on the GPU."""
+    ran = set()
+    for b, n, hq, hkv, d, bm, causal, _ in on_gpu.CASES + on_gpu.SMALL_TILES + on_gpu.FEW_TILES:
+        many = b * (1 + 150000 // (b * hq * n * (1 if causal else 2)))
+        ran |= {dispatch.forward(b, n, hq, hkv, d, bm, causal), dispatch.forward(b, n, hq, hkv, d, bm, causal, single_head=True),
+                dispatch.forward(many, n, hq, hkv, d, bm, causal)}
+    for hq, hkv, n, d, bm, causal, fp8, _ in on_gpu.SHARED_HEADS:
+        ran |= {dispatch.forward(1, n, hq, hkv, d, bm, causal, single_head=x, qk_fp8=fp8, workspace=True) for x in (False, True)}
+    ran |= {dispatch.scores(*x) for x in on_gpu.SCORES}
+    forms = dispatch.instantiated()
+    assert len(forms) >= 40 and not forms - {x[:7] for x in ran}
