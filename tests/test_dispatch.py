@@ -4,6 +4,7 @@ import pytest
 
 from tests import dispatch
 from tests import test_gpu_dispatch as on_gpu
+from tests import test_gpu_small_tiles as on_small_tiles
 
 
 @pytest.mark.parametrize("b, n, hq, hkv, d, seqlens, shares", [
@@ -86,3 +87,15 @@ def test_every_kernel_is_run_by_the_comparisons_of_forms():
     ran |= {dispatch.scores(*x) for x in on_gpu.SCORES}
     forms = dispatch.instantiated()
     assert len(forms) >= 40 and not forms - {x[:7] for x in ran}
+
+
+@pytest.mark.parametrize("hq, hkv, d, bm", on_small_tiles.PREDICATE)
+def test_the_predicate_meets_adjacent_tiles(hq, hkv, d, bm):
+    x = dispatch.forward(on_small_tiles.PREDICATE_BATCH, on_small_tiles.PREDICATE_TOKENS, hq, hkv, d, bm, gate_mode=1)
+    assert x.tiles == 128 // bm and x.shares == 1 and (on_small_tiles.PREDICATE_TOKENS // bm) % x.tiles
+
+
+@pytest.mark.parametrize("hq, hkv, d, bm", on_small_tiles.WITH_LENGTHS)
+def test_lengths_meet_adjacent_tiles(hq, hkv, d, bm):
+    x = dispatch.forward(len(on_small_tiles.LENGTHS), max(on_small_tiles.LENGTHS), hq, hkv, d, bm, seqlens=True)
+    assert x.tiles == 128 // bm and x.shares == 1

@@ -60,7 +60,7 @@ def test_small_calls_agree_with_every_other_form(case):
             assert torch.equal(x, y)
     if n > 256:
         assert alone[2][..., 0].sum() > 0                   # something is skipped
-    times = 1 + 150000 // (b * hq * n * (1 if causal else 2))    # (calls split tiles up to 65536 query rows over all heads)
+    times = 1 + 150000 // (b * hq * n * (1 if causal else 2))    # (calls split tiles up to 98304 query rows over all heads)
     many = call(*(t.repeat(times, 1, 1, 1) for t in (q, k, v)), tau, bm, causal)
     for lo in (0, (times - 1) * b):
         out, lse, counts, mask = (x[lo:lo + b] for x in many)
