@@ -211,6 +211,8 @@ __device__ __forceinline__ int row_sum16(int x)
 // (the others follow, for their empty statistics): consecutive workgroups are dealt to the parts of an XCD in turn, and
 // with gaps of a regular distance between them all of the longest element's late tiles fell to the same part (4 x up to
 // 4000 tokens of 16 heads of width 64 over 8, heads in pairs: 107 us, 63 this way; 2 x up to 5000 of 32 heads: 166, 139).
+// (Up to 256 workgroups, one to a CU, there is nothing to deal, and the counting takes half a microsecond: 4 x up to 54
+// tokens of 28 heads over 4 9.2 us with, 8.7 without.  More than 16 pairs to an XCD do not fit a row of lanes.)
 // With c the tiles of each pair, S(t) = sum of max(0, c - t) items lie in the rows of tiles from t up.  Item x is in row
 // t = the last with S(t) > x; the pairs that row holds are those with S(c) <= x (a lane each), and with their number k
 // S(t) = sum of their c - k t.
@@ -229,7 +231,7 @@ __device__ __forceinline__ bool decode_work(const FwdParams &p, uint32_t w, int 
     const int tiles = (p.mq + QT - 1) / QT;
     int pl, t;
     uint32_t sub;
-    if (p.seqlens && npx <= 16) {
+    if (p.counted) {
         const int lane = threadIdx.x & 63, mine = pairs >= 8 ? (int)(w & 7) + 8 * lane : lane;
         const bool valid = lane < npx && mine < pairs;
         const int n = valid ? min(max(p.seqlens[p.div_hkv.of((uint32_t)mine)], 0), p.seqlen) : 0;
@@ -268,7 +270,7 @@ __device__ __forceinline__ bool decode_work(const FwdParams &p, uint32_t w, int 
     if (g >= pairs) return false;
     b = (int)p.div_hkv.of((uint32_t)g);
     if (!p.seqlens) n_tok = p.seqlen;
-    else if (npx > 16) n_tok = min(max(__builtin_amdgcn_readfirstlane(p.seqlens[b]), 0), p.seqlen);
+    else if (!p.counted) n_tok = min(max(__builtin_amdgcn_readfirstlane(p.seqlens[b]), 0), p.seqlen);
     g -= b * p.hkv;
     h0 = g * p.group + (int)sub * HP;
     i = t * QT;

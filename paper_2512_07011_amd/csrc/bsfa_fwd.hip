@@ -996,7 +996,9 @@ template <int HP, int QT> static unsigned decompose(FwdParams &p)
     p.div_gsub = fast_div((uint32_t)gsub);
     p.div_hkv = fast_div((uint32_t)p.hkv);
     p.turn[0] = p.turn[1] = p.turn[2] = 0;
-    return (unsigned)(per_tile * wide * mqg);
+    const unsigned n = (unsigned)(per_tile * wide * mqg);
+    p.counted = p.seqlens && pairs <= 128 && n > 256;
+    return n;
 }
 
 // K -> workspace as fp8 tiles and V -> workspace as transposed tiles, as far as the call has room for them
@@ -1193,9 +1195,10 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    over 4, 9151 tokens in 32-row tiles 570 / 254; width 64, 28 over 4, 8192 tokens 240 / 218, 355 / 222).
 //    A 64-row tile of width 128 is left alone where every tile has a place, and where a sequence is a single tile (alone / with
 //    the next: 24 x 190 tokens of 6 over 2, 432 tiles, 10.8 / 11.9; 300 x 60 of 3 over 1, 904, 14.0 / 16.5; 64 x 130 of 3 heads, 576,
-//    12.6 / 11.7), and with elements of different lengths, which leave places free, up to 768 tiles, from 8 key blocks on 1024,
+//    12.6 / 11.7), and with elements of different lengths, which leave places free, up to 640 tiles, from 8 key blocks on 1024,
 //    from 12 on 1152 (4 x up to 900 tokens of 16 heads, 960, 21.1 / 23.4; 3 x up to 3000 of 8, 1128, 50.0 / 56.1; 8 x up to 500 of 12
-//    over 4, 768, 15.1 / 16.7, of 16, 1024, 16.5 / 17.2; 16 x up to 300, 960, 15.1 / 13.3; 4 x up to 600 of 28 over 4, 1120, 19.6 / 18.8;
+//    over 4, 768, 15.1 / 16.7, of 16, 1024, 16.5 / 17.2; 100 x up to 100 of 3 over 1, 624, 9.5 / 11.3; 64 x up to 127 of 6 over 2, 768, 14.2 /
+//    12.4; 16 x up to 300 of 12 over 4, 960, 15.1 / 13.3; 4 x up to 600 of 28 over 4, 1120, 19.6 / 18.8;
 //    3 x up to 2000 of 16, 1536, 43.2 / 43.3; 2 x up to 5000, 2528, 164 / 126).
 //    A 64-row tile of width 64 of an odd group likewise (four alone or three pairs to a CU), in sequences of four tiles or
 //    fewer also where both take more rounds (64 x 130 tokens of 3 heads, 576 tiles, 8.4 / 9.3; 1000 tokens of 40 over 8, 640,
@@ -1203,7 +1206,8 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    100 x 250, 1248, 14.2 / 13.6; 300 x 90, 3600, 24.6 / 25.3).  With elements of different lengths a tile is left alone up to rows
 //    262 144 where heads are even or on their own (4 x up to 2000 tokens of 16 heads 28.9 / 31.0, 3 x up to 7000 of 8 over 8
 //    86 / 92; 2 x up to 5000 of 32 heads, rows 320 000, 155 / 143), and where three or more heads of an odd group read the same K and
-//    V up to rows 196 608 and 40 key blocks (16 x up to 300 tokens of 28 over 4 15.7 / 18.5; 4 x up to 900 of 12 over 4 16.0 / 18.2; 6 x
+//    V up to rows 196 608 and 40 key blocks, and in sequences of up to two tiles (100 x up to 100 tokens of 3 heads 7.6 / 9.4, 300 x up to 128
+//    12.7 / 14.6; 16 x up to 300 tokens of 28 over 4 15.7 / 18.5; 4 x up to 900 of 12 over 4 16.0 / 18.2; 6 x
 //    up to 2500 41.8 / 43.3; 2 x up to 3000 of 28 over 4 72.2 / 70.5, 2 x up to 5000 of 12 over 4 83 / 78).
 //    A workgroup of several 32-row tiles has waves without one where a sequence is a single tile: heads alone share there (one
 //    tile / several: 2000 x 10 tokens of 4 over 2 41.4 / 47.1, of width 64 21.7 / 30.3; width 64, of 3 heads 24.4 / 40.2, 300 x 30 tokens
@@ -1304,10 +1308,10 @@ hipError_t launch_forward(const FwdParams &p, int head_dim, int block_m, bool ca
         if (d128 && split.narrow) return launch_fwd<128, 2, 1, 1, 2, 2>(p, stream);
         if (d128 && split.shares == 2) return launch_fwd<128, 2, 1, 2, 2, 2>(p, stream);
         if (d128 && two) return launch_fwd<128, 2, 2, 1, 1, 2>(p, stream);
-        if (d128) return tile_alone(p, 512, 512, p.mkv >= 12 ? 1152 : p.mkv >= 8 ? 1024 : 768) ? launch_fwd<128, 2, 1, 1, 1, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 1, 2>(p, stream);
+        if (d128) return tile_alone(p, 512, 512, p.mkv >= 12 ? 1152 : p.mkv >= 8 ? 1024 : 640) ? launch_fwd<128, 2, 1, 1, 1, 2>(p, stream) : launch_fwd<128, 2, 1, 2, 1, 2>(p, stream);
         if (split.shares > 1) return split.shares == 4 ? launch_fwd<64, 2, 1, 1, 4, 2>(p, stream) : launch_fwd<64, 2, 1, 1, 2, 2>(p, stream);
         if (two) return p.seqlens && rows <= 262144 ? launch_fwd<64, 2, 1, 1, 1, 2>(p, stream) : launch_fwd<64, 2, 2, 1, 1, 4>(p, stream);
-        const bool alone = p.seqlens ? p.mq == 1 || (p.group == 1 ? rows <= 262144 : rows <= 196608 && p.mkv <= 40)
+        const bool alone = p.seqlens ? p.mq <= 2 || (p.group == 1 ? rows <= 262144 : rows <= 196608 && p.mkv <= 40)
                                      : tile_alone(p, 1024, 768, 0) && (p.mq <= 4 || workgroups_of(p, 64) <= 1024);
         return alone ? launch_fwd<64, 2, 1, 1, 1, 2>(p, stream) : launch_fwd<64, 2, 1, 2, 1, 4>(p, stream);
     }

@@ -53,6 +53,7 @@ struct FwdParams {
     int mask_words;
     FastDiv div_tile, div_gsub, div_hkv;   // work decomposition (decode_work): work items per query tile, head groups per
                                            // KV head, KV heads; set by the launch
+    int counted;                     // work items that exist are counted off first (decode_work); set by the launch
     uint32_t turn[3];                // workgroups turn[0] .. turn[1] - 1 of an XCD, and from there to turn[2] - 1, take their
                                      // work items in reverse (decode_work); set by the launch
 };

@@ -17,7 +17,7 @@ SRC = r"""
 #include "bsfa_fwd.hip"
 #undef launch_fwd
 #undef launch_scores
-static int noted[14];
+static int noted[15];
 extern "C" const int *last_launch() { return noted; }
 namespace bsfa {
 template <int D, int NWH, int HP, int QT, int KSP, int KR> hipError_t launch_fwd(const FwdParams &params, hipStream_t, unsigned spare)
@@ -25,15 +25,15 @@ template <int D, int NWH, int HP, int QT, int KSP, int KR> hipError_t launch_fwd
     FwdParams p = params;
     const unsigned grid = decompose<HP, QT>(p);
     turned_places(p, grid, std::min(places_of(D, NWH * HP * QT, KSP), spare ? 2 : 3));
-    const int now[14] = {0, D, NWH, HP, QT, KSP, KR, (int)spare, (int)grid, (int)p.turn[0], (int)p.turn[1], (int)p.turn[2], p.vt != nullptr, p.k8 != nullptr};
-    std::copy(now, now + 14, noted);
+    const int now[15] = {0, D, NWH, HP, QT, KSP, KR, (int)spare, (int)grid, (int)p.turn[0], (int)p.turn[1], (int)p.turn[2], p.vt != nullptr, p.k8 != nullptr, p.counted};
+    std::copy(now, now + 15, noted);
     return hipSuccess;
 }
 template <int D, int NWH, int HP, int QT, int KR> hipError_t launch_scores(const FwdParams &params, hipStream_t)
 {
     FwdParams p = params;
-    const int now[14] = {1, D, NWH, HP, QT, 1, KR, 0, (int)decompose<HP, QT>(p)};
-    std::copy(now, now + 14, noted);
+    const int now[15] = {1, D, NWH, HP, QT, 1, KR, 0, (int)decompose<HP, QT>(p)};
+    std::copy(now, now + 15, noted);
     return hipSuccess;
 }
 %s
@@ -44,8 +44,8 @@ hipError_t launch_mfma_rate_probe(const float *, float *, int, int, hipStream_t)
 }
 """
 
-# score: the score half alone (calibration); tiles: adjacent query tiles of a workgroup; turn: see turned_places
-Launch = namedtuple("Launch", "score head_dim waves heads tiles shares ring spare grid turn vt k8")
+# score: the score half alone (calibration); tiles: adjacent query tiles of a workgroup; turn, counted: see FwdParams
+Launch = namedtuple("Launch", "score head_dim waves heads tiles shares ring spare grid turn vt k8 counted")
 
 
 @functools.lru_cache(maxsize=None)
@@ -81,8 +81,8 @@ def _problem(b, n, hq, hkv, d, bm, seqlens, single_head, gate_mode, qk_fp8):
 
 def _noted(lib, rc):
     assert rc == 0, lib.bsfa_last_error()
-    x = lib.last_launch()[:14]
-    return Launch(bool(x[0]), *x[1:9], tuple(x[9:12]), bool(x[12]), bool(x[13]))
+    x = lib.last_launch()[:15]
+    return Launch(bool(x[0]), *x[1:9], tuple(x[9:12]), *map(bool, x[12:15]))
 
 
 def forward(b, n, hq, hkv, d, bm, causal=True, seqlens=False, single_head=False, gate_mode=0, qk_fp8=False, workspace=False):

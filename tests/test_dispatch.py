@@ -19,7 +19,7 @@ def test_split_where_nearly_every_place_is_taken(b, n, hq, hkv, d, seqlens, shar
 @pytest.mark.parametrize("b, n, hq, hkv, seqlens, tiles, shares", [
     (64, 100, 3, 3, False, 1, 1), (8, 250, 12, 4, False, 1, 1), (24, 190, 6, 2, False, 1, 1), (300, 60, 3, 1, False, 1, 1), (2000, 10, 3, 3, False, 1, 1),
     (4, 900, 16, 16, True, 1, 1), (3, 3000, 8, 8, True, 1, 1), (8, 500, 12, 4, True, 1, 1), (8, 500, 16, 16, True, 1, 1), (32, 200, 3, 1, True, 1, 1),
-    (64, 130, 3, 3, False, 2, 1), (4, 600, 28, 4, True, 2, 1), (16, 300, 12, 4, True, 2, 1), (2, 5000, 16, 16, True, 2, 1), (4, 450, 12, 4, False, 2, 2),
+    (64, 130, 3, 3, False, 2, 1), (64, 127, 6, 2, True, 2, 1), (4, 600, 28, 4, True, 2, 1), (16, 300, 12, 4, True, 2, 1), (2, 5000, 16, 16, True, 2, 1), (4, 450, 12, 4, False, 2, 2),
 ])
 def test_64_row_tiles_of_width_128(b, n, hq, hkv, seqlens, tiles, shares):
     """Tiles of an odd group: alone or with the next one in a workgroup."""
@@ -33,7 +33,7 @@ def test_short_chains_of_shared_heads_are_not_split():
 
 @pytest.mark.parametrize("b, n, hq, hkv, seqlens, tiles, shares", [
     (64, 130, 3, 3, False, 1, 1), (1, 1000, 40, 8, False, 1, 1), (200, 180, 3, 1, False, 1, 1), (150, 250, 3, 1, False, 1, 1),
-    (16, 300, 28, 4, True, 1, 1), (4, 900, 12, 4, True, 1, 1), (32, 200, 28, 4, True, 1, 1), (300, 60, 3, 3, False, 1, 1), (4, 2000, 16, 16, True, 1, 1),
+    (16, 300, 28, 4, True, 1, 1), (4, 900, 12, 4, True, 1, 1), (32, 200, 28, 4, True, 1, 1), (600, 128, 9, 3, True, 1, 1), (300, 60, 3, 3, False, 1, 1), (4, 2000, 16, 16, True, 1, 1),
     (100, 250, 3, 1, False, 2, 1), (2, 5000, 12, 4, True, 2, 1), (2, 4096, 12, 4, False, 2, 1), (4, 500, 12, 4, False, 1, 2),
 ])
 def test_64_row_tiles_of_width_64(b, n, hq, hkv, seqlens, tiles, shares):
@@ -99,3 +99,10 @@ def test_the_predicate_meets_adjacent_tiles(hq, hkv, d, bm):
 def test_lengths_meet_adjacent_tiles(hq, hkv, d, bm):
     x = dispatch.forward(len(on_small_tiles.LENGTHS), max(on_small_tiles.LENGTHS), hq, hkv, d, bm, seqlens=True)
     assert x.tiles == 128 // bm and x.shares == 1
+
+
+@pytest.mark.parametrize("hq, hkv, d, bm, n, lengths", on_gpu.IN_PLACE_ORDER + on_gpu.COUNTED_OFF)
+def test_work_items_of_elements_with_lengths(hq, hkv, d, bm, n, lengths):
+    """Counted off where more than one workgroup comes to a CU and the pairs of an XCD fit a row of lanes."""
+    x = dispatch.forward(len(lengths), n, hq, hkv, d, bm, seqlens=True)
+    assert x.counted == ((hq, hkv, d, bm, n, lengths) in on_gpu.COUNTED_OFF)

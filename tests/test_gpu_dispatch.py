@@ -187,13 +187,21 @@ def test_small_tiles_agree_with_every_other_form(case):
     test_small_calls_agree_with_every_other_form(case)
 
 
-@pytest.mark.parametrize("hq, hkv, d, bm, n, lengths", [
-    (4, 2, 128, 128, 500, [500, 500, 0, 131, 64]), (6, 3, 64, 64, 700, [700, 0, 1, 63, 699, 128]), (16, 8, 128, 64, 640, [640, 17, 320, 321]),
-    (3, 1, 128, 32, 450, [450, 33, 32]), (8, 8, 64, 32, 200, [0, 200, 64] * 8), (5, 5, 64, 128, 300, [300, 1, 256, 300, 255]), (2, 1, 128, 128, 260, [0, 0]),
-])
+IN_PLACE_ORDER = [
+    (4, 2, 128, 128, 500, [500, 500, 0, 131, 64]), (3, 1, 128, 32, 450, [450, 33, 32]), (8, 8, 64, 32, 200, [0, 200, 64] * 8),
+    (5, 5, 64, 128, 300, [300, 1, 256, 300, 255]), (2, 1, 128, 128, 260, [0, 0]),
+]
+COUNTED_OFF = [
+    (6, 3, 64, 64, 700, [700, 0, 1, 63, 699, 128]), (16, 8, 128, 64, 640, [640, 17, 320, 321]),
+    (24, 2, 128, 128, 500, [500, 500, 0, 131, 64]), (40, 1, 64, 128, 300, [300, 1, 256, 300, 255]), (64, 1, 128, 128, 260, [0, 0]), (32, 1, 128, 32, 450, [450, 33, 32]),
+    (8, 4, 128, 128, 1300, [1300, 1299, 640, 5]), (12, 4, 64, 32, 500, [500, 33, 32, 257]), (8, 8, 64, 64, 330, [0, 330, 64, 65] * 4),
+]
+
+
+@pytest.mark.parametrize("hq, hkv, d, bm, n, lengths", IN_PLACE_ORDER + COUNTED_OFF)
 def test_every_tile_of_elements_with_lengths_is_counted_off(hq, hkv, d, bm, n, lengths):
-    """Work items of batches whose elements end early, with pairs of element and KV head that fill the XCDs or do not, one and
-    many to an XCD (more than 16 too): outputs, masks and counts of every element are those of a call of its own (out and lse up
+    """Work items of batches whose elements end early, counted off or in the order of their places, with pairs of element and KV
+    head that fill the XCDs or do not, one and many to an XCD (more than 16 too): outputs, masks and counts of every element are those of a call of its own (out and lse up
     to rounding, where only one of the two splits its tiles; bounds as above), what lies beyond its end is untouched or empty."""
     q, k, v = make(len(lengths), n, hq, hkv, d, "bnhd", torch.bfloat16, n)
     tau = torch.full((hq,), 2.0, device=DEV)
