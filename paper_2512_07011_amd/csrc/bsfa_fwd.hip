@@ -31,13 +31,15 @@
 // operand is a plain 16-byte LDS read; without one it is gathered with the transposing read.
 //
 // What bounds it.  Long sequences: the matrix pipe at the clock the card holds under this load (a plain
-// library product reaches 1360 TFLOP/s here, this kernel 1060 to 1190 dense, busy in 58 to 65 % of the cycles) and
-// the issue of each wave: a stage takes a wave about 2900 cycles for 1024 of MFMA, whether a second one shares its
-// SIMD or not (a vector instruction 4.4 cycles, an exponential 8, a taken branch 30, dependent ones 8), so every
-// instruction in a wave's way counts, above all between the last score MFMA and the first PV MFMA of a block.  Two workgroups of four waves on a CU
+// library product reaches 1360 TFLOP/s here, this kernel 1060 to 1190 dense, busy in 58 to 65 % of the cycles: a key
+// block takes the two waves of a SIMD 3540 cycles at 8K tokens and 3160 at 128K, for 2048 of MFMA) and the issue of each
+// wave: of a stage that a wave alone on its SIMD needed 3165 cycles for, two side by side needed 3199 (counted in an
+// earlier kernel with the same stages; a vector instruction 4.4 cycles, an exponential 8, a taken branch 30, dependent
+// ones 8), so every instruction in a wave's way counts, above all between the last score MFMA and the first PV MFMA of a
+// block.  Two workgroups of four waves on a CU
 // (HP = 1) run independently and hide that stretch for each other; eight waves that share a K/V stream
 // (HP = 2) all stand at the same barrier, but read half as much from L2 (see launch_forward for the line).
-// Short sequences: the chain of key blocks of the longest tile, about 1.6 us a block.
+// Short sequences: the chain of key blocks of the longest tile, about a microsecond a block (64 blocks 66.9 us).
 #include "bsfa_dev.h"
 #include <algorithm>
 
@@ -64,7 +66,7 @@ constexpr int min_waves(int d, int waves, int lds_bytes)
 // Workgroups a CU holds, as far as decode_work asks: tiles that are split are left as they are (turned_places)
 constexpr int places_of(int d, int waves, int shares) { return shares > 1 || waves != 4 ? 1 : d == 64 ? 3 : 2; }
 
-constexpr int k_slot_bytes(int d) { return d / 8 * kPitch16; }
+constexpr int k_slot_bytes(int d) { return d / 8 * kPitch16; }               // (an fp8 tile fills half of its slot)
 constexpr int v_slot_bytes(int d) { return d / 8 * v_pitch(d); }
 
 template <int D, int NWH, int HP, int QT, int KSP, int KR, bool CALIB, bool F16, bool VT, bool QK8>
@@ -119,9 +121,10 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
 
     const int64_t row0 = (int64_t)i * BM;                 // first query row of the tile
     // n_tok: tokens of this batch element; a sequence that does not fill its last query tile or key
-    // block behaves as if padded by repeating its last token (Section 4.3): loads of rows
-    // beyond the end read row n_tok - 1 instead, padded rows are not stored, and key blocks made
-    // of padding only are not visited (the causal mask hides them from every real row).
+    // block behaves as if padded by repeating its last token (Section 4.3): queries beyond the end are
+    // copies of row n_tok - 1 and not stored, key blocks made of padding only are not visited, and in the
+    // last real one the keys beyond the end are zeros (copies of the last token in the workspace's tiles),
+    // which the causal mask hides from every real row either way.
     const bool real_tile = QT == 1 || row0 < n_tok;       // (with QT > 1 the last tiles of a workgroup may lie beyond the sequence)
     const bool stat_lane = (wrow == 0 && lane == 0 && real_tile);   // one lane per head and tile writes statistics
     const int64_t stat_row = ((int64_t)b * p.hq + h) * p.mq + i;
@@ -560,7 +563,8 @@ __global__ void __launch_bounds__(NWH * HP * QT * KSP * 64, min_waves(D, NWH * H
     // Row sums of the rounded probabilities (the values the second MFMA multiplies).  The dot instructions run on the
     // matrix pipe: measured beside 32x32x16 MFMAs, each run of them stops the pipe for 12 cycles and 4 per instruction,
     // and a chain on one accumulator takes 8 per instruction.  So all sixteen together, on two accumulators, at a place
-    // where the pipe stands still anyway: behind the barrier, while the first V operands travel.
+    // where the pipe stands still anyway: behind the barrier, while the first V operands travel.  (A block's sum is
+    // therefore added up in another order here than in softmax_exp, which differs by 32-bit rounding only.)
     auto row_sum = [&](bf16x8 (&pb)[4]) {
         asm volatile("" : "+v"(pb[0]), "+v"(pb[1]), "+v"(pb[2]), "+v"(pb[3]));
         float ps[2] = {0.f, 0.f};
@@ -1019,7 +1023,7 @@ static hipError_t launch_prepasses(const FwdParams &p, hipStream_t stream)
 // 64-row tiles, 2 x 4096 tokens of 12 heads over 4 (768 workgroups) 58.5 / 57.3 (73.8 / 67.7), 12 000 tokens (1128) 210 / 201,
 // 4096 tokens of 28 over 4 (896) 63.4 / 61.6; 32-row tiles, 3500 tokens of 32 over 8 57.0 / 54.5; head_dim 128, 32 over 8,
 // 2300 tokens (576) 47.4 / 46.7 (56.8 / 56.0), 4096 tokens (1024) 113.9 / 111.3 (148.2 / 141.4); 28 over 4, 4096 tokens in
-// 64-row tiles 105.8 / 103.5; at worst even (3500 tokens of 32 heads half skip 90.7 / 91.4, dense 117.1 / 112.1).  With more
+// 64-row tiles 105.8 / 103.5; at worst 0.8 % slower (3500 tokens of 32 heads half skip 90.7 / 91.4, dense 117.1 / 112.1).  With more
 // than that, what is dealt first is soon forgotten (6000 tokens of 32 heads 226 / 226), and tiles that are split are as short
 // as the call allows (2300 tokens of 12 over 4, head_dim 64, 29.3 / 31.8).
 static void turned_places(FwdParams &p, unsigned workgroups, int places)
@@ -1140,8 +1144,8 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //    workgroup of eight waves has a CU to itself.  One set against two, 128-row tiles:
 //     * as long as every workgroup has a place (8 heads over 2, 256 tiles): 1000 tokens 25.1 / 22.2, 2048 tokens
 //       37.6 / 31.7, 4096 tokens 66.9 / 53.1, 512 tokens dense 17.3 / 16.8.  (Below that the merge costs more than the
-//       chain, 300 tokens dense 12.3 / 12.6, 64 tokens 7.0 / 9.1, but a call then takes the host 11 us; and elements of
-//       a batch get the bits of a call of their own.)
+//       chain, 300 tokens dense 12.3 / 12.6, 64 tokens 7.0 / 9.1, but a call then takes the host 11 us; and an element
+//       gets the bits of a call of its own as long as the batch has no more workgroups than that.)
 //     * with up to two workgroups to a place it takes a chain of 20 blocks or more (8 x 1000 tokens of 8 heads, 512 tiles,
 //       27.3 / 31.7; 2 x 2048 tokens of 12 over 4, 384, 35.9 / 35.4, dense 42.8 / 39.1; 3000 tokens of 16 over 8, 384,
 //       48.4 / 41.5), and of 32 where nearly every place is taken (turned_places: 1700 tokens of 32 heads, 448 tiles,
@@ -1153,9 +1157,15 @@ bool shape_supported(int head_dim, int block_m, int block_n)
 //     * beyond that nothing is gained but for the longest chains (9 x 1536 tokens of 4 heads, whose KV heads lie
 //       unevenly on the XCDs, 35.4 / 46.4, 2125 tokens of 32 heads 44.1 / 51.4; 2 heads, 34K tokens 548 / 460), and
 //       from rows 65 536 on tiles are not split (2 heads, 49K tokens 918 / 950).
+//     * with lengths the lines count the longest element's tokens for every element, as nothing else is known here.  What a
+//       split gives there depends on the others: 4 x up to 3000 tokens of 8 heads, 768 tiles, 55.7 / 50.8, 2 x up to 3000 of 16 over
+//       8, 768, 62.7 / 70.6, 4 x up to 2000 of 16 over 8, 1024, 40.8 / 50.4.
 //  - Tiles of 64 and 32 rows: a workgroup takes several, so that it has the waves of a 128-row tile (narrow: of 64 rows) on
 //    one K/V stream.  What that leaves is the question above, with workgroups counted in 128 or in 64 rows (n128, n64; one
-//    set of waves on 128 rows / two on 128 / two on 64, at head_dim 64 four on 64 as well):
+//    set of waves on 128 rows / two on 128 / two on 64, at head_dim 64 four on 64 as well).  Figures of 64-row tiles; those of
+//    32 rows, on the same workgroups, lie up to 10 % above them on both sides of a line (2 x 1700 tokens of 12 over 4 34.9 / 30.6 /
+//    39.7 and 36.5 / 31.8 / 43.5; 3000 tokens of 20 over 4 57.6 / 53.6 / 73.9 and 59.5 / 56.4 / 79.4; width 64, 1100 tokens of 28 over
+//    4, one on 128 / two on 64 / four on 64, 19.5 / 14.2 / 19.8 and 20.0 / 15.2 / 20.5):
 //     * head_dim 128.  2 heads, 4800 tokens (n64 150) 76 / 56 / 46, 14 400 tokens (450) 211 / 148 / 126, 12 heads over 4, 2384
 //       tokens (456) 44 / 35.2 / 34.1; from n64 512 on a CU that holds two workgroups of 64 rows has a wave too few (2709 tokens,
 //       516: - / 39.1 / 43.0), and short chains gain less than the second workgroup costs (28 heads over 4, 1026 tokens, 476:
