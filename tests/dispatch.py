@@ -1,9 +1,11 @@
 """Which kernel a call is sent to, on the host: the library's own argument checks and dispatch (bsfa_api.hip and part 0 of
 bsfa_fwd.hip, compiled for the host alone), linked with launchers that note their template arguments and launch nothing."""
+import atexit
 import ctypes
 import functools
 import os
 import re
+import shutil
 import subprocess
 import tempfile
 from collections import namedtuple
@@ -51,6 +53,7 @@ Launch = namedtuple("Launch", "score head_dim waves heads tiles shares ring spar
 @functools.lru_cache(maxsize=None)
 def _lib():
     d = tempfile.mkdtemp(prefix="bsfa_dispatch_")
+    atexit.register(shutil.rmtree, d, ignore_errors=True)
     parts = re.findall(r"#define (BSFA_SHAPES_\d+)\(", open(os.path.join(build.CSRC, "bsfa_fwd.hip")).read())
     stub = os.path.join(d, "stub.hip")
     with open(stub, "w") as f:
